@@ -1208,22 +1208,24 @@ struct gks_trainer {
     float *X = nullptr, *Y = nullptr, *logit = nullptr;
     int32_t *perm = nullptr;
     float *P = nullptr, *g = nullptr, *mo = nullptr, *ve = nullptr;
-    float *H1 = nullptr, *H2 = nullptr, *D1 = nullptr, *D2 = nullptr, *DZ = nullptr, *L = nullptr, *loss = nullptr;
+    float *part = nullptr, *lpart = nullptr, *loss = nullptr;  // gradient and loss sums of a batch's blocks
     short *W1b = nullptr, *W2b = nullptr;
     std::vector<void *> owned;
 };
 
 namespace {
 
-// forward, back-propagation and weight gradients of the minibatch tr->perm[off .. off + B)
-void train_grad(gks_trainer *tr, int64_t off, int B, float *loss_out)
+int train_blocks(int B) { return std::min<int>(gks::TRAIN_MAX_BLOCKS, (int)blocks(B, gks::TRAIN_TILE)); }
+
+// forward, back-propagation and weight gradients of the minibatch tr->perm[off .. off + B): the mean
+// loss to loss_out, and the gradient to tr->g (adam null) or into an Adam step
+void train_batch(gks_trainer *tr, int64_t off, int B, float *loss_out, const gks::AdamArgs *adam)
 {
-    const int32_t *idx = tr->perm + off;
-    hipLaunchKernelGGL(gks::k_mlp_forward_delta, dim3(blocks(B, gks::TRAIN_BLOCK)), dim3(gks::TRAIN_BLOCK), 0,
-                       tr->stream, tr->P, tr->X, tr->Y, idx, B, tr->H1, tr->H2, tr->D1, tr->D2, tr->DZ, tr->L);
-    hipLaunchKernelGGL(gks::k_mlp_weight_grad, dim3(blocks(gks::MLP_NP, 64)), dim3(64), 0, tr->stream, tr->X, idx, B,
-                       tr->H1, tr->H2, tr->D1, tr->D2, tr->DZ, tr->g);
-    hipLaunchKernelGGL(gks::k_mean, dim3(1), dim3(256), 0, tr->stream, tr->L, B, loss_out);
+    const int nb = train_blocks(B);
+    hipLaunchKernelGGL(gks::k_mlp_batch, dim3(nb), dim3(256), 0, tr->stream, tr->P, tr->X, tr->Y, tr->perm + off, B,
+                       tr->part, tr->lpart);
+    hipLaunchKernelGGL(gks::k_mlp_reduce, dim3(blocks(gks::MLP_NP + 1, 64)), dim3(64), 0, tr->stream, tr->part, tr->lpart,
+                       nb, B, loss_out, adam ? nullptr : tr->g, adam ? *adam : gks::AdamArgs{});
 }
 
 gks_status trainer_logits(gks_trainer *tr)
@@ -1362,15 +1364,14 @@ gks_status gks_trainer_create(int64_t capacity, int32_t max_batch, const float *
             delete t;
             return fail(GKS_EDEVICE, "no HIP device");
         }
-        const size_t C = (size_t)capacity, B = (size_t)max_batch, NP = gks::MLP_NP;
+        const size_t C = (size_t)capacity, B = (size_t)train_blocks(max_batch), NP = gks::MLP_NP;
         struct Buf {
             void **p;
             size_t bytes;
         } bufs[] = {{(void **)&t->X, C * gks::MLP_IN * 4}, {(void **)&t->Y, C * 4}, {(void **)&t->logit, C * 4},
                     {(void **)&t->perm, C * 4}, {(void **)&t->P, NP * 4}, {(void **)&t->g, NP * 4},
-                    {(void **)&t->mo, NP * 4}, {(void **)&t->ve, NP * 4}, {(void **)&t->H1, B * gks::MLP_H * 4},
-                    {(void **)&t->H2, B * 64 * 4}, {(void **)&t->D1, B * 64 * 4}, {(void **)&t->D2, B * 64 * 4},
-                    {(void **)&t->DZ, B * 4}, {(void **)&t->L, B * 4}, {(void **)&t->loss, (C / 1 + 1) * 4},
+                    {(void **)&t->mo, NP * 4}, {(void **)&t->ve, NP * 4}, {(void **)&t->part, B * NP * 4},
+                    {(void **)&t->lpart, B * 4}, {(void **)&t->loss, (C / 1 + 1) * 4},
                     {(void **)&t->W1b, (size_t)gks::MLP_K * gks::MLP_H * 2},
                     {(void **)&t->W2b, (size_t)gks::MLP_H * gks::MLP_H * 2}};
         for (auto &b : bufs) {
@@ -1471,7 +1472,7 @@ gks_status gks_trainer_grad(gks_trainer *t, const int32_t *idx, int32_t B, float
             if (idx[i] < 0 || idx[i] >= t->n) return fail(GKS_EINVAL, "sample index out of range");
         HIP_OK(hipStreamSynchronize(t->stream));
         HIP_OK(hipMemcpy(t->perm, idx, (size_t)B * 4, hipMemcpyHostToDevice));
-        train_grad(t, 0, B, t->loss);
+        train_batch(t, 0, B, t->loss, nullptr);
         HIP_OK(hipGetLastError());
         HIP_OK(hipStreamSynchronize(t->stream));
         if (loss) HIP_OK(hipMemcpy(loss, t->loss, 4, hipMemcpyDeviceToHost));
@@ -1503,11 +1504,10 @@ gks_status gks_trainer_fit(gks_trainer *t, int32_t epochs, int32_t batch, float 
             for (int64_t k = 0; k < nb; k++) {
                 const int64_t off = k * batch;
                 const int B = (int)std::min<int64_t>(batch, n - off);
-                train_grad(t, off, B, t->loss + k);
                 t->adam_t++;
                 const float c1 = 1.f - std::pow(b1, (float)t->adam_t), c2 = 1.f - std::pow(b2, (float)t->adam_t);
-                hipLaunchKernelGGL(gks::k_adam, dim3(blocks(gks::MLP_NP, 256)), dim3(256), 0, t->stream, t->P, t->g, t->mo,
-                                   t->ve, lr, b1, b2, eps, c1, c2);
+                const gks::AdamArgs adam{t->P, t->mo, t->ve, lr, b1, b2, eps, c1, c2};
+                train_batch(t, off, B, t->loss + k, &adam);
             }
             HIP_OK(hipGetLastError());
             if (epoch_loss) {

@@ -9,8 +9,8 @@
 //             face neighbours' area ratios and the cell's edge lengths over hs (static, from the mesh)
 //   inference BF16 MFMA (v_mfma_f32_32x32x16_bf16), FP32 accumulation, 32 cells per wave; the
 //             44 inputs are padded with zeros to 48 (six K-steps of 8)
-//   training  FP32: per-sample forward and backward deltas, deterministic weight-gradient sums
-//             (one thread per parameter, fixed order over the batch), Adam
+//   training  FP32 on the matrix cores: tiles of 32 samples forward, backward and into block-wise
+//             weight-gradient sums, added in a fixed order (deterministic) by the Adam step
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -177,127 +177,174 @@ __global__ void k_u8_to_f32(const uint8_t *__restrict__ a, int64_t n, float *__r
 // ---------------------------------------------------------------------------------------------
 // training (FP32)
 
-constexpr int TRAIN_BLOCK = 128;
+constexpr int TRAIN_TILE = 32;          // samples a block takes through the network at a time
+constexpr int TRAIN_MAX_BLOCKS = 512;   // a larger batch loops over its tiles (bounds the partial sums)
+// LDS row strides of the tile's matrices: multiples of 4 whose sixteen first multiples are distinct
+// modulo the 64 banks, so that a 16 x 4 matrix-core operand (row * stride + 0..3) is conflict free
+constexpr int TX = 52, TH = MLP_H + 4;
 
-// per sample s of the batch (rows idx[s] of X, Y): forward pass, logistic loss L[s] and the
-// back-propagated pre-activation gradients of the mean loss, dz (output), D2, D1 (hidden layers);
-// keeps H1, H2 for the weight gradients.  Per-sample arrays are [B][64].
-__global__ void __launch_bounds__(TRAIN_BLOCK) k_mlp_forward_delta(const float *__restrict__ P,
-                                                                    const float *__restrict__ X,
-                                                                    const float *__restrict__ Y,
-                                                                    const int32_t *__restrict__ idx, int B,
-                                                                    float *__restrict__ H1, float *__restrict__ H2,
-                                                                    float *__restrict__ D1, float *__restrict__ D2,
-                                                                    float *__restrict__ DZ, float *__restrict__ L)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// acc[r] += A[i][k] B[k][j] over k = 0 .. 4 steps - 1 on one wave (v_mfma_f32_16x16x4_f32: lane l
+// supplies A row l % 16 and B column l % 16 at k = 4 step + l / 16, register r holds row
+// 4 (l / 16) + r, column l % 16).  Element strides: A (ai, ak), B (bk, bj).
+__device__ inline f32x4 tile_product(const float *A, int ai, int ak, const float *Bm, int bk, int bj, int steps,
+                                     int lane, f32x4 acc)
 {
-    __shared__ float Ps[MLP_NP];
-    for (int i = threadIdx.x; i < MLP_NP; i += blockDim.x) Ps[i] = P[i];
-    __syncthreads();
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= B) return;
-    const int64_t r = idx[s];
-    const float *x = X + r * MLP_IN;
-    float h1[MLP_H];
-    {
-        float xin[MLP_IN];
+    const int i = lane & 15, k = lane >> 4;
+    A += i * ai + k * ak;
+    Bm += i * bj + k * bk;
+    for (int s = 0; s < steps; s++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(A[4 * s * ak], Bm[4 * s * bk], acc, 0, 0, 0);
+    return acc;
+}
+
+// One minibatch (rows idx[0 .. B) of X, Y): forward pass, logistic loss, back-propagation and the
+// weight gradients of the mean loss, tile by tile of 32 samples held in LDS; each block leaves its
+// sums over its tiles in part[block][MLP_NP] and its loss sum in lpart[block], and k_mlp_reduce
+// adds the blocks in order (no atomics, the same bits every time).  All products run on the matrix
+// cores in FP32, column block w of every matrix on wave w.
+// What bounds it: a batch of 2048 is 86 MFLOP on 64 blocks, about 2 us of matrix work a block, so
+// launch and LDS latency.  One thread per parameter summing the batch serially (111 waves on the whole chip)
+// and a forward pass on 16 blocks took 526 + 79 us for 2048 samples.
+__global__ void __launch_bounds__(256) k_mlp_batch(const float *__restrict__ P, const float *__restrict__ X,
+                                                   const float *__restrict__ Y, const int32_t *__restrict__ idx, int B,
+                                                   float *__restrict__ part, float *__restrict__ lpart)
+{
+    __shared__ float w1[MLP_IN * TH], w2[MLP_H * TH], b1[MLP_H], b2[MLP_H], w3[MLP_H];
+    __shared__ float xs[TRAIN_TILE * TX], h1[TRAIN_TILE * TH], h2[TRAIN_TILE * TH], d1[TRAIN_TILE * TH],
+        d2[TRAIN_TILE * TH], dz[TRAIN_TILE], ls[TRAIN_TILE];
+    const int t = threadIdx.x, w = t >> 6, lane = t & 63, j0 = 16 * w;
+    const int col = lane & 15, row4 = 4 * (lane >> 4);
+    for (int i = t; i < MLP_IN * MLP_H; i += 256) w1[(i / MLP_H) * TH + i % MLP_H] = P[i];
+    for (int i = t; i < MLP_H * MLP_H; i += 256) w2[(i / MLP_H) * TH + i % MLP_H] = P[OFF_W2 + i];
+    if (t < MLP_H) {
+        b1[t] = P[OFF_B1 + t];
+        b2[t] = P[OFF_B2 + t];
+        w3[t] = P[OFF_W3 + t];
+    }
+    const float b3 = P[OFF_B3];
+    f32x4 g1[3] = {}, g2[4] = {};  // column block w of dW1 (44 rows padded to 48) and dW2
+    float gb = 0.f;                // threads 0..63 db1, 64..127 db2, 128..191 dw3, 192 db3, 193 the loss
+    for (int tile = blockIdx.x; tile * TRAIN_TILE < B; tile += gridDim.x) {
+        const int s0 = tile * TRAIN_TILE, ns = B - s0 < TRAIN_TILE ? B - s0 : TRAIN_TILE;
+        __syncthreads();
+        for (int i = t; i < TRAIN_TILE * 48; i += 256) {
+            const int r = i / 48, k = i % 48;
+            xs[r * TX + k] = (r < ns && k < MLP_IN) ? X[(int64_t)idx[s0 + r] * MLP_IN + k] : 0.f;
+        }
+        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < MLP_IN; i++) xin[i] = x[i];
+        for (int rb = 0; rb < 2; rb++) {
+            const f32x4 a = tile_product(xs + 16 * rb * TX, TX, 1, w1 + j0, TH, 1, MLP_IN / 4, lane, f32x4{0});
 #pragma unroll
-        for (int j = 0; j < MLP_H; j++) {
-            float a = Ps[OFF_B1 + j];
+            for (int r = 0; r < 4; r++) h1[(16 * rb + row4 + r) * TH + j0 + col] = fmaxf(a[r] + b1[j0 + col], 0.f);
+        }
+        __syncthreads();
 #pragma unroll
-            for (int i = 0; i < MLP_IN; i++) a = fmaf(xin[i], Ps[i * MLP_H + j], a);
-            h1[j] = fmaxf(a, 0.f);
+        for (int rb = 0; rb < 2; rb++) {
+            const f32x4 a = tile_product(h1 + 16 * rb * TH, TH, 1, w2 + j0, TH, 1, MLP_H / 4, lane, f32x4{0});
+#pragma unroll
+            for (int r = 0; r < 4; r++) h2[(16 * rb + row4 + r) * TH + j0 + col] = fmaxf(a[r] + b2[j0 + col], 0.f);
+        }
+        __syncthreads();
+        {  // output unit: eight threads a sample
+            const int s = t >> 3, q = t & 7;
+            float z = 0.f;
+#pragma unroll
+            for (int k = 0; k < 8; k++) z = fmaf(h2[s * TH + 8 * k + q], w3[8 * k + q], z);
+            z += __shfl_xor(z, 1);
+            z += __shfl_xor(z, 2);
+            z += __shfl_xor(z, 4);
+            z += b3;
+            const float y = s < ns ? Y[idx[s0 + s]] : 0.f;
+            // softplus(z) - y z, evaluated without overflow
+            const float L = fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))) - y * z;
+            const float e = s < ns ? (1.f / (1.f + expf(-z)) - y) / (float)B : 0.f;
+            if (q == 0) {
+                dz[s] = e;
+                ls[s] = s < ns ? L : 0.f;
+            }
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                const int j = 8 * k + q;
+                d2[s * TH + j] = h2[s * TH + j] > 0.f ? e * w3[j] : 0.f;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int rb = 0; rb < 2; rb++) {  // D2 W2^T
+            const f32x4 a = tile_product(d2 + 16 * rb * TH, TH, 1, w2 + j0 * TH, 1, TH, MLP_H / 4, lane, f32x4{0});
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const int i = (16 * rb + row4 + r) * TH + j0 + col;
+                d1[i] = h1[i] > 0.f ? a[r] : 0.f;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int rb = 0; rb < 3; rb++)
+            g1[rb] = tile_product(xs + 16 * rb, 1, TX, d1 + j0, TH, 1, TRAIN_TILE / 4, lane, g1[rb]);
+#pragma unroll
+        for (int rb = 0; rb < 4; rb++)
+            g2[rb] = tile_product(h1 + 16 * rb, 1, TH, d2 + j0, TH, 1, TRAIN_TILE / 4, lane, g2[rb]);
+        if (t < 192) {
+            const int j = t & 63;
+            for (int s = 0; s < TRAIN_TILE; s++)
+                gb += t < 64 ? d1[s * TH + j] : t < 128 ? d2[s * TH + j] : dz[s] * h2[s * TH + j];
+        } else if (t < 194) {
+            for (int s = 0; s < TRAIN_TILE; s++) gb += t == 192 ? dz[s] : ls[s];
         }
     }
-    float *h2o = H2 + (int64_t)s * MLP_H;
-    float z = Ps[OFF_B3];
-    for (int j = 0; j < MLP_H; j++) {
-        float a = Ps[OFF_B2 + j];
+    float *g = part + (int64_t)blockIdx.x * MLP_NP;
 #pragma unroll
-        for (int i = 0; i < MLP_H; i++) a = fmaf(h1[i], Ps[OFF_W2 + i * MLP_H + j], a);
-        const float h2 = fmaxf(a, 0.f);
-        h2o[j] = h2;
-        z = fmaf(h2, Ps[OFF_W3 + j], z);
-    }
-    const float y = Y[r];
-    // softplus(z) - y z, evaluated without overflow
-    L[s] = fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))) - y * z;
-    const float dz = (1.f / (1.f + expf(-z)) - y) / (float)B;
-    DZ[s] = dz;
-    float acc[MLP_H];
+    for (int rb = 0; rb < 3; rb++)
 #pragma unroll
-    for (int i = 0; i < MLP_H; i++) acc[i] = 0.f;
-    float *d2o = D2 + (int64_t)s * MLP_H;
-    for (int j = 0; j < MLP_H; j++) {
-        const float d2 = h2o[j] > 0.f ? dz * Ps[OFF_W3 + j] : 0.f;
-        d2o[j] = d2;
+        for (int r = 0; r < 4; r++) {
+            const int i = 16 * rb + row4 + r;
+            if (i < MLP_IN) g[i * MLP_H + j0 + col] = g1[rb][r];
+        }
 #pragma unroll
-        for (int i = 0; i < MLP_H; i++) acc[i] = fmaf(Ps[OFF_W2 + i * MLP_H + j], d2, acc[i]);
-    }
-    float *d1o = D1 + (int64_t)s * MLP_H, *h1o = H1 + (int64_t)s * MLP_H;
+    for (int rb = 0; rb < 4; rb++)
 #pragma unroll
-    for (int i = 0; i < MLP_H; i++) {
-        d1o[i] = h1[i] > 0.f ? acc[i] : 0.f;
-        h1o[i] = h1[i];
-    }
+        for (int r = 0; r < 4; r++) g[OFF_W2 + (16 * rb + row4 + r) * MLP_H + j0 + col] = g2[rb][r];
+    if (t < 193) g[t < 64 ? OFF_B1 + t : t < 128 ? OFF_B2 + t - 64 : t < 192 ? OFF_W3 + t - 128 : OFF_B3] = gb;
+    if (t == 193) lpart[blockIdx.x] = gb;
 }
 
-// one thread per parameter: sum over the batch in sample order (deterministic, no atomics)
-__global__ void k_mlp_weight_grad(const float *__restrict__ X, const int32_t *__restrict__ idx, int B,
-                                  const float *__restrict__ H1, const float *__restrict__ H2,
-                                  const float *__restrict__ D1, const float *__restrict__ D2,
-                                  const float *__restrict__ DZ, float *__restrict__ grad)
+struct AdamArgs {
+    float *P, *mo, *ve;
+    float lr, b1, b2, eps, c1, c2;  // c1, c2: 1 - b1^t, 1 - b2^t
+};
+
+// the blocks' partial sums in a fixed order: the mean loss, and the gradient (grad not null) or the
+// Adam step with it.  One thread per parameter, thread MLP_NP the loss.
+__global__ void __launch_bounds__(64) k_mlp_reduce(const float *__restrict__ part, const float *__restrict__ lpart, int nb,
+                                                   int B, float *__restrict__ loss, float *__restrict__ grad, AdamArgs o)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= MLP_NP) return;
-    float acc = 0.f;
-    if (p < OFF_B1) {
-        const int i = p / MLP_H, j = p % MLP_H;
-        for (int s = 0; s < B; s++) acc = fmaf(X[(int64_t)idx[s] * MLP_IN + i], D1[(int64_t)s * MLP_H + j], acc);
-    } else if (p < OFF_W2) {
-        const int j = p - OFF_B1;
-        for (int s = 0; s < B; s++) acc += D1[(int64_t)s * MLP_H + j];
-    } else if (p < OFF_B2) {
-        const int i = (p - OFF_W2) / MLP_H, j = (p - OFF_W2) % MLP_H;
-        for (int s = 0; s < B; s++) acc = fmaf(H1[(int64_t)s * MLP_H + i], D2[(int64_t)s * MLP_H + j], acc);
-    } else if (p < OFF_W3) {
-        const int j = p - OFF_B2;
-        for (int s = 0; s < B; s++) acc += D2[(int64_t)s * MLP_H + j];
-    } else if (p < OFF_B3) {
-        const int j = p - OFF_W3;
-        for (int s = 0; s < B; s++) acc = fmaf(DZ[s], H2[(int64_t)s * MLP_H + j], acc);
-    } else {
-        for (int s = 0; s < B; s++) acc += DZ[s];
+    if (p > MLP_NP) return;
+    const float *q = p < MLP_NP ? part + p : lpart;
+    const int64_t st = p < MLP_NP ? MLP_NP : 1;
+    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    int b = 0;
+    for (; b + 8 <= nb; b += 8)
+#pragma unroll
+        for (int k = 0; k < 8; k++) s[k] += q[(b + k) * st];
+    for (; b < nb; b++) s[0] += q[b * st];
+    const float g = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+    if (p == MLP_NP) {
+        loss[0] = g / (float)B;
+        return;
     }
-    grad[p] = acc;
-}
-
-__global__ void k_adam(float *__restrict__ P, const float *__restrict__ g, float *__restrict__ mo,
-                       float *__restrict__ ve, float lr, float b1, float b2, float eps, float c1, float c2)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= MLP_NP) return;
-    const float m = b1 * mo[p] + (1.f - b1) * g[p];
-    const float v = b2 * ve[p] + (1.f - b2) * g[p] * g[p];
-    mo[p] = m;
-    ve[p] = v;
-    P[p] -= lr * (m / c1) / (sqrtf(v / c2) + eps);
-}
-
-// mean of the per-sample losses (one block, fixed-order tree)
-__global__ void k_mean(const float *__restrict__ L, int B, float *__restrict__ out)
-{
-    __shared__ float sh[256];
-    float a = 0.f;
-    for (int i = threadIdx.x; i < B; i += 256) a += L[i];
-    sh[threadIdx.x] = a;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-        __syncthreads();
+    if (grad) {
+        grad[p] = g;
+        return;
     }
-    if (threadIdx.x == 0) out[0] = sh[0] / (float)B;
+    const float m = o.b1 * o.mo[p] + (1.f - o.b1) * g;
+    const float v = o.b2 * o.ve[p] + (1.f - o.b2) * g * g;
+    o.mo[p] = m;
+    o.ve[p] = v;
+    o.P[p] -= o.lr * (m / o.c1) / (sqrtf(v / o.c2) + o.eps);
 }
 
 }  // namespace gks

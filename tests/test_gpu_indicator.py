@@ -379,3 +379,23 @@ def test_indicator_at_full_size(gks):
     print(f"   rel-L1 full {ef:.2e} indicator {ei:.2e} skipped {k / sc.n_tri:.3f}", flush=True)
     assert ef <= TOL_FP32_REL_L1 and ei <= TOL_FP32_REL_L1, (ef, ei)
     assert k > 0.5 * sc.n_tri
+
+
+@pytest.mark.parametrize("B", [1, 31, 32, 33, 64, 1000, 16384, 16417])
+def test_trainer_gradient_at_the_tiles_edges(gks, B):
+    """Tiles of 32 samples, 512 blocks at most (beyond 16,384 samples a block takes several tiles).
+    Tolerance: a pre-activation sums 64 terms and a weight gradient 32 per tile, then the tiles, in
+    FP32; 64 * 2^-24 = 4e-6 for the first, the same again on the way back, and 2e-5 in all against
+    the largest entry."""
+    rng = np.random.default_rng(31)
+    X = rng.normal(0, 1, (B, o.MLP_IN)).astype(np.float32)
+    y = (rng.uniform(size=B) < 0.4).astype(np.uint8)
+    P = _random_params(33)
+    tr = gks.Trainer(B, P, max_batch=B)
+    tr.add(X, y)
+    idx = rng.permutation(B).astype(np.int32)
+    loss, g = tr.grad(idx)
+    lr, gr = o.mlp_grad(P.astype(np.float64), X[idx].astype(np.float64), y[idx].astype(np.float64))
+    assert abs(loss - lr) <= 2e-5 * max(1.0, abs(lr)), (B, loss, lr)
+    assert np.abs(g - gr).max() <= 2e-5 * np.abs(gr).max(), (B, np.abs(g - gr).max(), np.abs(gr).max())
+    assert np.array_equal(g, tr.grad(idx)[1])
