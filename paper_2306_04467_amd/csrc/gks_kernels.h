@@ -1792,6 +1792,30 @@ __global__ void __launch_bounds__(256) k_mass_partial(MeshDev m, const double *_
     }
 }
 
+// values [i0, i1) of the snapshot a caller reads: W [6][T] (h1 = eta1 - B), then gradW [6][2][T]
+// (grad h1 = grad eta1 - grad B), in double, into out[0 .. i1 - i0).  One read and one write per
+// value, coalesced; the host used to unpack and convert them component by component (31 ms on
+// 520,200 cells in FP64, of which the transfer over PCIe is 1.4 ms).
+template <typename R>
+__global__ void __launch_bounds__(256) k_snapshot(MeshDev m, const double *__restrict__ Wh, const R *__restrict__ Wm,
+                                                  const R *__restrict__ gW, int64_t i0, int64_t i1,
+                                                  double *__restrict__ out)
+{
+    const int64_t i = i0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= i1) return;
+    const int64_t T = m.T, TG = m.T + m.NG, row = i / T, c = i - row * T;
+    double x;
+    if (row < 6) {
+        const int v = (int)row;
+        x = v == 0 ? Wh[c] : v == 3 ? Wh[TG + c] - m.Bbar[c] : (double)Wm[mom_slot(v) * TG + c];
+    } else {
+        x = gW[(row - 6) * TG + c];
+        if (row == 12) x -= m.gB[c];
+        if (row == 13) x -= m.gB[T + c];
+    }
+    out[i - i0] = x;
+}
+
 // Per-step diagnostics of a scenario's cells [c0, c1) (Sec. 3.2's well-balance property: a lake
 // at rest keeps U = 0 and both levels flat): per block the largest speed |h U| / h of each layer
 // (desingularised in thin layers when h_dry > 0, as in the time step) and the largest and smallest
