@@ -107,8 +107,8 @@ struct gks_state {
     gks::MeshDev md{};
     gks::Phys p{};
     hipStream_t stream = nullptr;
-    double *Wh[2] = {nullptr, nullptr};
-    void *Wm[2] = {nullptr, nullptr}, *gW[2] = {nullptr, nullptr};
+    // LayerW[TG][2] and behind it in the same allocation LayerG[TG][2]
+    void *W[2] = {nullptr, nullptr}, *gW[2] = {nullptr, nullptr};
     double *Wc = nullptr, *hmid = nullptr, *gP1 = nullptr;
     double *eoh = nullptr;
     void *Gc = nullptr, *rec = nullptr, *r0 = nullptr, *eom = nullptr;  // rec: GpRec[6T]
@@ -191,21 +191,24 @@ void timed(gks_state *s, hipStream_t st, int kernel, F &&launch)
 }
 
 template <typename R, int SRC>
-void launch_recon(gks_state *s, int stage, hipStream_t st, const double *Whin, const R *Wmin, const R *gWin)
+void launch_recon(gks_state *s, int stage, hipStream_t st, const gks::LayerW<R> *Win, const gks::LayerG<R> *gWin)
 {
     const gks::MeshDev &m = s->md;
-    const dim3 g(blocks(m.T, gks::RECON_CELLS)), t(192);
+    const dim3 g(blocks(m.T, gks::RECON_CELLS)), t(64);
     R *src = SRC ? (R *)s->src : nullptr;
     if (s->ind_on) {
         const gks::IndArgs ia{s->ind_W1b, s->ind_W2b, s->ind_P, s->ind_thr, s->smooth};
         if (stage == 1)  // the second stage reuses the decisions of the step's first stage
-            hipLaunchKernelGGL((gks::k_recon<R, 2, SRC>), g, t, 0, st, m, s->p, Whin, Wmin, gWin, ia,
+            hipLaunchKernelGGL((gks::k_recon<R, 2, SRC>), g, t, 0, st, m, s->p, Win, gWin, ia,
                                recs_of<R>(s->rec, m.T), (R *)s->r0, src);
         else
-            hipLaunchKernelGGL((gks::k_recon<R, 1, SRC>), g, t, 0, st, m, s->p, Whin, Wmin, gWin, ia,
+            hipLaunchKernelGGL((gks::k_recon<R, 1, SRC>), g, t, 0, st, m, s->p, Win, gWin, ia,
                                recs_of<R>(s->rec, m.T), (R *)s->r0, src);
-    } else
-        hipLaunchKernelGGL((gks::k_recon<R, 0, SRC>), g, t, 0, st, m, s->p, Whin, Wmin, gWin, gks::IndArgs{},
+    } else if (SRC == 0 && s->p.h_dry > 0)
+        hipLaunchKernelGGL((gks::k_recon<R, 0, 0, 1>), g, t, 0, st, m, s->p, Win, gWin, gks::IndArgs{},
+                           recs_of<R>(s->rec, m.T), (R *)s->r0, src);
+    else
+        hipLaunchKernelGGL((gks::k_recon<R, 0, SRC>), g, t, 0, st, m, s->p, Win, gWin, gks::IndArgs{},
                            recs_of<R>(s->rec, m.T), (R *)s->r0, src);
 }
 
@@ -232,28 +235,28 @@ void launch_flux(gks_state *s, hipStream_t st)
 }
 
 template <typename R, int SRC, int GM>
-void launch_update_gm(gks_state *s, int stage, hipStream_t st, const double *Whin, const R *Wmin, const R *gWin,
-                      double *Whout, R *Wmout, R *gWout)
+void launch_update_gm(gks_state *s, int stage, hipStream_t st, const gks::LayerW<R> *Win, const gks::LayerG<R> *gWin,
+                      gks::LayerW<R> *Wout, gks::LayerG<R> *gWout)
 {
     const gks::MeshDev &m = s->md;
     const int b = s->bs[GKS_KERNEL_UPDATE];
     const R *src = SRC ? (const R *)s->src : nullptr;
     if (stage == 0)
         hipLaunchKernelGGL((gks::k_update<R, 0, SRC, GM>), dim3(blocks(m.T, b)), dim3(b), 0, st, m, s->p, s->eoh,
-                           (const R *)s->eom, Whin, Wmin, gWin, Whout, Wmout, gWout, s->Wc, (R *)s->Gc, src);
+                           (const R *)s->eom, Win, gWin, Wout, gWout, s->Wc, (R *)s->Gc, src);
     else
         hipLaunchKernelGGL((gks::k_update<R, 1, SRC, GM>), dim3(blocks(m.T, b)), dim3(b), 0, st, m, s->p, s->eoh,
-                           (const R *)s->eom, Whin, Wmin, gWin, Whout, Wmout, gWout, s->Wc, (R *)s->Gc, src);
+                           (const R *)s->eom, Win, gWin, Wout, gWout, s->Wc, (R *)s->Gc, src);
 }
 
 template <typename R, int SRC>
-void launch_update(gks_state *s, int stage, hipStream_t st, const double *Whin, const R *Wmin, const R *gWin,
-                   double *Whout, R *Wmout, R *gWout)
+void launch_update(gks_state *s, int stage, hipStream_t st, const gks::LayerW<R> *Win, const gks::LayerG<R> *gWin,
+                   gks::LayerW<R> *Wout, gks::LayerG<R> *gWout)
 {
     if (s->gm1)
-        launch_update_gm<R, SRC, 1>(s, stage, st, Whin, Wmin, gWin, Whout, Wmout, gWout);
+        launch_update_gm<R, SRC, 1>(s, stage, st, Win, gWin, Wout, gWout);
     else
-        launch_update_gm<R, SRC, 0>(s, stage, st, Whin, Wmin, gWin, Whout, Wmout, gWout);
+        launch_update_gm<R, SRC, 0>(s, stage, st, Win, gWin, Wout, gWout);
 }
 
 template <typename R>
@@ -261,20 +264,18 @@ void launch_stage(gks_state *s, int stage, hipStream_t st)
 {
     const gks::MeshDev &m = s->md;
     const int in = stage == 0 ? 0 : 1, out = 1 - in;
-    double *Whin = s->Wh[in];
-    R *Wmin = (R *)s->Wm[in], *gWin = (R *)s->gW[in];
-    double *Whout = s->Wh[out];
-    R *Wmout = (R *)s->Wm[out], *gWout = (R *)s->gW[out];
+    gks::LayerW<R> *Win = (gks::LayerW<R> *)s->W[in], *Wout = (gks::LayerW<R> *)s->W[out];
+    gks::LayerG<R> *gWin = (gks::LayerG<R> *)s->gW[in], *gWout = (gks::LayerG<R> *)s->gW[out];
     if (m.NG > 0)
         timed(s, st, GKS_KERNEL_GHOST, [&] {
             const int b = s->bs[GKS_KERNEL_GHOST];
-            hipLaunchKernelGGL(gks::k_ghost_fill<R>, dim3(blocks(m.NG, b)), dim3(b), 0, st, m, Whin, Wmin, gWin);
+            hipLaunchKernelGGL(gks::k_ghost_fill<R>, dim3(blocks(m.NG, b)), dim3(b), 0, st, m, Win, gWin);
         });
     timed(s, st, GKS_KERNEL_RECON, [&] {
         if (s->src4)
-            launch_recon<R, 1>(s, stage, st, Whin, Wmin, gWin);
+            launch_recon<R, 1>(s, stage, st, Win, gWin);
         else
-            launch_recon<R, 0>(s, stage, st, Whin, Wmin, gWin);
+            launch_recon<R, 0>(s, stage, st, Win, gWin);
     });
     timed(s, st, GKS_KERNEL_HHAT, [&] {
         const int b = s->bs[GKS_KERNEL_HHAT];
@@ -301,9 +302,9 @@ void launch_stage(gks_state *s, int stage, hipStream_t st)
     });
     timed(s, st, GKS_KERNEL_UPDATE, [&] {
         if (s->src4)
-            launch_update<R, 1>(s, stage, st, Whin, Wmin, gWin, Whout, Wmout, gWout);
+            launch_update<R, 1>(s, stage, st, Win, gWin, Wout, gWout);
         else
-            launch_update<R, 0>(s, stage, st, Whin, Wmin, gWin, Whout, Wmout, gWout);
+            launch_update<R, 0>(s, stage, st, Win, gWin, Wout, gWout);
     });
 }
 
@@ -313,12 +314,12 @@ void launch_dt(gks_state *s, hipStream_t st)
     const gks::MeshDev &m = s->md;
     timed(s, st, GKS_KERNEL_DT, [&] {
         if (m.S == 1) {
-            hipLaunchKernelGGL(gks::k_dt_partial<R>, dim3(s->nparts), dim3(gks::DT_BLOCK), 0, st, m, s->p, s->Wh[0],
-                               (const R *)s->Wm[0], s->part);
+            hipLaunchKernelGGL(gks::k_dt_partial<R>, dim3(s->nparts), dim3(gks::DT_BLOCK), 0, st, m, s->p,
+                               (const gks::LayerW<R> *)s->W[0], s->part);
             hipLaunchKernelGGL(gks::k_dt_final, dim3(1), dim3(gks::DT_BLOCK), 0, st, m, s->p, s->part, s->nparts);
         } else {
-            hipLaunchKernelGGL(gks::k_dt_chunk<R>, dim3(m.NCH), dim3(gks::DT_BLOCK), 0, st, m, s->p, s->Wh[0],
-                               (const R *)s->Wm[0], s->part);
+            hipLaunchKernelGGL(gks::k_dt_chunk<R>, dim3(m.NCH), dim3(gks::DT_BLOCK), 0, st, m, s->p,
+                               (const gks::LayerW<R> *)s->W[0], s->part);
             hipLaunchKernelGGL(gks::k_dt_scenario, dim3(m.S), dim3(64), 0, st, m, s->p, s->part);
         }
     });
@@ -341,16 +342,21 @@ void dt_any(gks_state *s, hipStream_t st)
 }
 
 // The least-squares operators as the reconstruction reads them: block-major, each block of
-// RECON_CELLS cells holding its 153 rows of RECON_CELLS entries as one contiguous span
-// ([ceil(T / RECON_CELLS)][153][RECON_CELLS], the last block padded with zeros), so that a block's
-// operators stream in as one piece.  The host mesh keeps them row-major [153][T].
+// RECON_CELLS cells one contiguous span of OP_LOADS loads of a wave ([OP_LOADS][RECON_CELLS][4], entry
+// 9 r + k for coefficient k and right-hand side r, padded with zeros), in the order of their use.  The
+// host mesh keeps them row-major [9 x 17][T].
 std::vector<double> operators_block_major(const gks::HostMesh &h)
 {
-    const int64_t T = h.nt, C = gks::RECON_CELLS, nb = (T + C - 1) / C;
-    std::vector<double> out((size_t)(nb * 153 * C), 0.0);
+    const int64_t T = h.nt, C = gks::RECON_CELLS, nb = (T + C - 1) / C, n = gks::OP_LOADS * 4 * C;
+    std::vector<double> out((size_t)(nb * n), 0.0);
     for (int64_t b = 0; b < nb; b++)
-        for (int64_t j = 0; j < 153; j++)
-            for (int64_t l = 0; l < C && b * C + l < T; l++) out[(size_t)((b * 153 + j) * C + l)] = h.M[(size_t)(j * T + b * C + l)];
+        for (int64_t r = 0; r < 17; r++)
+            for (int64_t k = 0; k < 9; k++) {
+                const int64_t i = 9 * r + k;
+                const double *from = &h.M[(size_t)((k * 17 + r) * T + b * C)];
+                double *to = &out[(size_t)(b * n + (i / 4 * C) * 4 + i % 4)];
+                for (int64_t l = 0; l < C && b * C + l < T; l++) to[4 * l] = from[l];
+            }
     return out;
 }
 
@@ -464,6 +470,17 @@ int64_t ckpt_bytes(const gks_state *s)
     return (int64_t)sizeof(CkptHeader) + 2 * TG * 8 + 16 * TG * rs + 2 * (int64_t)h.S * 8 + 8;
 }
 
+void launch_mass(const gks_state *s, int64_t c0, int64_t c1, double *part)
+{
+    const int b = s->half ? 1 : 0;
+    if (s->prec == GKS_FP64)
+        hipLaunchKernelGGL(gks::k_mass_partial<double>, dim3(256), dim3(256), 0, s->stream, s->md,
+                           (const gks::LayerW<double> *)s->W[b], c0, c1, part);
+    else
+        hipLaunchKernelGGL(gks::k_mass_partial<float>, dim3(256), dim3(256), 0, s->stream, s->md,
+                           (const gks::LayerW<float> *)s->W[b], c0, c1, part);
+}
+
 constexpr size_t PIN_BYTES = (size_t)1 << 20;   // the pinned page of a state
 constexpr size_t SLOT_BYTES = (size_t)1 << 20;  // a copying thread's pinned slot
 
@@ -574,12 +591,56 @@ gks_status copy_out(const gks_state *s, const double *src, void *dst, size_t byt
     return GKS_OK;
 }
 
+// the initial state as the device holds it (ghost cells zero)
 template <typename R>
-void to_real(const std::vector<double> &src, std::vector<unsigned char> &dst)
+gks_status device_state(const gks::HostMesh &h, const double *W0, const double *gradW0, bool may_be_dry,
+                        std::vector<unsigned char> &wb, std::vector<unsigned char> &gb)
 {
-    dst.resize(src.size() * sizeof(R));
-    R *p = reinterpret_cast<R *>(dst.data());
-    for (size_t i = 0; i < src.size(); i++) p[i] = (R)src[i];
+    const int64_t T = h.nt, TG = T + h.ng;
+    wb.assign((size_t)(2 * TG) * sizeof(gks::LayerW<R>), 0);
+    gb.assign((size_t)(2 * TG) * sizeof(gks::LayerG<R>), 0);
+    gks::LayerW<R> *w = reinterpret_cast<gks::LayerW<R> *>(wb.data());
+    gks::LayerG<R> *g = reinterpret_cast<gks::LayerG<R> *>(gb.data());
+    for (int v = 0; v < 6; v++) {
+        const int l = v / 3, q = v % 3;
+        for (int64_t c = 0; c < T; c++) {
+            const double x = W0[v * T + c];
+            // a layer thickness must be positive, or >= 0 with wet/dry layers
+            if (!std::isfinite(x) || (q == 0 && !(x > 0 || (may_be_dry && x >= 0))))
+                return fail(GKS_ENONFINITE, "bad initial value at component " + std::to_string(v) + ", cell " +
+                                                std::to_string(c));
+            if (q == 0) w[2 * c + l].h = l ? x + h.Bbar[c] : x;
+            else w[2 * c + l].m[q - 1] = (R)x;
+            for (int d = 0; d < 2; d++) {
+                const double y = gradW0[(2 * v + d) * T + c];
+                if (!std::isfinite(y)) return fail(GKS_ENONFINITE, "non-finite initial gradient");
+                g[2 * c + l].g[2 * q + d] = (R)(v == 3 ? y + h.gB[d * T + c] : y);
+            }
+        }
+    }
+    return GKS_OK;
+}
+
+size_t w_bytes(int prec, int64_t TG)
+{
+    return (size_t)(2 * TG) * (prec == GKS_FP64 ? sizeof(gks::LayerW<double>) : sizeof(gks::LayerW<float>));
+}
+
+// the state between the device's layout and a checkpoint's arrays (in device memory)
+void move_checkpoint(const gks_state *s, bool to_state, void *raw)
+{
+    const gks::MeshDev &m = s->md;
+    const dim3 g(blocks(18 * (m.T + m.NG), 256)), t(256);
+    auto go = [&](auto real) {
+        using R = decltype(real);
+        gks::LayerW<R> *W = (gks::LayerW<R> *)s->W[0];
+        gks::LayerG<R> *G = (gks::LayerG<R> *)s->gW[0];
+        if (to_state)
+            hipLaunchKernelGGL((gks::k_checkpoint<R, true>), g, t, 0, s->stream, m, W, G, raw);
+        else
+            hipLaunchKernelGGL((gks::k_checkpoint<R, false>), g, t, 0, s->stream, m, W, G, raw);
+    };
+    if (s->prec == GKS_FP64) go(double()); else go(float());
 }
 
 }  // namespace
@@ -711,24 +772,11 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
             if (r != GKS_OK) return r;
         }
         const int64_t T = h.nt, TG = T + h.ng, E = h.ne;
-        // host conversion: the device state carries eta1 = h1 + B and grad(eta1)
-        std::vector<double> wh(2 * TG, 0.0), wm(4 * TG, 0.0), g(12 * TG, 0.0);
-        for (int v = 0; v < 6; v++)
-            for (int64_t c = 0; c < T; c++) {
-                double x = W0[v * T + c];
-                // a layer thickness must be positive, or >= 0 with wet/dry layers
-                if (!std::isfinite(x) || ((v == 0 || v == 3) && !(x > 0 || (prm[0].h_dry > 0 && x >= 0))))
-                    return fail(GKS_ENONFINITE, "bad initial value at component " + std::to_string(v) + ", cell " +
-                                                    std::to_string(c));
-                if (v == 0) wh[c] = x;
-                else if (v == 3) wh[TG + c] = x + h.Bbar[c];
-                else wm[(v < 3 ? v - 1 : v - 2) * TG + c] = x;
-                for (int d = 0; d < 2; d++) {
-                    double y = gradW0[(2 * v + d) * T + c];
-                    if (!std::isfinite(y)) return fail(GKS_ENONFINITE, "non-finite initial gradient");
-                    g[(2 * v + d) * TG + c] = v == 3 ? y + h.gB[d * T + c] : y;
-                }
-            }
+        // host conversion: the device state carries eta1 = h1 + B and grad(eta1), by cell and layer
+        std::vector<unsigned char> w0, g0;
+        const gks_status conv = prec == GKS_FP64 ? device_state<double>(h, W0, gradW0, prm[0].h_dry > 0, w0, g0)
+                                                 : device_state<float>(h, W0, gradW0, prm[0].h_dry > 0, w0, g0);
+        if (conv != GKS_OK) return conv;
         gks_state *s = new gks_state();
         s->mesh = mesh;
         s->prec = prec;
@@ -742,8 +790,7 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
         struct Buf {
             void **p;
             size_t bytes;
-        } bufs[] = {{(void **)&s->Wh[0], 2 * uTG * 8}, {(void **)&s->Wh[1], 2 * uTG * 8}, {&s->Wm[0], 4 * uTG * rs},
-                    {&s->Wm[1], 4 * uTG * rs}, {&s->gW[0], 12 * uTG * rs}, {&s->gW[1], 12 * uTG * rs},
+        } bufs[] = {{&s->W[0], w_bytes(prec, TG) + 12 * uTG * rs}, {&s->W[1], w_bytes(prec, TG) + 12 * uTG * rs},
                     {(void **)&s->Wc, 6 * uT * 8}, {&s->Gc, 12 * uT * rs}, {&s->rec, 6 * uT * rec_bytes(prec)},
                     {&s->r0, 2 * uT * rs}, {(void **)&s->hmid, 2 * uE * 8},
                     {(void **)&s->gP1, 4 * uT * 8}, {(void **)&s->need, uT}, {(void **)&s->eoh, (s->gm1 ? 8 : 6) * uE * 8},
@@ -759,6 +806,7 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
             }
             s->owned.push_back(*b.p);
         }
+        for (int i = 0; i < 2; i++) s->gW[i] = static_cast<char *>(s->W[i]) + w_bytes(prec, TG);
         std::vector<double> chi(S), tend(S), scal(2 * S, 0.0);
         for (int32_t i = 0; i < S; i++) {
             chi[i] = prm[i].chi;
@@ -775,26 +823,16 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
         s->p.t_end = s->tend;
         s->p.scal = s->scal;
         s->p.bad = s->bad;
-        std::vector<unsigned char> bm, bg;
-        if (prec == GKS_FP64) {
-            to_real<double>(wm, bm);
-            to_real<double>(g, bg);
-        } else {
-            to_real<float>(wm, bm);
-            to_real<float>(g, bg);
-        }
         // a failed copy releases the partly built state
         const gks_status r = [&]() -> gks_status {
-            HIP_OK(hipMemcpy(s->Wh[0], wh.data(), wh.size() * 8, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(s->Wm[0], bm.data(), bm.size(), hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(s->gW[0], bg.data(), bg.size(), hipMemcpyHostToDevice));
+            HIP_OK(hipMemcpy(s->W[0], w0.data(), w0.size(), hipMemcpyHostToDevice));
+            HIP_OK(hipMemcpy(s->gW[0], g0.data(), g0.size(), hipMemcpyHostToDevice));
             HIP_OK(hipMemcpy(s->chi, chi.data(), S * 8, hipMemcpyHostToDevice));
             HIP_OK(hipMemcpy(s->tend, tend.data(), S * 8, hipMemcpyHostToDevice));
             HIP_OK(hipMemcpy(s->scal, scal.data(), 2 * S * 8, hipMemcpyHostToDevice));
             const unsigned long long none = ~0ull;
             HIP_OK(hipMemcpy(s->bad, &none, 8, hipMemcpyHostToDevice));
-            HIP_OK(hipMemset(s->Wh[1], 0, 2 * TG * 8));
-            HIP_OK(hipMemset(s->Wm[1], 0, 4 * TG * rs));
+            HIP_OK(hipMemset(s->W[1], 0, w_bytes(prec, TG)));
             HIP_OK(hipMemset(s->gW[1], 0, 12 * TG * rs));
             return GKS_OK;
         }();
@@ -970,11 +1008,11 @@ gks_status gks_state_read(const gks_state *s, double *W, double *gradW, double *
             const size_t i1 = std::min(last, i0 + cap_n);
             const dim3 g(blocks((int64_t)(i1 - i0), 256)), n(256);
             if (s->prec == GKS_FP64)
-                hipLaunchKernelGGL(gks::k_snapshot<double>, g, n, 0, s->stream, s->md, s->Wh[b], (const double *)s->Wm[b],
-                                   (const double *)s->gW[b], (int64_t)i0, (int64_t)i1, buf);
+                hipLaunchKernelGGL(gks::k_snapshot<double>, g, n, 0, s->stream, s->md, (const gks::LayerW<double> *)s->W[b],
+                                   (const gks::LayerG<double> *)s->gW[b], (int64_t)i0, (int64_t)i1, buf);
             else
-                hipLaunchKernelGGL(gks::k_snapshot<float>, g, n, 0, s->stream, s->md, s->Wh[b], (const float *)s->Wm[b],
-                                   (const float *)s->gW[b], (int64_t)i0, (int64_t)i1, buf);
+                hipLaunchKernelGGL(gks::k_snapshot<float>, g, n, 0, s->stream, s->md, (const gks::LayerW<float> *)s->W[b],
+                                   (const gks::LayerG<float> *)s->gW[b], (int64_t)i0, (int64_t)i1, buf);
             HIP_OK(hipGetLastError());
             const size_t m0 = std::min(std::max(6 * T, i0), i1);  // W before it, gradW from it on
             const Piece pw{buf, (m0 - i0) * 8, m0 > i0 ? W + i0 : nullptr};
@@ -1025,8 +1063,7 @@ gks_status gks_state_mass(const gks_state *s, int32_t scen, double mass[2])
         const int64_t c0 = scen < 0 ? 0 : h.scell[scen], c1 = scen < 0 ? h.nt : h.scell[scen + 1];
         constexpr int nb = 256;
         std::lock_guard<std::mutex> lock(s->io_mu);
-        hipLaunchKernelGGL(gks::k_mass_partial, dim3(nb), dim3(256), 0, s->stream, s->md, s->Wh[s->half ? 1 : 0], c0, c1,
-                           s->part);
+        launch_mass(s, c0, c1, s->part);
         HIP_OK(hipGetLastError());
         double part[2 * nb];
         unsigned long long bad = 0;
@@ -1051,14 +1088,14 @@ gks_status gks_state_diagnostics(const gks_state *s, int32_t scen, double out[8]
         constexpr int nb = 256;
         const int b = s->half ? 1 : 0;
         std::lock_guard<std::mutex> lock(s->io_mu);
-        hipLaunchKernelGGL(gks::k_mass_partial, dim3(nb), dim3(256), 0, s->stream, s->md, s->Wh[b], c0, c1, s->part);
+        launch_mass(s, c0, c1, s->part);
         HIP_OK(hipGetLastError());
         if (s->prec == GKS_FP64)
-            hipLaunchKernelGGL(gks::k_diag_partial<double>, dim3(nb), dim3(256), 0, s->stream, s->md, s->Wh[b],
-                               (const double *)s->Wm[b], c0, c1, s->p.h_dry, s->part + 2 * nb);
+            hipLaunchKernelGGL(gks::k_diag_partial<double>, dim3(nb), dim3(256), 0, s->stream, s->md,
+                               (const gks::LayerW<double> *)s->W[b], c0, c1, s->p.h_dry, s->part + 2 * nb);
         else
-            hipLaunchKernelGGL(gks::k_diag_partial<float>, dim3(nb), dim3(256), 0, s->stream, s->md, s->Wh[b],
-                               (const float *)s->Wm[b], c0, c1, s->p.h_dry, s->part + 2 * nb);
+            hipLaunchKernelGGL(gks::k_diag_partial<float>, dim3(nb), dim3(256), 0, s->stream, s->md,
+                               (const gks::LayerW<float> *)s->W[b], c0, c1, s->p.h_dry, s->part + 2 * nb);
         HIP_OK(hipGetLastError());
         double part[8 * nb], sc[2];
         unsigned long long bad = 0;
@@ -1140,12 +1177,14 @@ gks_status gks_state_save(const gks_state *s, void *blob, int64_t bytes)
         std::memcpy(p, &hd, sizeof(hd));
         p += sizeof(hd);
         HIP_OK(hipStreamSynchronize(s->stream));
-        HIP_OK(hipMemcpy(p, s->Wh[0], 2 * TG * 8, hipMemcpyDeviceToHost));
-        p += 2 * TG * 8;
-        HIP_OK(hipMemcpy(p, s->Wm[0], 4 * TG * rs, hipMemcpyDeviceToHost));
-        p += 4 * TG * rs;
-        HIP_OK(hipMemcpy(p, s->gW[0], 12 * TG * rs, hipMemcpyDeviceToHost));
-        p += 12 * TG * rs;
+        const size_t raw_bytes = 2 * (size_t)TG * 8 + 16 * (size_t)TG * rs;
+        // between steps the second stage's input (as large as the checkpoint's arrays) holds nothing
+        // that is read again: the arrays are put into the checkpoint's order there
+        move_checkpoint(s, false, s->W[1]);
+        HIP_OK(hipGetLastError());
+        HIP_OK(hipStreamSynchronize(s->stream));
+        HIP_OK(hipMemcpy(p, s->W[1], raw_bytes, hipMemcpyDeviceToHost));
+        p += raw_bytes;
         HIP_OK(hipMemcpy(p, s->scal, 2 * (size_t)h.S * 8, hipMemcpyDeviceToHost));
         p += 2 * (size_t)h.S * 8;
         HIP_OK(hipMemcpy(p, s->bad, 8, hipMemcpyDeviceToHost));
@@ -1167,12 +1206,12 @@ gks_status gks_state_load(gks_state *s, const void *blob, int64_t bytes)
         const int64_t TG = h.nt + h.ng, rs = s->prec == GKS_FP64 ? 8 : 4;
         const unsigned char *p = static_cast<const unsigned char *>(blob) + sizeof(hd);
         HIP_OK(hipStreamSynchronize(s->stream));
-        HIP_OK(hipMemcpy(s->Wh[0], p, 2 * TG * 8, hipMemcpyHostToDevice));
-        p += 2 * TG * 8;
-        HIP_OK(hipMemcpy(s->Wm[0], p, 4 * TG * rs, hipMemcpyHostToDevice));
-        p += 4 * TG * rs;
-        HIP_OK(hipMemcpy(s->gW[0], p, 12 * TG * rs, hipMemcpyHostToDevice));
-        p += 12 * TG * rs;
+        const size_t raw_bytes = 2 * (size_t)TG * 8 + 16 * (size_t)TG * rs;
+        HIP_OK(hipMemcpy(s->W[1], p, raw_bytes, hipMemcpyHostToDevice));
+        move_checkpoint(s, true, s->W[1]);
+        HIP_OK(hipGetLastError());
+        HIP_OK(hipStreamSynchronize(s->stream));
+        p += raw_bytes;
         HIP_OK(hipMemcpy(s->scal, p, 2 * (size_t)h.S * 8, hipMemcpyHostToDevice));
         p += 2 * (size_t)h.S * 8;
         HIP_OK(hipMemcpy(s->bad, p, 8, hipMemcpyHostToDevice));
@@ -1202,8 +1241,8 @@ gks_status read_buffer(const gks_state *s, int32_t which, void *dst)
         HIP_OK(hipMemcpy(tl.data(), rr.tail, tl.size() * sizeof(gks::GpTail<R>), hipMemcpyDeviceToHost));
         for (int64_t c = 0; c < T; c++)
             for (int slot = 0; slot < 6; slot++) {
-                const gks::GpHead<R> &h = hd[6 * c + slot];
-                const gks::GpTail<R> &t = tl[6 * c + slot];
+                const gks::GpHead<R> &h = hd[(size_t)gks::rec_at(T, c, slot / 2, slot % 2)];
+                const gks::GpTail<R> &t = tl[(size_t)gks::rec_at(T, c, slot / 2, slot % 2)];
                 if (which == GKS_BUF_RECH) {
                     for (int q = 0; q < 2; q++) static_cast<double *>(dst)[(slot * 2 + q) * T + c] = h.h[q];
                 } else {
@@ -1279,8 +1318,8 @@ void ghost_latest(gks_state *s, int b)
 {
     const gks::MeshDev &m = s->md;
     if (m.NG > 0)
-        hipLaunchKernelGGL(gks::k_ghost_fill<R>, dim3(blocks(m.NG, 256)), dim3(256), 0, s->stream, m, s->Wh[b],
-                           (R *)s->Wm[b], (R *)s->gW[b]);
+        hipLaunchKernelGGL(gks::k_ghost_fill<R>, dim3(blocks(m.NG, 256)), dim3(256), 0, s->stream, m,
+                           (gks::LayerW<R> *)s->W[b], (gks::LayerG<R> *)s->gW[b]);
 }
 
 template <typename R>
@@ -1289,7 +1328,7 @@ void launch_features(gks_state *s, float *X)
     const int b = s->half ? 1 : 0;
     ghost_latest<R>(s, b);
     hipLaunchKernelGGL(gks::k_features<R>, dim3(blocks(s->md.T, 256)), dim3(256), 0, s->stream, s->md, s->p.G,
-                       s->Wh[b], (const R *)s->Wm[b], (const R *)s->gW[b], X);
+                       (const gks::LayerW<R> *)s->W[b], (const gks::LayerG<R> *)s->gW[b], X);
 }
 
 template <typename R>
@@ -1301,12 +1340,20 @@ void launch_labels(gks_state *s, double tol)
     gks::Phys pn = s->p, pl = s->p;
     pn.linear = 0;
     pl.linear = 1;
-    const dim3 g(blocks(m.T, gks::RECON_CELLS)), t(192);
-    hipLaunchKernelGGL((gks::k_recon<R, 0>), g, t, 0, s->stream, m, pn, s->Wh[b], (const R *)s->Wm[b],
-                       (const R *)s->gW[b], gks::IndArgs{}, recs_of<R>(s->rec, m.T), (R *)s->r0, nullptr);
-    hipLaunchKernelGGL((gks::k_recon<R, 0>), g, t, 0, s->stream, m, pl, s->Wh[b], (const R *)s->Wm[b],
-                       (const R *)s->gW[b], gks::IndArgs{}, recs_of<R>(s->lab_rec, m.T), (R *)s->lab_r0, nullptr);
-    hipLaunchKernelGGL(gks::k_label<R>, dim3(blocks(m.T, 256)), dim3(256), 0, s->stream, m, s->p.G, tol, s->Wh[b],
+    const dim3 g(blocks(m.T, gks::RECON_CELLS)), t(64);
+    const gks::LayerW<R> *W = (const gks::LayerW<R> *)s->W[b];
+    const gks::LayerG<R> *gW = (const gks::LayerG<R> *)s->gW[b];
+    auto recon = [&](const gks::Phys &p, void *rec, void *r0) {
+        if (s->p.h_dry > 0)
+            hipLaunchKernelGGL((gks::k_recon<R, 0, 0, 1>), g, t, 0, s->stream, m, p, W, gW, gks::IndArgs{},
+                               recs_of<R>(rec, m.T), (R *)r0, nullptr);
+        else
+            hipLaunchKernelGGL((gks::k_recon<R, 0>), g, t, 0, s->stream, m, p, W, gW, gks::IndArgs{},
+                               recs_of<R>(rec, m.T), (R *)r0, nullptr);
+    };
+    recon(pn, s->rec, s->r0);
+    recon(pl, s->lab_rec, s->lab_r0);
+    hipLaunchKernelGGL(gks::k_label<R>, dim3(blocks(m.T, 256)), dim3(256), 0, s->stream, m, s->p.G, tol, W,
                        (const gks::GpHead<R> *)s->rec, (const gks::GpHead<R> *)s->lab_rec, s->lab_y);
 }
 
@@ -1434,14 +1481,14 @@ gks_status gks_indicator_eval(gks_state *s, float *logits, uint8_t *mask, int64_
         if (s->prec == GKS_FP64) {
             ghost_latest<double>(s, b);
             hipLaunchKernelGGL(gks::k_indicator<double>, dim3(blocks(m.T, 32 * gks::IND_WAVES)),
-                               dim3(64 * gks::IND_WAVES), 0, s->stream, m, s->p.G, s->Wh[b], (const double *)s->Wm[b],
-                               (const double *)s->gW[b], s->ind_W1b, s->ind_W2b, s->ind_P, s->ind_thr, s->smooth,
+                               dim3(64 * gks::IND_WAVES), 0, s->stream, m, s->p.G, (const gks::LayerW<double> *)s->W[b],
+                               (const gks::LayerG<double> *)s->gW[b], s->ind_W1b, s->ind_W2b, s->ind_P, s->ind_thr, s->smooth,
                                s->ind_logit);
         } else {
             ghost_latest<float>(s, b);
             hipLaunchKernelGGL(gks::k_indicator<float>, dim3(blocks(m.T, 32 * gks::IND_WAVES)),
-                               dim3(64 * gks::IND_WAVES), 0, s->stream, m, s->p.G, s->Wh[b], (const float *)s->Wm[b],
-                               (const float *)s->gW[b], s->ind_W1b, s->ind_W2b, s->ind_P, s->ind_thr, s->smooth,
+                               dim3(64 * gks::IND_WAVES), 0, s->stream, m, s->p.G, (const gks::LayerW<float> *)s->W[b],
+                               (const gks::LayerG<float> *)s->gW[b], s->ind_W1b, s->ind_W2b, s->ind_P, s->ind_thr, s->smooth,
                                s->ind_logit);
         }
         HIP_OK(hipGetLastError());
@@ -1733,15 +1780,15 @@ extern "C" gks_status gks_autotune(gks_state *s, int32_t reps, int32_t *chosen)
         const gks::HostMesh &h = s->mesh->host;
         const int64_t TG = h.nt + h.ng;
         const size_t rs = s->prec == GKS_FP64 ? 8 : 4;
-        const size_t nb[4] = {2 * (size_t)TG * 8, 4 * (size_t)TG * rs, 12 * (size_t)TG * rs, 2 * (size_t)h.S * 8};
-        void *src[4] = {s->Wh[0], s->Wm[0], s->gW[0], s->scal};
-        void *save[4] = {nullptr, nullptr, nullptr, nullptr};
+        const size_t nb[3] = {w_bytes(s->prec, TG), 12 * (size_t)TG * rs, 2 * (size_t)h.S * 8};
+        void *src[3] = {s->W[0], s->gW[0], s->scal};
+        void *save[3] = {nullptr, nullptr, nullptr};
         gks_status r = GKS_OK;
         HIP_OK(hipStreamSynchronize(s->stream));
-        for (int i = 0; i < 4 && r == GKS_OK; i++)
+        for (int i = 0; i < 3 && r == GKS_OK; i++)
             if (hipMalloc(&save[i], nb[i]) != hipSuccess) r = fail(GKS_ENOMEM, "autotune state copy");
         auto copy = [&](bool restore) {
-            for (int i = 0; i < 4; i++)
+            for (int i = 0; i < 3; i++)
                 (void)hipMemcpyAsync(restore ? src[i] : save[i], restore ? save[i] : src[i], nb[i], hipMemcpyDeviceToDevice,
                                      s->stream);
         };
@@ -1847,8 +1894,8 @@ extern "C" gks_status gks_state_mass_noalloc(const gks_state *s, int32_t scen, d
         const int64_t c0 = scen < 0 ? 0 : h.scell[scen], c1 = scen < 0 ? h.nt : h.scell[scen + 1];
         // every block writes its pair, so nothing needs clearing; the grid strides over any number
         // of cells, so every mesh fits the fixed-size scratch
-        hipLaunchKernelGGL(gks::k_mass_partial, dim3(MASS_PARTS), dim3(256), 0, s->stream, s->md,
-                           s->Wh[s->half ? 1 : 0], c0, c1, part_d);
+        static_assert(MASS_PARTS == 256, "the mass reduction's grid");
+        launch_mass(s, c0, c1, part_d);
         HIP_OK(hipGetLastError());
         double part[2 * MASS_PARTS];
         HIP_OK(hipMemcpyAsync(part, part_d, sizeof(part), hipMemcpyDeviceToHost, s->stream));

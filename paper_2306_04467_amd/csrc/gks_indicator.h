@@ -25,23 +25,21 @@ namespace gks {
 // variation, x[18] the size of the momentum variation.  Computed from the reconstruction's own
 // right-hand sides, with the arithmetic of the reconstruction kernel's fused indicator.
 template <typename R>
-__device__ inline void field_features(const MeshDev &m, double G, const double *__restrict__ Wh,
-                                      const R *__restrict__ Wm, const R *__restrict__ gW, int f, int64_t c, float *x)
+__device__ inline void field_features(const MeshDev &m, double G, const LayerW<R> *__restrict__ W,
+                                      const LayerG<R> *__restrict__ gW, int f, int64_t c, float *x)
 {
-    const int vt = f == 0 ? 3 : 0, vu = f == 0 ? 4 : 1;
-    ReconRhs<R> q, qu, qv;
-    recon_rhs<R>(m, Wh, Wm, gW, vt, true, c, q);
-    recon_rhs<R>(m, Wh, Wm, gW, vu, false, c, qu);
-    recon_rhs<R>(m, Wh, Wm, gW, vu + 1, false, c, qv);
-    const double h = f == 0 ? q.Q0h - m.Bbar[c] : q.Q0h;
-    thick_features<R>(q.rhs, q.Q0h, h, x);
-    x[18] = mom_feature(fmax(max_diff<R>(qu.rhs), max_diff<R>(qv.rhs)), h, G);
+    double Q0h;
+    R rhs[3][17];
+    recon_rhs<R>(m, W, gW, 1 - f, c, Q0h, rhs);
+    const double h = f == 0 ? Q0h - m.Bbar[c] : Q0h;
+    thick_features<R>(rhs[0], Q0h, h, x);
+    x[18] = mom_feature(fmax(max_diff<R>(rhs[1]), max_diff<R>(rhs[2])), h, G);
 }
 
 // all 44 features of cell c (training export)
 template <typename R>
-__global__ void k_features(MeshDev m, double G, const double *__restrict__ Wh, const R *__restrict__ Wm,
-                           const R *__restrict__ gW, float *__restrict__ X)
+__global__ void k_features(MeshDev m, double G, const LayerW<R> *__restrict__ W,
+                           const LayerG<R> *__restrict__ gW, float *__restrict__ X)
 {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= m.T) return;
@@ -49,7 +47,7 @@ __global__ void k_features(MeshDev m, double G, const double *__restrict__ Wh, c
 #pragma unroll
     for (int f = 0; f < 2; f++) {
         float y[19];
-        field_features<R>(m, G, Wh, Wm, gW, f, c, y);
+        field_features<R>(m, G, W, gW, f, c, y);
 #pragma unroll
         for (int k = 0; k < 17; k++) x[17 * f + k] = y[k];
         x[34 + f] = y[17];
@@ -66,8 +64,8 @@ __global__ void k_features(MeshDev m, double G, const double *__restrict__ Wh, c
 // the output layer).
 // Writes mask[c] = (logit > thr) and, when logit is not null, the logit.
 template <typename R>
-__global__ void __launch_bounds__(64 * IND_WAVES) k_indicator(MeshDev m, double G, const double *__restrict__ Wh,
-                                                               const R *__restrict__ Wm, const R *__restrict__ gW,
+__global__ void __launch_bounds__(64 * IND_WAVES) k_indicator(MeshDev m, double G, const LayerW<R> *__restrict__ W,
+                                                               const LayerG<R> *__restrict__ gW,
                                                                const short *__restrict__ W1b,
                                                                const short *__restrict__ W2b,
                                                                const float *__restrict__ P, float thr,
@@ -84,7 +82,7 @@ __global__ void __launch_bounds__(64 * IND_WAVES) k_indicator(MeshDev m, double 
     {
         float x[19];
         if (c < T) {
-            field_features<R>(m, G, Wh, Wm, gW, half, c, x);
+            field_features<R>(m, G, W, gW, half, c, x);
         } else {
 #pragma unroll
             for (int k = 0; k < 19; k++) x[k] = 0.f;
@@ -151,17 +149,17 @@ __global__ void __launch_bounds__(64 * IND_WAVES) k_mlp_infer(const float *__res
 // tol times the variable's scale (layer thickness, or h sqrt(G h) for momenta)
 
 template <typename R>
-__global__ void k_label(MeshDev m, double G, double tol, const double *__restrict__ Wh,
+__global__ void k_label(MeshDev m, double G, double tol, const LayerW<R> *__restrict__ W,
                         const GpHead<R> *__restrict__ rec_nl, const GpHead<R> *__restrict__ rec_li, uint8_t *__restrict__ y)
 {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= m.T) return;
-    const int64_t TG = m.T + m.NG;
-    const double h2 = Wh[c], h1 = Wh[TG + c] - m.Bbar[c];
+    const double h2 = W[2 * c].h, h1 = W[2 * c + 1].h - m.Bbar[c];
     const double sh[2] = {h2, h1}, sm[2] = {h2 * sqrt(G * h2), h1 * sqrt(G * h1)};
     bool ok = true;
     for (int slot = 0; slot < 6; slot++) {
-        const GpHead<R> &a = rec_nl[6 * c + slot], &b = rec_li[6 * c + slot];
+        const int64_t at = rec_at(m.T, c, slot / 2, slot % 2);
+        const GpHead<R> &a = rec_nl[at], &b = rec_li[at];
         for (int q = 0; q < 2; q++) ok = ok && fabs(a.h[q] - b.h[q]) <= tol * sh[q];
         for (int q = 0; q < 4; q++) ok = ok && fabs((double)a.q[q] - (double)b.q[q]) <= tol * sm[q / 2];
     }

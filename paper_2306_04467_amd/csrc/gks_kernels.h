@@ -8,11 +8,11 @@
 // sources).  What is computed in R there vanishes exactly at rest by left/right symmetry.
 //
 // Data layout:
-//   state  structure of arrays, index = component * stride + cell: Wh[2][TG] (double: h2, eta1),
-//          Wm[4][TG] (R: h2U2, h2V2, h1U1, h1V1), gW[12][TG] (R: x/y gradients of h2, h2U2, h2V2,
-//          eta1, h1U1, h1V1), TG = T + NG ghosts
-//   rec    GpHead[6 T] and GpTail[6 T], cell-major: the reconstruction at each cell's six Gauss
-//          points, read by the edge kernels as 16-byte words (one cache line per record)
+//   state  by cell, then layer (0 upper, 1 lower): LayerW W[TG][2] {h2 or eta1 in double, the two
+//          momenta}, LayerG G[TG][2] {x/y gradients of the three}, TG = T + NG ghosts: what the
+//          reconstruction gathers of a stencil cell lies in one or two cache lines
+//   rec    GpHead[6 T] and GpTail[6 T]: the reconstruction at each cell's six Gauss points, by local
+//          edge, then cell (rec_at), read by the edge kernels as 16-byte words
 //   eoh    [6][E] double: per edge, Gauss points averaged: 1/2 G hb^2 (upper, lower), hb (upper,
 //          lower), hb the interface thickness of the evolution, then the mean of the two sides'
 //          reconstructed thicknesses (upper, lower) for the layer coupling
@@ -33,7 +33,8 @@ struct MeshDev {
     // FP64 tables
     const double *area, *Bbar, *gB, *fl, *gg, *eBgp, *gR, *sdxmin;
     // tables in the bulk precision (double or float copies); M, the least-squares operators, is
-    // block-major [ceil(T / RECON_CELLS)][153][RECON_CELLS]
+    // block-major [ceil(T / RECON_CELLS)][OP_LOADS][RECON_CELLS][4]: entry 9 r + k of a cell's
+    // operator (coefficient k, right-hand side r) is entry 4 j + e of that order
     const void *M, *hs, *vtx, *nbc, *en, *egB;
     const float *igeo;              // [6][T] indicator geometry
     const uint8_t *cand;            // [T] plane candidates of the nonlinear reconstruction (bits 0..2)
@@ -127,8 +128,18 @@ __device__ inline int64_t xcd_block()
     return x * q + (x < r ? x : r) + j;
 }
 
-// the four momentum components in paper order 1, 2, 4, 5 -> slots 0..3 of Wm
-__device__ inline int mom_slot(int v) { return v < 3 ? v - 1 : v - 2; }
+// one layer of a cell: h2 and its momenta, or eta1 = h1 + B and the lower layer's momenta
+template <typename R>
+struct LayerW {
+    double h;
+    R m[2];
+};
+
+// x / y derivatives of the layer's three variables
+template <typename R>
+struct LayerG {
+    R g[6];
+};
 
 // a / b in the bulk precision: in FP32 the product with the hardware reciprocal (one instruction,
 // within about an ulp, where the correctly rounded quotient costs about ten; FP32 results are
@@ -137,9 +148,11 @@ __device__ inline float div_(float a, float b) { return a * __builtin_amdgcn_rcp
 __device__ inline double div_(double a, double b) { return a / b; }
 
 // Gauss-point records of one cell at one of its six Gauss points (slot = 2 * local edge + point),
-// written by the reconstruction and read by the edge kernels.  Records are stored cell-major,
-// index 6 c + slot, in two arrays: the head (thicknesses and momenta, all that the force model's
-// edge kernel reads) and the tail (gradients), so that each is read as a few 16-byte words.
+// written by the reconstruction and read by the edge kernels, in two arrays: the head (thicknesses
+// and momenta, all that the force model's edge kernel reads) and the tail (gradients), so that each is
+// read as a few 16-byte words.  Both are stored by local edge, then cell, then point (rec_at): the two
+// points an edge reads lie side by side, and a block of cells writes whole contiguous spans an
+// edge at a time.
 //   head.h[0] h2, head.h[1] eta1 = h1 + B (double in both precisions)
 //   head.q[0..3]  momenta h2U2, h2V2, h1U1, h1V1
 //   tail.g[2 v], tail.g[2 v + 1]  x / y derivative of paper component v (v = 0..5, eta1 for h1)
@@ -160,378 +173,394 @@ struct GpRecs {
     GpTail<R> *tail;
 };
 
+// index of the record of cell c at Gauss point g of its local edge k
+__host__ __device__ inline int64_t rec_at(int64_t T, int64_t c, int k, int g) { return 2 * (k * T + c) + g; }
+
 
 // --------------------------------------------------------------------------------------------
 // ghost mirror cells: state of the source cell seen through an orthogonal map
 
 template <typename R>
-__global__ void k_ghost_fill(MeshDev m, double *__restrict__ Wh, R *__restrict__ Wm, R *__restrict__ gW)
+__global__ void k_ghost_fill(MeshDev m, LayerW<R> *__restrict__ W, LayerG<R> *__restrict__ G)
 {
     int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= m.NG) return;
-    const int64_t TG = m.T + m.NG, s = GKS_IX(m.gsrc[g], m.T), d = m.T + g, NG = m.NG;
+    const int64_t s = GKS_IX(m.gsrc[g], m.T), d = m.T + g, NG = m.NG;
     // R (a b; c e) maps gradient directions, V (va vb; vc ve) momentum vectors: V = R across a
     // wall, V = I across a free boundary (each component extended evenly)
     const double a = m.gR[g], b = m.gR[NG + g], c = m.gR[2 * NG + g], e = m.gR[3 * NG + g];
     const double va = m.gR[4 * NG + g], vb = m.gR[5 * NG + g], vc = m.gR[6 * NG + g], ve = m.gR[7 * NG + g];
 #pragma unroll
-    for (int l = 0; l < 2; l++) {  // l = 0 upper (paper components 0..2), 1 lower (3..5)
-        const int o = 3 * l;
-        Wh[l * TG + d] = Wh[l * TG + s];
-        const double mx = Wm[(2 * l) * TG + s], my = Wm[(2 * l + 1) * TG + s];
-        Wm[(2 * l) * TG + d] = (R)(va * mx + vb * my);
-        Wm[(2 * l + 1) * TG + d] = (R)(vc * mx + ve * my);
-        const double hx = gW[(2 * o) * TG + s], hy = gW[(2 * o + 1) * TG + s];
-        gW[(2 * o) * TG + d] = (R)(a * hx + b * hy);
-        gW[(2 * o + 1) * TG + d] = (R)(c * hx + e * hy);
+    for (int l = 0; l < 2; l++) {
+        const LayerW<R> w = W[2 * s + l];
+        const LayerG<R> q = G[2 * s + l];
+        const double mx = w.m[0], my = w.m[1], hx = q.g[0], hy = q.g[1];
+        W[2 * d + l] = {w.h, {(R)(va * mx + vb * my), (R)(vc * mx + ve * my)}};
         // momentum gradient G[i][j] = d m_i / d x_j  ->  V G R^T
-        const double g00 = gW[(2 * o + 2) * TG + s], g01 = gW[(2 * o + 3) * TG + s];
-        const double g10 = gW[(2 * o + 4) * TG + s], g11 = gW[(2 * o + 5) * TG + s];
+        const double g00 = q.g[2], g01 = q.g[3], g10 = q.g[4], g11 = q.g[5];
         const double r00 = va * g00 + vb * g10, r01 = va * g01 + vb * g11;
         const double r10 = vc * g00 + ve * g10, r11 = vc * g01 + ve * g11;
-        gW[(2 * o + 2) * TG + d] = (R)(r00 * a + r01 * b);
-        gW[(2 * o + 3) * TG + d] = (R)(r00 * c + r01 * e);
-        gW[(2 * o + 4) * TG + d] = (R)(r10 * a + r11 * b);
-        gW[(2 * o + 5) * TG + d] = (R)(r10 * c + r11 * e);
+        G[2 * d + l] = {{(R)(a * hx + b * hy), (R)(c * hx + e * hy), (R)(r00 * a + r01 * b), (R)(r00 * c + r01 * e),
+                         (R)(r10 * a + r11 * b), (R)(r10 * c + r11 * e)}};
     }
 }
 
 // --------------------------------------------------------------------------------------------
-// compact reconstruction (Sec. 3.4): one thread per (cell, variable); 192 threads = 32 cells x 6.
-// Wave 0 holds the two thicknesses (h2, eta1), waves 1 and 2 the momenta of each layer, so a
-// wave never splits between the FP64 thickness path and the momentum path.
+// compact reconstruction (Sec. 3.4): one wave per 32 cells, lane l layer l % 2 of cell l / 2
 
 constexpr int RECON_CELLS = 32;
+constexpr int OP_LOADS = 39;  // loads of four operator entries per cell (153, padded to 156)
 
-// values of one variable at a cell's six Gauss points and its gradient there
-template <typename R>
-struct ReconOut {
-    // Gauss-point values: a thickness (h2, eta1) in double, a momentum in the bulk precision widened
-    // to double (exact); one array for both keeps every access at a constant index (registers)
-    double v[6];
-    R gx[6], gy[6];
-};
-
-// right-hand side of the least-squares system of variable v of cell c
-template <typename R>
-struct ReconRhs {
-    R rhs[17];  // average differences, then scaled gradients of the cell and its face neighbours
-    R hs, Q0;
-    double Q0h;  // cell average of a thickness in double
-    double hl;   // momenta: thickness of the variable's layer (scale of the smoothness floor)
-};
-
-template <typename R>
-__device__ inline void recon_rhs(const MeshDev &m, const double *__restrict__ Wh, const R *__restrict__ Wm,
-                                 const R *__restrict__ gW, int v, bool thick, int64_t c, ReconRhs<R> &q)
+// An operator load brings entries 4 j and 4 j + 1 to a cell's even lane and 4 j + 2 and 4 j + 3 to its
+// odd lane; both need all four: each entry is spread over the pair in registers (DPP), so that none is
+// fetched or held in flight twice.
+template <int ODD>
+__device__ inline uint32_t spread_pair(uint32_t x)
 {
-    const int64_t T = m.T, TG = m.T + m.NG;
-    const R hs = tab<R>(m.hs)[c];
-    // differences of thicknesses are taken in FP64 before rounding
-    double Q0h = 0;
-    R Q0 = 0;
-    R *rhs = q.rhs;
-    int32_t nb[9];
-#pragma unroll
-    for (int s = 0; s < 9; s++) nb[s] = GKS_IX(m.sten[s * T + c], T + m.NG);
-    // the level of the variable's layer (h2, or eta1 for the lower layer), loaded outside the
-    // branch so that a wave holding a thickness and a momentum issues it once: a thickness
-    // differences it, a momentum takes its layer's thickness from it
-    const double hq = Wh[(v < 3 ? 0 : TG) + c], bq = m.Bbar[c];
-    if (thick) {
-        const double *Q = Wh + (v == 3 ? TG : 0);
-        Q0h = hq;
-        Q0 = (R)Q0h;
-#pragma unroll
-        for (int s = 0; s < 9; s++) rhs[s] = (R)(Q[nb[s]] - Q0h);
-    } else {
-        const R *Q = Wm + mom_slot(v) * TG;
-        Q0 = Q[c];
-#pragma unroll
-        for (int s = 0; s < 9; s++) rhs[s] = Q[nb[s]] - Q0;
-    }
-    q.hl = v < 3 ? hq : hq - bq;
-    rhs[9] = hs * gW[(2 * v) * TG + c];
-    rhs[10] = hs * gW[(2 * v + 1) * TG + c];
-#pragma unroll
-    for (int l = 0; l < 3; l++) {
-        rhs[11 + 2 * l] = hs * gW[(2 * v) * TG + nb[l]];
-        rhs[12 + 2 * l] = hs * gW[(2 * v + 1) * TG + nb[l]];
-    }
-    q.hs = hs;
-    q.Q0 = Q0;
-    q.Q0h = Q0h;
+    constexpr int perm = ODD ? 0xF5 : 0xA0;  // quad_perm [1,1,3,3] or [0,0,2,2]
+    return __builtin_amdgcn_mov_dpp(x, perm, 0xF, 0xF, false);
 }
 
-// reconstruction of variable v of cell c: P^3 coefficients from its right-hand side (Ms points
-// at the cell's least-squares operator in LDS, entry j at Ms[32 j]), then the weights and the
-// Gauss-point values
-// coefficients k0 <= k < k1 of the P^3 fit; Ms holds the operator rows from row 17 k0 on
-template <int k0, int k1, typename R>
-__device__ inline void recon_coeffs(const ReconRhs<R> &q, const R *Ms, R a[9])
+template <int ODD>
+__device__ inline float spread_pair(float x)
 {
-#pragma unroll
-    for (int k = k0; k < k1; k++) {
-        R s = 0;
-#pragma unroll
-        for (int r = 0; r < 17; r++) s = fma(Ms[((k - k0) * 17 + r) * RECON_CELLS], q.rhs[r], s);
-        a[k] = s;
-    }
+    return __builtin_bit_cast(float, spread_pair<ODD>(__builtin_bit_cast(uint32_t, x)));
 }
 
-// the reconstruction from the P^3 coefficients a; lin: take the linear weights (no smoothness
-// indicators)
-// the combination that recon_cell settled on, for evaluations away from the Gauss points:
-// R(x) = Q0 + theta (ratio P(x) + sbx x + sby y) in scaled coordinates (P the zero-mean P^3 part)
-template <typename R>
-struct ReconComb {
-    R ratio, sbx, sby, theta;
-};
+template <int ODD>
+__device__ inline double spread_pair(double x)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    return __builtin_bit_cast(double, (uint64_t)spread_pair<ODD>((uint32_t)u) |
+                                          ((uint64_t)spread_pair<ODD>((uint32_t)(u >> 32)) << 32));
+}
 
+// right-hand sides of the least-squares systems of the three variables of layer l of cell c (training
+// features): average differences, then scaled gradients of the cell and its face neighbours
 template <typename R>
-__device__ inline void recon_cell(const MeshDev &m, const Phys &p, bool lin, R *__restrict__ r0, int v, bool thick,
-                                  int64_t c, const ReconRhs<R> &q, const R a[9], ReconOut<R> &out,
-                                  ReconComb<R> &comb)
+__device__ inline void recon_rhs(const MeshDev &m, const LayerW<R> *__restrict__ W, const LayerG<R> *__restrict__ G, int l,
+                                 int64_t c, double &Q0h, R rhs[3][17])
 {
     const int64_t T = m.T;
-    const R *rhs = q.rhs;
-    const R hs = q.hs, Q0 = q.Q0;
-    const double Q0h = q.Q0h;
-    // scaled vertices (centroid at the origin) and the cell means of the basis
-    const R *vt = tab<R>(m.vtx);
-    R vx[3], vy[3];
+    const R hs = tab<R>(m.hs)[c];
+    const LayerW<R> w0 = W[2 * c + l];
+    Q0h = w0.h;
+    int64_t nb[9];
 #pragma unroll
-    for (int k = 0; k < 3; k++) {
-        vx[k] = vt[(2 * k) * T + c];
-        vy[k] = vt[(2 * k + 1) * T + c];
+    for (int s = 0; s < 9; s++) {
+        nb[s] = GKS_IX(m.sten[s * T + c], T + m.NG);
+        const LayerW<R> w = W[2 * nb[s] + l];
+        // differences of thicknesses are taken in FP64 before rounding
+        rhs[0][s] = (R)(w.h - w0.h);
+        rhs[1][s] = w.m[0] - w0.m[0];
+        rhs[2][s] = w.m[1] - w0.m[1];
     }
-    R mxx = 0, mxy = 0, myy = 0, mx3 = 0, mx2y = 0, mxy2 = 0, my3 = 0;
 #pragma unroll
-    for (int k = 0; k < 3; k++) {
-        mxx += vx[k] * vx[k];
-        mxy += vx[k] * vy[k];
-        myy += vy[k] * vy[k];
-        mx3 += vx[k] * vx[k] * vx[k];
-        mx2y += vx[k] * vx[k] * vy[k];
-        mxy2 += vx[k] * vy[k] * vy[k];
-        my3 += vy[k] * vy[k] * vy[k];
+    for (int k = 0; k < 4; k++) {
+        const LayerG<R> g = G[2 * (k == 0 ? c : nb[k - 1]) + l];
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+            rhs[q][9 + 2 * k] = hs * g.g[2 * q];
+            rhs[q][10 + 2 * k] = hs * g.g[2 * q + 1];
+        }
     }
-    const R c12 = R(1) / R(12), c30 = R(1) / R(30);
-    const R mean_const = a[2] * mxx * c12 + a[3] * mxy * c12 + a[4] * myy * c12 + a[5] * mx3 * c30 +
-                         a[6] * mx2y * c30 + a[7] * mxy2 * c30 + a[8] * my3 * c30;
+}
+
+// nothing is scheduled across this point: bounds what the scheduler holds in flight at once
+__device__ inline void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
+
+// Makes the compiler treat the values as computed here and new: what they come from is not moved
+// below this point, and what was computed from them before is formed again afterwards instead of
+// being held in registers meanwhile.
+template <typename R, int N>
+__device__ inline void settle(R (&v)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; i++) asm volatile("" : "+v"(v[i]));
+}
+
+// The reconstructions of the three variables of one layer (q = 0 the thickness, 1 and 2 the momenta)
+// in scaled coordinates, as deviations from the cell averages:
+//   ratio (P - mean) + sx x + sy y,  P = a0 x + a1 y + a2 x^2 + a3 xy + a4 y^2 + a5 x^3 + ... + a8 y^3
+// In FP64 the combination is folded into the coefficients (ratio = 1, sx = sy = 0, not stored): fewer
+// operations, and 18 registers less through the evaluation.  In FP32 it is not: the mixed path's rounding
+// is amplified at a few obtuse cells of jittered meshes until the smoothness floor holds it (1e-5 of the
+// variable), so that any other order of its FP32 operations gives gradients there that differ by as
+// much; the order is kept, expression by expression.
+template <typename R>
+constexpr bool FOLD = sizeof(R) == 8;
+
+template <typename R>
+struct Fit {
+    R a[3][9], mean[3];
+    R ratio[3], sx[3], sy[3];
+};
+
+// products that are rounded before they are added (no fused multiply-add)
+template <typename R>
+__device__ inline R rounded(R a, R b)
+{
+#pragma clang fp contract(off)
+    R p = a * b;
+    asm volatile("" : "+v"(p));
+    return p;
+}
+
+template <typename R>
+__device__ inline R fit_dev(const Fit<R> &f, int q, R x, R y, bool first = false)
+{
+    const R *a = f.a[q];
+    if constexpr (FOLD<R>) {
+        const R xx = x * x, yy = y * y;
+        return a[0] * x + a[1] * y + a[2] * xx + a[3] * (x * y) + a[4] * yy + (a[5] * x + a[6] * y) * xx +
+               (a[7] * x + a[8] * y) * yy - f.mean[q];
+    } else {
+        const R P = a[0] * x + a[1] * y + a[2] * x * x + a[3] * x * y + a[4] * y * y + a[5] * x * x * x +
+                    a[6] * x * x * y + a[7] * x * y * y + a[8] * y * y * y - f.mean[q];
+        return first ? fma(f.sy[q], y, fma(f.ratio[q], P, rounded(f.sx[q], x)))
+                     : fma(f.sy[q], y, fma(f.sx[q], x, rounded(f.ratio[q], P)));
+    }
+}
+
+// derivatives of P; in scaled coordinates
+template <typename R>
+__device__ inline R fit_px(const R *a, R x, R y)
+{
+    if constexpr (FOLD<R>)
+        return a[0] + a[2] * (2 * x) + a[3] * y + a[5] * (3 * (x * x)) + a[6] * (2 * x * y) + a[7] * (y * y);
+    else
+        return a[0] + 2 * a[2] * x + a[3] * y + 3 * a[5] * x * x + 2 * a[6] * x * y + a[7] * y * y;
+}
+
+template <typename R>
+__device__ inline R fit_py(const R *a, R x, R y)
+{
+    if constexpr (FOLD<R>)
+        return a[1] + a[3] * x + a[4] * (2 * y) + a[6] * (x * x) + a[7] * (2 * x * y) + a[8] * (3 * (y * y));
+    else
+        return a[1] + a[3] * x + 2 * a[4] * y + a[6] * x * x + 2 * a[7] * x * y + 3 * a[8] * y * y;
+}
+
+template <typename R>
+__device__ inline R fit_dx(const Fit<R> &f, int q, R x, R y, R ihs)
+{
+    const R P = fit_px(f.a[q], x, y);
+    if constexpr (FOLD<R>)
+        return P * ihs;
+    else
+        return (f.ratio[q] * P + f.sx[q]) * ihs;
+}
+
+template <typename R>
+__device__ inline R fit_dy(const Fit<R> &f, int q, R x, R y, R ihs)
+{
+    if constexpr (FOLD<R>) {
+        return fit_py(f.a[q], x, y) * ihs;
+    } else {
+        const R *a = f.a[q];
+        R P = fma(2 * a[4], y, a[1] + rounded(a[3], x)) + rounded(a[6] * x, x);
+        P = fma(3 * a[8] * y, y, fma(2 * a[7] * x, y, P));
+        return (f.ratio[q] * P + f.sy[q]) * ihs;
+    }
+}
+
+// The nonlinear weights of a layer's three variables from their P^3 coefficients f.a and the
+// differences that the plane candidates take, d[64 (5 q + i)], i = 0..2 to the face neighbours and 3, 4
+// the scaled gradient; completes f and returns the thickness's weight ratio omega_0 / d_0.
+template <typename R>
+__device__ inline R recon_weights(const Phys &p, bool lin, unsigned cmask, const R *nbc, int64_t T, unsigned cl, double Q0h,
+                                  double hl, const R Qm[2], const R vx[3], const R vy[3], const R *d, Fit<R> &f)
+{
+    // cell means of the basis (centroid at the origin)
+    {
+        R mxx = 0, mxy = 0, myy = 0, mx3 = 0, mx2y = 0, mxy2 = 0, my3 = 0;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            mxx += vx[k] * vx[k];
+            mxy += vx[k] * vy[k];
+            myy += vy[k] * vy[k];
+            mx3 += vx[k] * vx[k] * vx[k];
+            mx2y += vx[k] * vx[k] * vy[k];
+            mxy2 += vx[k] * vy[k] * vy[k];
+            my3 += vy[k] * vy[k] * vy[k];
+        }
+        const R c12 = R(1) / R(12), c30 = R(1) / R(30);
+#pragma unroll
+        for (int q = 0; q < 3; q++) {
+            const R *a = f.a[q];
+            f.mean[q] = a[2] * mxx * c12 + a[3] * mxy * c12 + a[4] * myy * c12 + a[5] * mx3 * c30 + a[6] * mx2y * c30 +
+                        a[7] * mxy2 * c30 + a[8] * my3 * c30;
+        }
+    }
     // lower-order candidates (reading of the nonlinear compact reconstruction): planes through
     // the averages of {0, f0, f1}, {0, f1, f2}, {0, f2, f0} and the cell's own gradient.  A
     // sub-stencil whose centroid offsets are nearly parallel is not a candidate (bit clear in
-    // m.cand, decided at setup in FP64): its plane would carry a huge slope into the combination
+    // cmask, decided at setup in FP64): its plane would carry a huge slope into the combination
     // below; its linear weight goes to P^3.
-    const R *nbc = tab<R>(m.nbc);
-    const unsigned cmask = m.cand[c] | 8u;  // the own-gradient plane is always a candidate
-    R bx[4], by[4];
-#pragma unroll
-    for (int s = 0; s < 3; s++) {
-        const int sa = s, sb = (s + 1) % 3;
-        const R ax_ = nbc[(2 * sa) * T + c], ay_ = nbc[(2 * sa + 1) * T + c];
-        const R bx_ = nbc[(2 * sb) * T + c], by_ = nbc[(2 * sb + 1) * T + c];
-        const R ra = rhs[sa], rb = rhs[sb];
-        const R invd = R(1) / (ax_ * by_ - ay_ * bx_);
-        const R inv = ((cmask >> s) & 1u) ? invd : R(0);  // excluded planes: slope 0, weight 0
-        bx[s] = (ra * by_ - ay_ * rb) * inv;
-        by[s] = (ax_ * rb - ra * bx_) * inv;
-    }
-    bx[3] = rhs[9];
-    by[3] = rhs[10];
+    cmask |= 8u;  // the own-gradient plane is always a candidate
     const int ncand = __builtin_popcount(cmask);
     const R d0 = ncand == 4 ? R(0.8) : ncand == 3 ? R(0.85) : ncand == 2 ? R(0.9) : R(0.95), dm = R(0.05);
-    R w0 = d0, wm[4];
-#pragma unroll
-    for (int s = 0; s < 4; s++) wm[s] = ((cmask >> s) & 1u) ? dm : R(0);
     const bool nonlinear = !p.linear && !lin;
+    R beta0[3] = {0, 0, 0};
     if (nonlinear) {
         // smoothness indicator of P^3 in scaled coordinates: the cell has area 1/2 there, so the
         // |Omega|^(|alpha|-1) weights become (1/2)^(|alpha|-1) and integrals are averages / 2.
         // First derivatives (quadratics): 6-point degree-4 rule; second (linear): edge midpoints.
         const R qa[2] = {R(0.445948490915964886), R(0.091576213509770743)};
         const R qw[2] = {R(0.223381589678011466), R(1.0 / 3.0 - 0.223381589678011466)};
-        R s1 = 0;
+        R s1[3] = {0, 0, 0}, s2[3] = {0, 0, 0};
 #pragma unroll
         for (int r = 0; r < 2; r++)
 #pragma unroll
             for (int j = 0; j < 3; j++) {
-                const R l0 = (j == 0) ? 1 - 2 * qa[r] : qa[r];
-                const R l1 = (j == 1) ? 1 - 2 * qa[r] : qa[r];
-                const R l2 = (j == 2) ? 1 - 2 * qa[r] : qa[r];
-                const R x = l0 * vx[0] + l1 * vx[1] + l2 * vx[2];
-                const R y = l0 * vy[0] + l1 * vy[1] + l2 * vy[2];
-                const R px = a[0] + 2 * a[2] * x + a[3] * y + 3 * a[5] * x * x + 2 * a[6] * x * y + a[7] * y * y;
-                const R py = a[1] + a[3] * x + 2 * a[4] * y + a[6] * x * x + 2 * a[7] * x * y + 3 * a[8] * y * y;
-                s1 += qw[r] * (px * px + py * py);
+                R x, y;
+                if constexpr (FOLD<R>) {  // (1 - 2 qa) v_j + qa (v_i + v_k), with v_i + v_k = -v_j about the centroid
+                    x = (1 - 3 * qa[r]) * vx[j];
+                    y = (1 - 3 * qa[r]) * vy[j];
+                } else {
+                    const R l0 = (j == 0) ? 1 - 2 * qa[r] : qa[r];
+                    const R l1 = (j == 1) ? 1 - 2 * qa[r] : qa[r];
+                    const R l2 = (j == 2) ? 1 - 2 * qa[r] : qa[r];
+                    x = l0 * vx[0] + l1 * vx[1] + l2 * vx[2];
+                    y = l0 * vy[0] + l1 * vy[1] + l2 * vy[2];
+                }
+#pragma unroll
+                for (int q = 0; q < 3; q++) {
+                    const R px = fit_px(f.a[q], x, y), py = fit_py(f.a[q], x, y);
+                    s1[q] += qw[r] * fma(px, px, rounded(py, py));
+                }
+                sched_fence();
             }
-        R s2 = 0;
 #pragma unroll
         for (int j = 0; j < 3; j++) {
             const R x = R(0.5) * (vx[j] + vx[(j + 1) % 3]), y = R(0.5) * (vy[j] + vy[(j + 1) % 3]);
-            const R pxx = 2 * a[2] + 6 * a[5] * x + 2 * a[6] * y;
-            const R pxy = a[3] + 2 * a[6] * x + 2 * a[7] * y;
-            const R pyy = 2 * a[4] + 2 * a[7] * x + 6 * a[8] * y;
-            s2 += (pxx * pxx + pxy * pxy + pyy * pyy) * (R(1) / R(3));
+#pragma unroll
+            for (int q = 0; q < 3; q++) {
+                const R *a = f.a[q];
+                const R pxx = 2 * a[2] + 6 * a[5] * x + 2 * a[6] * y;
+                const R pxy = a[3] + 2 * a[6] * x + 2 * a[7] * y;
+                const R pyy = 2 * a[4] + 2 * a[7] * x + 6 * a[8] * y;
+                s2[q] += fma(pyy, pyy, fma(pxx, pxx, rounded(pxy, pxy))) * (R(1) / R(3));
+            }
+            sched_fence();
         }
-        const R s3 = 36 * a[5] * a[5] + 4 * a[6] * a[6] + 4 * a[7] * a[7] + 36 * a[8] * a[8];
-        const R beta0 = R(0.5) * s1 + R(0.25) * s2 + R(0.125) * s3;
-        R tz = 0, bm[4];
 #pragma unroll
-        for (int s = 0; s < 4; s++) {
-            bm[s] = R(0.5) * (bx[s] * bx[s] + by[s] * by[s]);
-            tz += ((cmask >> s) & 1u) ? fabs(beta0 - bm[s]) : R(0);
+        for (int q = 0; q < 3; q++) {
+            const R *a = f.a[q];
+            const R s3 = fma(36 * a[8], a[8], fma(4 * a[7], a[7], fma(36 * a[5], a[5], rounded(4 * a[6], a[6]))));
+            beta0[q] = R(0.5) * s1[q] + R(0.25) * s2[q] + R(0.125) * s3;
         }
-        tz = ncand == 4 ? tz * R(0.25) : div_(tz, R(ncand));
-        // floor of the smoothness indicators with the variable's scale: the level of a thickness,
-        // 1e-8 h sqrt(G h) of the layer for a momentum
-        const R S2 = thick ? R(1e-20) : (R)(1e-16 * p.G * q.hl * q.hl * q.hl);
-        const R epsw = eps_rel<R>() * fmax(Q0 * Q0, S2);
-        const R t0 = d0 * (1 + div_(tz, beta0 + epsw));
-        R sum = t0, tm[4];
-#pragma unroll
-        for (int s = 0; s < 4; s++) {
-            tm[s] = ((cmask >> s) & 1u) ? dm * (1 + div_(tz, bm[s] + epsw)) : R(0);
-            sum += tm[s];
-        }
-        // where every unnormalised weight equals its linear weight (tau = 0, or tau / (beta + eps)
-        // below the rounding of 1), the weights are the linear ones, which sum to one: take them
-        // exactly instead of dividing by their rounded sum
-        bool lin = t0 == d0;
-#pragma unroll
-        for (int s = 0; s < 4; s++) lin = lin && tm[s] == wm[s];
-        const R isum = lin ? R(1) : div_(R(1), sum);
-        w0 = t0 * isum;
-#pragma unroll
-        for (int s = 0; s < 4; s++) wm[s] = tm[s] * isum;
     }
-    const R ratio = w0 / d0;
-    if (v == 3) r0[c] = ratio;
-    if (v == 0) r0[T + c] = ratio;
-    // combined polynomial R = ratio (P0 - sum dm Pm) + sum wm Pm, Pm = Q0 + b . x
-    R sbx = 0, sby = 0;
+    R ox[3], oy[3], inv[3];
 #pragma unroll
-    for (int s = 0; s < 4; s++) {
-        const R cm = wm[s] - ratio * (((cmask >> s) & 1u) ? dm : R(0));
-        sbx += cm * bx[s];
-        sby += cm * by[s];
+    for (int s = 0; s < 3; s++) {
+        ox[s] = (nbc + (2 * s) * T)[cl];
+        oy[s] = (nbc + (2 * s + 1) * T)[cl];
     }
-    const R ihs = div_(R(1), hs);
-    const R gs[2] = {R(0.5 - 0.28867513459481288225), R(0.5 + 0.28867513459481288225)};
-    // positivity safeguard (not in the paper): where a layer thickness at a Gauss point would fall
-    // below a tenth of the cell's average, the deviation from the average is scaled down
-    // (Zhang-Shu scaling) until it does not; the lower layer's thickness is eta1 minus the
-    // piecewise-linear bottom.  The factor is 1 at rest and in ordinary flows; it is formed in the
-    // bulk precision (it only decides how far to pull the values back).
-    const R hbar = (R)(v == 0 ? Q0h : Q0h - m.Bbar[c]), floor_h = R(0.1) * hbar;
-    const R gBx = v == 3 ? (R)m.gB[c] : R(0), gBy = v == 3 ? (R)m.gB[T + c] : R(0);
-    R theta = 1;
 #pragma unroll
-    for (int k = 0; k < 3; k++)
+    for (int s = 0; s < 3; s++) {
+        const int sb = (s + 1) % 3;
+        const R invd = R(1) / (ox[s] * oy[sb] - oy[s] * ox[sb]);
+        inv[s] = ((cmask >> s) & 1u) ? invd : R(0);  // excluded planes: slope 0, weight 0
+    }
+    R ratio0 = 1;
 #pragma unroll
-        for (int g = 0; g < 2; g++) {
-            const int k1 = (k + 1) % 3;
-            const R x = vx[k] + gs[g] * (vx[k1] - vx[k]);
-            const R y = vy[k] + gs[g] * (vy[k1] - vy[k]);
-            const R P = a[0] * x + a[1] * y + a[2] * x * x + a[3] * x * y + a[4] * y * y + a[5] * x * x * x +
-                        a[6] * x * x * y + a[7] * x * y * y + a[8] * y * y * y - mean_const;
-            const R Px = a[0] + 2 * a[2] * x + a[3] * y + 3 * a[5] * x * x + 2 * a[6] * x * y + a[7] * y * y;
-            const R Py = a[1] + a[3] * x + 2 * a[4] * y + a[6] * x * x + 2 * a[7] * x * y + 3 * a[8] * y * y;
-            // all candidates share the cell average Q0 (ratio + sum cm = 1)
-            const R dev = ratio * P + sbx * x + sby * y;
-            const int slot = 2 * k + g;
-            out.v[slot] = thick ? Q0h + (double)dev : (double)(Q0 + dev);
-            out.gx[slot] = (ratio * Px + sbx) * ihs;
-            out.gy[slot] = (ratio * Py + sby) * ihs;
-            if (thick && dev < 0) {
-                const R bdev = hs * (gBx * x + gBy * y);
-                theta = fmin(theta, fmax(R(0), div_(hbar - bdev - floor_h, -dev)));
+    for (int q = 0; q < 3; q++) {
+        R bx[4], by[4];
+#pragma unroll
+        for (int s = 0; s < 3; s++) {
+            const int sb = (s + 1) % 3;
+            const R ra = d[64 * (5 * q + s)], rb = d[64 * (5 * q + sb)];
+            bx[s] = fma(ra, oy[sb], -rounded(oy[s], rb)) * inv[s];
+            by[s] = fma(ox[s], rb, -rounded(ra, ox[sb])) * inv[s];
+        }
+        bx[3] = d[64 * (5 * q + 3)];
+        by[3] = d[64 * (5 * q + 4)];
+        R w0 = d0, wm[4];
+#pragma unroll
+        for (int s = 0; s < 4; s++) wm[s] = ((cmask >> s) & 1u) ? dm : R(0);
+        // FP64: the planes' slopes weighted by their linear weights and by the nonlinear ones, in place
+        // of the four weights
+        R lx = 0, ly = 0, nx = 0, ny = 0;
+        if constexpr (FOLD<R>) {
+#pragma unroll
+            for (int s = 0; s < 4; s++) {
+                lx += wm[s] * bx[s];
+                ly += wm[s] * by[s];
+            }
+            nx = lx;
+            ny = ly;
+        }
+        if (nonlinear) {
+            R tz = 0, bm[4];
+#pragma unroll
+            for (int s = 0; s < 4; s++) {
+                bm[s] = R(0.5) * (s < 3 ? fma(bx[s], bx[s], rounded(by[s], by[s])) : fma(by[s], by[s], rounded(bx[s], bx[s])));
+                tz += ((cmask >> s) & 1u) ? fabs(beta0[q] - bm[s]) : R(0);
+            }
+            if constexpr (FOLD<R>)
+                tz *= ncand == 4 ? R(0.25) : ncand == 3 ? R(1.0 / 3.0) : ncand == 2 ? R(0.5) : R(1);
+            else
+                tz = ncand == 4 ? tz * R(0.25) : div_(tz, R(ncand));
+            // floor of the smoothness indicators with the variable's scale: the level of a thickness,
+            // 1e-8 h sqrt(G h) of the layer for a momentum
+            const R Q0 = q == 0 ? (R)Q0h : Qm[q - 1];
+            const R S2 = q == 0 ? R(1e-20) : (R)(1e-16 * p.G * hl * hl * hl);
+            const R Q2 = fmax(Q0 * Q0, S2), epsw = rounded(eps_rel<R>(), Q2);
+            const R t0 = d0 * (1 + div_(tz, fma(eps_rel<R>(), Q2, beta0[q])));
+            R sum = t0, tm[4], sx = 0, sy = 0;
+            // where every unnormalised weight equals its linear weight (tau = 0, or tau / (beta + eps)
+            // below the rounding of 1), the weights are the linear ones, which sum to one: take them
+            // exactly instead of dividing by their rounded sum
+            bool same = t0 == d0;
+#pragma unroll
+            for (int s = 0; s < 4; s++) {
+                tm[s] = ((cmask >> s) & 1u) ? dm * (1 + div_(tz, bm[s] + epsw)) : R(0);
+                sum += tm[s];
+                same = same && tm[s] == wm[s];
+                if constexpr (FOLD<R>) {
+                    sx += tm[s] * bx[s];
+                    sy += tm[s] * by[s];
+                    if (s & 1) sched_fence();
+                }
+            }
+            const R isum = same ? R(1) : div_(R(1), sum);
+            w0 = t0 * isum;
+            if constexpr (FOLD<R>) {
+                nx = sx * isum;
+                ny = sy * isum;
+            } else {
+#pragma unroll
+                for (int s = 0; s < 4; s++) wm[s] = tm[s] * isum;
             }
         }
-    if (theta < R(1)) {
+        const R ratio = w0 / d0;
+        if (q == 0) ratio0 = ratio;
+        // combined polynomial R = ratio (P0 - sum dm Pm) + sum wm Pm, Pm = Q0 + b . x; all candidates
+        // share the cell average Q0 (the weights sum to one)
+        R sbx = 0, sby = 0;
+        if constexpr (FOLD<R>) {
+            sbx = nx - ratio * lx;
+            sby = ny - ratio * ly;
+            f.a[q][0] = ratio * f.a[q][0] + sbx;
+            f.a[q][1] = ratio * f.a[q][1] + sby;
 #pragma unroll
-        for (int slot = 0; slot < 6; slot++) {
-            out.v[slot] = Q0h + (double)theta * (out.v[slot] - Q0h);
-            out.gx[slot] *= theta;
-            out.gy[slot] *= theta;
-        }
-    }
-    comb.ratio = ratio;
-    comb.sbx = sbx;
-    comb.sby = sby;
-    comb.theta = theta;
-}
-
-// Higher-order layer coupling (Sec. 3.2, Eq. SWE-source-discretization, and its remark that more
-// integration points raise the order): the part of the cell average of h_a grad h_b that the
-// product of averages misses, mean((h_a - mean h_a) grad h_b), and its time derivative with the
-// thickness rate h_t = -div(h U), from the cell's own reconstructions.  Each variable thread
-// evaluates three numbers per interior point: a thickness its deviation from the cell average and
-// its gradient (the lower layer's thickness is eta1 minus the linear bottom), a momentum its
-// derivative along its own direction and that derivative's gradient (so the two momentum threads
-// of a layer sum to div(h U)).  Radon's 7-point rule is exact for these degree-5 products.
-// cell geometry for the interior evaluations: scaled vertices and the cell mean of P^3's
-// non-constant part (as in recon_cell)
-template <typename R>
-struct SrcGeo {
-    R vx[3], vy[3], mean_const, ihs;
-};
-
-template <typename R>
-__device__ inline void src_geo(const MeshDev &m, int64_t c, const R a[9], R hs, SrcGeo<R> &g)
-{
-    const R *vt = tab<R>(m.vtx);
-    R mxx = 0, mxy = 0, myy = 0, mx3 = 0, mx2y = 0, mxy2 = 0, my3 = 0;
+            for (int i = 2; i < 9; i++) f.a[q][i] *= ratio;
+            f.mean[q] *= ratio;
+        } else {
 #pragma unroll
-    for (int k = 0; k < 3; k++) {
-        const R vx = vt[(2 * k) * m.T + c], vy = vt[(2 * k + 1) * m.T + c];
-        g.vx[k] = vx;
-        g.vy[k] = vy;
-        mxx += vx * vx;
-        mxy += vx * vy;
-        myy += vy * vy;
-        mx3 += vx * vx * vx;
-        mx2y += vx * vx * vy;
-        mxy2 += vx * vy * vy;
-        my3 += vy * vy * vy;
-    }
-    const R c12 = R(1) / R(12), c30 = R(1) / R(30);
-    g.mean_const = a[2] * mxx * c12 + a[3] * mxy * c12 + a[4] * myy * c12 + a[5] * mx3 * c30 +
-                   a[6] * mx2y * c30 + a[7] * mxy2 * c30 + a[8] * my3 * c30;
-    g.ihs = div_(R(1), hs);
-}
-
-// three numbers of variable v at the scaled point (x, y), see the block comment above
-template <typename R>
-__device__ inline void src_point(const MeshDev &m, int v, bool thick, int64_t c, const R a[9],
-                                 const ReconComb<R> &cb, const SrcGeo<R> &g, R hs, R x, R y, R o[3])
-{
-    const R ihs = g.ihs;
-    const R Px = a[0] + 2 * a[2] * x + a[3] * y + 3 * a[5] * x * x + 2 * a[6] * x * y + a[7] * y * y;
-    const R Py = a[1] + a[3] * x + 2 * a[4] * y + a[6] * x * x + 2 * a[7] * x * y + 3 * a[8] * y * y;
-    if (thick) {
-        const R P = a[0] * x + a[1] * y + a[2] * x * x + a[3] * x * y + a[4] * y * y + a[5] * x * x * x +
-                    a[6] * x * x * y + a[7] * x * y * y + a[8] * y * y * y - g.mean_const;
-        o[0] = cb.theta * (cb.ratio * P + cb.sbx * x + cb.sby * y);
-        o[1] = cb.theta * (cb.ratio * Px + cb.sbx) * ihs;
-        o[2] = cb.theta * (cb.ratio * Py + cb.sby) * ihs;
-        if (v == 3) {  // h1 = eta1 - B: remove the linear bottom's deviation and slope
-            const R gBx = (R)m.gB[c], gBy = (R)m.gB[m.T + c];
-            o[0] -= hs * (gBx * x + gBy * y);
-            o[1] -= gBx;
-            o[2] -= gBy;
+            for (int s = 0; s < 4; s++) {
+                const R cm = wm[s] - ratio * (((cmask >> s) & 1u) ? dm : R(0));
+                sbx += cm * bx[s];
+                sby += cm * by[s];
+            }
+            f.ratio[q] = ratio;
+            f.sx[q] = sbx;
+            f.sy[q] = sby;
         }
-    } else {
-        const R Pxx = 2 * a[2] + 6 * a[5] * x + 2 * a[6] * y;
-        const R Pxy = a[3] + 2 * a[6] * x + 2 * a[7] * y;
-        const R Pyy = 2 * a[4] + 2 * a[7] * x + 6 * a[8] * y;
-        const bool dx = (v == 1 || v == 4);  // x-momentum: d/dx; y-momentum: d/dy
-        const R i2 = ihs * ihs;
-        o[0] = dx ? (cb.ratio * Px + cb.sbx) * ihs : (cb.ratio * Py + cb.sby) * ihs;
-        o[1] = cb.ratio * (dx ? Pxx : Pxy) * i2;
-        o[2] = cb.ratio * (dx ? Pxy : Pyy) * i2;
+        sched_fence();
     }
+    return ratio0;
 }
 
 // the learned indicator inside the reconstruction: bf16 weight matrices, FP32 parameters, logit
@@ -543,25 +572,17 @@ struct IndArgs {
     uint8_t *mask;
 };
 
-// IND: the learned indicator decides per cell whether the smoothness indicators are computed.
-// IND = 1: its 44 features come from the right-hand sides the block has gathered anyway; one wave
-// evaluates the network for the block's 32 cells on the matrix cores and the decisions go to
-// ind.mask.  IND = 2: the decisions are read from ind.mask (the network ran on the step's first
-// stage, the second reuses them).
-// SRC = 1: the block then also forms the interior correction of the higher-order layer coupling
-// (src[8][T], see src_point) in the LDS space the records used.
-// whether cell c lies in the front band of the layer of variable v (h2 for v < 3, the lower layer
-// eta1 - B for v >= 3); a wall ghost holds its cell's mirrored state and bottom
-__device__ inline bool wd_band(const MeshDev &m, const Phys &p, const double *__restrict__ Wh, int v, int64_t c)
+// whether cell c lies in the front band of the upper layer (h2) or the lower (eta1 - B); a wall ghost
+// holds its cell's mirrored state and bottom
+template <typename R>
+__device__ inline bool wd_band(const MeshDev &m, const Phys &p, const LayerW<R> *__restrict__ W, bool lower, int64_t c)
 {
     const int64_t T = m.T, TG = m.T + m.NG;
-    const bool lower = v >= 3;
-    const double *H = Wh + (lower ? TG : 0);
     double hk[4];
 #pragma unroll
     for (int l = 0; l < 4; l++) {
         const int64_t i = l == 0 ? c : (int64_t)GKS_IX(m.sten[(l - 1) * T + c], TG);
-        double h = H[i];
+        double h = W[2 * i + (lower ? 1 : 0)].h;
         if (lower) h -= m.Bbar[i < T ? i : (int64_t)GKS_IX(m.gsrc[i - T], T)];
         hk[l] = h;
     }
@@ -578,253 +599,360 @@ __device__ inline bool wd_band(const MeshDev &m, const Phys &p, const double *__
     return band;
 }
 
-template <typename R, int IND, int SRC = 0>
-__global__ void __launch_bounds__(192) k_recon(MeshDev m, Phys p, const double *__restrict__ Wh,
-                                               const R *__restrict__ Wm, const R *__restrict__ gW, IndArgs ind,
-                                               GpRecs<R> rec, R *__restrict__ r0, R *__restrict__ src)
+// One wave takes the 32 cells of a block of operators; a lane holds all three variables of its layer.
+//
+// Bound by the rate of issue and by the latency of the scattered reads, at the occupancy that the 27
+// coefficients a lane keeps allow (168 registers, three waves a SIMD in FP64; four in FP32), the
+// operators' stream (1,248 bytes a cell in FP64, 624 in FP32) beneath it.  With the state as one
+// array a variable, 15 scattered 8-byte reads a stencil cell kept the address units 78 % busy, and the
+// operators, staged by a block through LDS behind barriers, the reads, the arithmetic and the records
+// ran one after another (taking any of them out shortened the kernel by its own time).  Hence a layer's
+// averages and gradients each in one piece (one wide read a stencil cell), a wave to itself without a
+// barrier, the operators read straight into registers eight loads ahead and shared between a cell's two
+// lanes by DPP, and the records turned in LDS into whole lines.  520k cells, between events: FP64 285 us
+// before, 228 after; FP32 148, 128; 80k cells FP64 47.7, 39.8.  At 800 cells one wave's chain is all
+// there is, 11.4 before, 13.6 after; 20 loads ahead instead of eight leave that and all sizes unchanged
+// or slower (80k 46.5).
+// IND: the learned indicator decides per cell whether the smoothness indicators are computed.
+// IND = 1: its 44 features come from the right-hand sides the wave has gathered anyway; the wave
+// evaluates the network for its 32 cells on the matrix cores and the decisions go to ind.mask.
+// IND = 2: the decisions are read from ind.mask (the network ran on the step's first stage, the
+// second reuses them).
+// SRC = 1: the higher-order layer coupling (Sec. 3.2, Eq. SWE-source-discretization, and its remark
+// that more integration points raise the order): the part of the cell average of h_a grad h_b that
+// the product of averages misses, mean((h_a - mean h_a) grad h_b), and its time derivative with the
+// thickness rate h_t = -div(h U), from the cell's own reconstructions, into src[8][T].  Radon's
+// 7-point rule is exact for these degree-5 products; the two layers of a cell exchange their
+// gradients between their two lanes.
+// WD = 1: wet/dry layers (Phys::h_dry > 0), the front band's first-order reconstruction; it excludes
+// the indicator and the higher-order coupling (the library rejects the combinations).
+template <typename R, int IND, int SRC = 0, int WD = 0>
+__global__ void __launch_bounds__(64, (sizeof(R) == 8 ? 3 : 4)) k_recon(MeshDev m, Phys p, const LayerW<R> *__restrict__ W,
+                                              const LayerG<R> *__restrict__ G, IndArgs ind, GpRecs<R> rec,
+                                              R *__restrict__ r0, R *__restrict__ src)
 {
-    // LDS: first the block's 32 least-squares operators, loaded once with coalesced reads and
-    // shared by the six variable threads of each cell; then, in the same space, the indicator's
-    // features and hidden activations (with IND); then the block's 32 x 6 Gauss-point records
-    // (heads, then tails), each array written out as one contiguous span
-    constexpr int NR = RECON_CELLS * 6;
-    // the operator is staged in two parts (rows of coefficients 0..4, then the other 153 - ROWS1
-    // rows of 5..8), both loaded at once into registers, so that the LDS holds only the larger part
-    constexpr int ROWS1 = 5 * 17;
-    constexpr int MBYTES = ROWS1 * RECON_CELLS * (int)sizeof(R);
-    constexpr int OBYTES = NR * (int)(sizeof(GpHead<R>) + sizeof(GpTail<R>));
-    constexpr int IBYTES = IND == 1 ? RECON_CELLS * (FB + HB) * 2 + 4 * RECON_CELLS * 8 + RECON_CELLS : 0;
-    constexpr int B1 = MBYTES > OBYTES ? MBYTES : OBYTES, LBYTES = B1 > IBYTES ? B1 : IBYTES;
-    __shared__ uint4 lds[(LBYTES + 15) / 16];
-    R *Ms = reinterpret_cast<R *>(lds);
-    GpHead<R> *th = reinterpret_cast<GpHead<R> *>(lds);
-    GpTail<R> *tt = reinterpret_cast<GpTail<R> *>(th + NR);
-    const int lane = threadIdx.x & 31, wv = threadIdx.x >> 5;
-    const int v = (wv == 0) ? 0 : (wv == 1) ? 3 : (wv == 2) ? 1 : (wv == 3) ? 2 : (wv == 4) ? 4 : 5;
-    const bool thick = (v == 0 || v == 3);
-    const int64_t c0 = xcd_block() * RECON_CELLS, c = c0 + lane;
-    const int64_t T = m.T;
+    // LDS: the differences that the plane candidates take, put away here while the fit needs the
+    // registers; then, in the same space, the records of one local edge (two points) of the 32 cells,
+    // heads then tails, each cell's span padded by 8 bytes so that the lanes' 8-byte writes fall on
+    // different banks.  The indicator's features lie behind the differences, and behind those the
+    // thickness's right-hand side until the features are made of it, then the hidden activations.
+    constexpr int HB2 = 2 * (int)sizeof(GpHead<R>), TB2 = 2 * (int)sizeof(GpTail<R>);
+    constexpr int HS = HB2 + 8, TS = TB2 + 8;
+    constexpr int OBYTES = RECON_CELLS * (HS + TS), DBYTES = 15 * 64 * (int)sizeof(R);
+    constexpr int FBYTES = RECON_CELLS * FB * 2, QBYTES = 17 * 64 * (int)sizeof(R), ABYTES = RECON_CELLS * (HB * 2 + 1);
+    constexpr int IBYTES = DBYTES + (IND == 1 ? FBYTES + (QBYTES > ABYTES ? QBYTES : ABYTES) : 0);
+    __shared__ uint4 lds[((OBYTES > IBYTES ? OBYTES : IBYTES) + 15) / 16];
+    typedef R R2 __attribute__((ext_vector_type(2)));
+    const int lane = threadIdx.x >> 1, l = threadIdx.x & 1;
+    const bool lower = l == 1;
+    const int64_t T = m.T, TG = m.T + m.NG;
+    const int64_t blk = xcd_block(), c0 = blk * RECON_CELLS;
     const int ncell = T - c0 < RECON_CELLS ? (int)(T - c0) : RECON_CELLS;
     const bool valid = lane < ncell;
-    // the cell's own gathers are issued first, so that they overlap the operator staging
-    ReconRhs<R> q;
-    if (valid) recon_rhs<R>(m, Wh, Wm, gW, v, thick, c, q);
-    R a[9];
+    // lanes beyond the last cell compute it again and write nothing; a wave's cells lie at a uniform
+    // base plus a small index, so that the tables' addresses stay in scalar registers
+    const unsigned cl = (valid ? lane : ncell - 1) & (RECON_CELLS - 1);
+    const int64_t c = c0 + cl;
+    int32_t nb[9];
+#pragma unroll
+    for (int s = 0; s < 9; s++) nb[s] = GKS_IX((m.sten + s * T + c0)[cl], TG);
+    const R hs = (tab<R>(m.hs) + c0)[cl];
+    const LayerW<R> *Wl = W + l;
+    const LayerG<R> *Gl = G + l;
+    const LayerW<R> w0 = (W + 2 * c0)[2 * cl + l];
+    const double Q0h = w0.h, hl = lower ? Q0h - (m.Bbar + c0)[cl] : Q0h;
+    const R Qm[2] = {w0.m[0], w0.m[1]};
+    // made here, before the fit, the test holds one bit and not the stencil's addresses through it
+    const bool band = WD && wd_band(m, p, W, lower, c);
+    // P^3 coefficients: the operator's column r times the right-hand side's entry r of each variable
+    Fit<R> f;
+    auto &a = f.a;
+    R *d = reinterpret_cast<R *>(lds) + threadIdx.x;
+    R *rh = reinterpret_cast<R *>(reinterpret_cast<char *>(lds) + DBYTES + FBYTES) + threadIdx.x;
+    double td = 0, md = 0;  // largest differences of the thickness and of the momenta (features)
     {
-        // every load of the staging is issued before the first LDS write
-        constexpr int NM = 153 * RECON_CELLS, NM1 = ROWS1 * RECON_CELLS, IT = (NM + 191) / 192;
-        const R *M = tab<R>(m.M);
-        R buf[IT];
+        // Software pipeline: the operator's loads run AHEAD loads in front of their use and the gathers
+        // of an entry RHS_AHEAD entries in front; the scheduling fences keep the compiler from sinking
+        // them to their uses (a handful of loads in flight per wave instead of AHEAD + 3 RHS_AHEAD).
+        constexpr int AHEAD = 8, RHS_AHEAD = 3;
+        const R2 *M = reinterpret_cast<const R2 *>(m.M) + blk * (OP_LOADS * 64) + threadIdx.x;
+        R2 ring[AHEAD];
 #pragma unroll
-        for (int it = 0; it < IT; it++) {
-            const int i = (int)threadIdx.x + 192 * it, l = i % RECON_CELLS;
-            buf[it] = (i < NM && l < ncell) ? M[c0 * 153 + i] : R(0);  // block-major operators
-        }
+        for (int j = 0; j < AHEAD; j++) ring[j] = M[64 * j];
+        // what a stencil cell contributes: its averages (entries 0 to 8), or the gradients of the cell and
+        // its face neighbours (two entries each, 9 to 16)
+        LayerW<R> wq[RHS_AHEAD];
+        LayerG<R> gq[2];
 #pragma unroll
-        for (int it = 0; it < IT; it++) {
-            const int i = (int)threadIdx.x + 192 * it;
-            if (i < NM1) Ms[i] = buf[it];
-        }
-        __syncthreads();
-        if (valid) recon_coeffs<0, 5, R>(q, Ms + lane, a);
-        __syncthreads();
+        for (int s = 0; s < RHS_AHEAD; s++) wq[s] = Wl[2 * (int64_t)nb[s]];
+        R row[4];  // operator entries 4 j .. 4 j + 3 of the lane's cell
 #pragma unroll
-        for (int it = 0; it < IT; it++) {
-            const int i = (int)threadIdx.x + 192 * it;
-            if (i >= NM1 && i < NM) Ms[i - NM1] = buf[it];
+        for (int r = 0; r < 17; r++) {
+            R b[3];
+            if (r < 9) {
+                const LayerW<R> w = wq[r % RHS_AHEAD];
+                // differences of thicknesses are taken in FP64 before rounding
+                b[0] = (R)(w.h - Q0h);
+                b[1] = w.m[0] - Qm[0];
+                b[2] = w.m[1] - Qm[1];
+                if constexpr (IND == 1) {
+                    td = fmax(td, fabs((double)b[0]));
+                    md = fmax(md, fmax(fabs((double)b[1]), fabs((double)b[2])));
+                }
+                if (r + RHS_AHEAD < 9) wq[r % RHS_AHEAD] = Wl[2 * (int64_t)nb[r + RHS_AHEAD]];
+                if (r == 5) gq[0] = (G + 2 * c0)[2 * cl + l];
+                if (r == 7) gq[1] = Gl[2 * (int64_t)nb[0]];
+            } else {
+                const int k = (r - 9) / 2;
+#pragma unroll
+                for (int q = 0; q < 3; q++) b[q] = hs * gq[k & 1].g[2 * q + ((r - 9) & 1)];
+                if ((r == 10 || r == 12) && k < 2) gq[k & 1] = Gl[2 * (int64_t)nb[k + 1]];
+            }
+            if (r < 3 || r == 9 || r == 10) {
+#pragma unroll
+                for (int q = 0; q < 3; q++) d[64 * (5 * q + (r < 3 ? r : r - 6))] = b[q];
+            }
+            if constexpr (IND == 1) rh[64 * r] = b[0];
+#pragma unroll
+            for (int i = 0; i < 9; i++) {
+                const int e = 9 * r + i, j = e / 4;
+                if (e % 4 == 0) {
+                    const R2 v = ring[j % AHEAD];
+                    row[0] = spread_pair<0>((R)v[0]);
+                    row[1] = spread_pair<0>((R)v[1]);
+                    row[2] = spread_pair<1>((R)v[0]);
+                    row[3] = spread_pair<1>((R)v[1]);
+                    if (j + AHEAD < OP_LOADS) ring[j % AHEAD] = M[64 * (j + AHEAD)];
+                    sched_fence();
+                }
+#pragma unroll
+                for (int q = 0; q < 3; q++) a[q][i] = r == 0 ? row[e % 4] * b[q] : fma(row[e % 4], b[q], a[q][i]);
+            }
         }
-        __syncthreads();
-        if (valid) recon_coeffs<5, 9, R>(q, Ms + lane, a);
     }
+#pragma unroll
+    for (int q = 0; q < 3; q++) settle(a[q]);
     bool lin = false;
-    if constexpr (IND == 2) lin = valid && ind.mask[c] != 0;
+    if constexpr (IND == 2) lin = (ind.mask + c0)[cl] != 0;
     if constexpr (IND == 1) {
-        __syncthreads();  // the operators are no longer needed: the space holds the network's data
-        short(*feat)[FB] = reinterpret_cast<short(*)[FB]>(lds);
+        short(*feat)[FB] = reinterpret_cast<short(*)[FB]>(reinterpret_cast<char *>(lds) + DBYTES);
         short(*hid)[HB] = reinterpret_cast<short(*)[HB]>(&feat[RECON_CELLS][0]);
-        double *msc = reinterpret_cast<double *>(&hid[RECON_CELLS][0]);  // [4][32] momentum differences
-        uint8_t *skip = reinterpret_cast<uint8_t *>(msc + 4 * RECON_CELLS);
-        // thickness threads: their field's 17 features and size; momentum threads: their largest
-        // stencil difference
-        if (thick) {
-            const int f = v == 3 ? 0 : 1;
-            float x[18];
-            if (valid) {
-                const double h = f == 0 ? q.Q0h - m.Bbar[c] : q.Q0h;
-                thick_features<R>(q.rhs, q.Q0h, h, x);
-            } else {
+        uint8_t *skip = reinterpret_cast<uint8_t *>(&hid[RECON_CELLS][0]);
+        const int fl = lower ? 0 : 1;
+        {
+            const double s = td + 1e-12 * fabs(Q0h), is = 1.0 / s;
 #pragma unroll
-                for (int k = 0; k < 18; k++) x[k] = 0.f;
-            }
+            for (int k = 0; k < 17; k++) feat[lane][17 * fl + k] = to_bf16(thick_feature((double)rh[64 * k], is));
+            feat[lane][34 + fl] = to_bf16(size_feature(s, hl));
+        }
+        feat[lane][36 + fl] = to_bf16(mom_feature(md, hl, p.G));
+        if (lower) {
 #pragma unroll
-            for (int k = 0; k < 17; k++) feat[lane][17 * f + k] = to_bf16(x[k]);
-            feat[lane][34 + f] = to_bf16(x[17]);
-            if (f == 0) {
-#pragma unroll
-                for (int k = 0; k < 6; k++) feat[lane][38 + k] = to_bf16(valid ? m.igeo[k * T + c] : 0.f);
-            } else {
-#pragma unroll
-                for (int k = MLP_IN; k < MLP_K; k++) feat[lane][k] = 0;
-            }
+            for (int k = 0; k < 6; k++) feat[lane][38 + k] = to_bf16((m.igeo + k * T + c0)[cl]);
         } else {
-            msc[mom_slot(v) * RECON_CELLS + lane] = valid ? max_diff<R>(q.rhs) : 0.0;
-        }
-        __syncthreads();
-        if (thick) {  // the layer's momentum feature: lower layer with eta1, upper with h2
-            const int f = v == 3 ? 0 : 1, s0 = f == 0 ? 2 : 0;
-            float y = 0.f;
-            if (valid) {
-                const double h = f == 0 ? q.Q0h - m.Bbar[c] : q.Q0h;
-                const double sm = fmax(msc[s0 * RECON_CELLS + lane], msc[(s0 + 1) * RECON_CELLS + lane]);
-                y = mom_feature(sm, h, p.G);
-            }
-            feat[lane][36 + f] = to_bf16(y);
-        }
-        __syncthreads();
-        // waves 0 and 1 take one block of 32 hidden units each
-        const int hw = threadIdx.x >> 6, hl = threadIdx.x & 63;
-        if (hw < 2) mlp_layer1(feat, hid, hl, hw, ind.W1b, ind.P);
-        __syncthreads();
-        float *zp = reinterpret_cast<float *>(msc);  // [2][32] partial logits (msc is no longer read)
-        if (hw < 2) {
-            float z[16];
-            mlp_layer2(hid, hl, hw, ind.W2b, ind.P, z);
-            if ((hl & 31) == 0) {
-                const int half = hl >> 5;
 #pragma unroll
-                for (int r = 0; r < 16; r++) zp[hw * RECON_CELLS + 8 * (r / 4) + 4 * half + (r % 4)] = z[r];
-            }
+            for (int k = MLP_IN; k < MLP_K; k++) feat[lane][k] = 0;
         }
         __syncthreads();
-        if (threadIdx.x < RECON_CELLS) {
-            const float z = zp[threadIdx.x] + zp[RECON_CELLS + threadIdx.x] + ind.P[OFF_B3];
-            skip[threadIdx.x] = z > ind.thr ? 1 : 0;
+        mlp_layer1(feat, hid, threadIdx.x, 0, ind.W1b, ind.P);
+        sched_fence();
+        mlp_layer1(feat, hid, threadIdx.x, 1, ind.W1b, ind.P);
+        __syncthreads();
+        sched_fence();
+        float z[16];
+        mlp_layer2_out(hid, threadIdx.x, ind.W2b, ind.P, z);
+        sched_fence();
+        if ((threadIdx.x & 31) == 0) {
+            const int half = threadIdx.x >> 5;
+#pragma unroll
+            for (int r = 0; r < 16; r++) skip[8 * (r / 4) + 4 * half + (r % 4)] = z[r] > ind.thr ? 1 : 0;
         }
         __syncthreads();
         lin = skip[lane] != 0;
-        if (threadIdx.x < 32 && valid && ind.mask) ind.mask[c] = lin ? 1 : 0;
+        if (lower && valid) ind.mask[c] = lin ? 1 : 0;
     }
-    ReconOut<R> out;
-    ReconComb<R> comb;
-    if (valid) recon_cell<R>(m, p, lin, r0, v, thick, c, q, a, out, comb);
-    // wet/dry layers exclude the indicator and the higher-order coupling (the library rejects the
-    // combinations), so only the plain instance carries the band test and its registers
-    if (IND == 0 && SRC == 0 && p.h_dry > 0 && valid && wd_band(m, p, Wh, v, c)) {
-        // front band: the layer's cell average, thickness constant (the lower layer's level follows
-        // the bottom), momentum the thickness times the desingularised velocity; r0 = 0 marks it
-        const R *vt = tab<R>(m.vtx);
-        const R gs[2] = {R(0.5 - 0.28867513459481288225), R(0.5 + 0.28867513459481288225)};
-        const double gBx = v == 3 ? m.gB[c] : 0.0, gBy = v == 3 ? m.gB[T + c] : 0.0;
-        const double mv = thick ? 0.0 : q.hl * wd_velocity(q.hl, (double)q.Q0, p.h_dry);
+    // scaled vertices (centroid at the origin)
+    const R *vt = tab<R>(m.vtx) + c0;
+    R vx[3], vy[3];
 #pragma unroll
-        for (int k = 0; k < 3; k++)
-#pragma unroll
-            for (int g = 0; g < 2; g++) {
-                const int k1 = (k + 1) % 3, slot = 2 * k + g;
-                const R x = vt[(2 * k) * T + c] + gs[g] * (vt[(2 * k1) * T + c] - vt[(2 * k) * T + c]);
-                const R y = vt[(2 * k + 1) * T + c] + gs[g] * (vt[(2 * k1 + 1) * T + c] - vt[(2 * k + 1) * T + c]);
-                out.v[slot] = thick ? q.Q0h + (double)q.hs * (gBx * (double)x + gBy * (double)y) : mv;
-                out.gx[slot] = (R)gBx;
-                out.gy[slot] = (R)gBy;
-            }
-        if (v == 3) r0[c] = R(0);
-        if (v == 0) r0[T + c] = R(0);
+    for (int k = 0; k < 3; k++) {
+        vx[k] = (vt + (2 * k) * T)[cl];
+        vy[k] = (vt + (2 * k + 1) * T)[cl];
     }
-    __syncthreads();  // the space becomes the record tile
-    if (valid) {
+    R ratio = recon_weights<R>(p, lin, (m.cand + c0)[cl], tab<R>(m.nbc) + c0, T, cl, Q0h, hl, Qm, vx, vy, d, f);
+    const R ihs = div_(R(1), hs);
+    const double gB[2] = {lower ? (m.gB + c0)[cl] : 0.0, lower ? (m.gB + T + c0)[cl] : 0.0};
+    const R gs[2] = {R(0.5 - 0.28867513459481288225), R(0.5 + 0.28867513459481288225)};
+    double h6[6];  // the thickness at the Gauss points
+    R theta = 1;
+    {
+        // positivity safeguard (not in the paper): where a layer thickness at a Gauss point would fall
+        // below a tenth of the cell's average, the deviation from the average is scaled down
+        // (Zhang-Shu scaling) until it does not; the lower layer's thickness is eta1 minus the
+        // piecewise-linear bottom.  The factor is 1 at rest and in ordinary flows; it is formed in the
+        // bulk precision (it only decides how far to pull the values back).
+        const R hbar = (R)hl, floor_h = R(0.1) * hbar;
+        const R gBx = (R)gB[0], gBy = (R)gB[1];
 #pragma unroll
         for (int slot = 0; slot < 6; slot++) {
-            const int i = 6 * lane + slot;
-            if (thick)
-                th[i].h[v == 3] = out.v[slot];
-            else
-                th[i].q[mom_slot(v)] = (R)out.v[slot];
-            tt[i].g[2 * v] = out.gx[slot];
-            tt[i].g[2 * v + 1] = out.gy[slot];
+            const int k = slot / 2, k1 = (k + 1) % 3, g = slot & 1;
+            const R x = vx[k] + gs[g] * (vx[k1] - vx[k]);
+            const R y = vy[k] + gs[g] * (vy[k1] - vy[k]);
+            const R dev = fit_dev(f, 0, x, y, slot == 0);
+            h6[slot] = Q0h + (double)dev;
+            if (dev < 0) {
+                const R bdev = hs * (gBx * x + gBy * y), room = hbar - bdev - floor_h;
+                // FP64: a quotient of at least 1 changes nothing and is not formed
+                if (!FOLD<R> || room < -dev) theta = fmin(theta, fmax(R(0), div_(room, -dev)));
+            }
+            sched_fence();
+        }
+        if (theta < R(1)) {
+#pragma unroll
+            for (int slot = 0; slot < 6; slot++) h6[slot] = Q0h + (double)theta * (h6[slot] - Q0h);
         }
     }
-    __syncthreads();
-    // copy out: 16-byte words of the valid cells' records
-    const int nh = (int)(ncell * 6 * sizeof(GpHead<R>) / 16), nt = (int)(ncell * 6 * sizeof(GpTail<R>) / 16);
-    const uint4 *sh = reinterpret_cast<const uint4 *>(th), *st = reinterpret_cast<const uint4 *>(tt);
-    uint4 *dh = reinterpret_cast<uint4 *>(rec.head + 6 * c0), *dtl = reinterpret_cast<uint4 *>(rec.tail + 6 * c0);
-    for (int i = threadIdx.x; i < nh; i += blockDim.x) dh[i] = sh[i];
-    for (int i = threadIdx.x; i < nt; i += blockDim.x) dtl[i] = st[i];
+    R Qv[2] = {Qm[0], Qm[1]};
+    if (WD && band) {
+        // front band: the layer's cell average, thickness constant (the lower layer's level follows
+        // the bottom), momentum the thickness times the desingularised velocity; r0 = 0 marks it
+#pragma unroll
+        for (int q = 0; q < 2; q++) Qv[q] = (R)(hl * wd_velocity(hl, (double)Qm[q], p.h_dry));
+#pragma unroll
+        for (int slot = 0; slot < 6; slot++) {
+            const int k = slot / 2, k1 = (k + 1) % 3, g = slot & 1;
+            const R x = vx[k] + gs[g] * (vx[k1] - vx[k]);
+            const R y = vy[k] + gs[g] * (vy[k1] - vy[k]);
+            h6[slot] = fma((double)hs, fma(gB[1], (double)y, rounded(gB[0], (double)x)), Q0h);
+        }
+        ratio = R(0);
+    }
+    if (valid) (r0 + c0)[(lower ? 0 : T) + cl] = ratio;
+    // the records, one local edge (two points) at a time through LDS; the points' monomials are formed
+    // again and not kept from above (60 registers in FP64)
+    settle(vx);
+    settle(vy);
+    char *lh = reinterpret_cast<char *>(lds) + lane * HS, *lt = reinterpret_cast<char *>(lds) + RECON_CELLS * HS + lane * TS;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+#pragma unroll
+        for (int g = 0; g < 2; g++) {
+            const int k1 = (k + 1) % 3;
+            const R x = vx[k] + gs[g] * (vx[k1] - vx[k]);
+            const R y = vy[k] + gs[g] * (vy[k1] - vy[k]);
+            char *h = lh + g * (int)sizeof(GpHead<R>), *t = lt + g * (int)sizeof(GpTail<R>) + (lower ? 6 : 0) * (int)sizeof(R);
+            *reinterpret_cast<double *>(h + (lower ? 8 : 0)) = h6[2 * k + g];
+            R *hm = reinterpret_cast<R *>(h + 16) + (lower ? 2 : 0), *gt = reinterpret_cast<R *>(t);
+#pragma unroll
+            for (int q = 1; q < 3; q++) {
+                const R dev = fit_dev(f, q, x, y, k == 0 && g == 0);
+                hm[q - 1] = WD && band ? Qv[q - 1] : Qv[q - 1] + dev;
+            }
+#pragma unroll
+            for (int q = 0; q < 3; q++) {
+                R gx = fit_dx(f, q, x, y, ihs), gy = fit_dy(f, q, x, y, ihs);
+                if (q == 0 && theta < R(1)) {
+                    gx *= theta;
+                    gy *= theta;
+                }
+                if (WD && band) {
+                    gx = q == 0 ? (R)gB[0] : R(0);
+                    gy = q == 0 ? (R)gB[1] : R(0);
+                }
+                gt[2 * q] = gx;
+                gt[2 * q + 1] = gy;
+                sched_fence();
+            }
+        }
+        __syncthreads();
+        // copy out: the block's span of this edge, 16-byte words
+        struct alignas(8) W16 {
+            uint64_t a, b;
+        };
+        constexpr int HW = HB2 / 16, TW = TB2 / 16;
+        const char *l0 = reinterpret_cast<const char *>(lds);
+        uint4 *oh = reinterpret_cast<uint4 *>(rec.head + rec_at(T, c0, k, 0)), *ot = reinterpret_cast<uint4 *>(rec.tail + rec_at(T, c0, k, 0));
+#pragma unroll
+        for (int j = 0; j < RECON_CELLS * HW / 64; j++) {
+            const int i = threadIdx.x + 64 * j;
+            const W16 w = *reinterpret_cast<const W16 *>(l0 + (i / HW) * HS + (i % HW) * 16);
+            if (i < ncell * HW) oh[i] = __builtin_bit_cast(uint4, w);
+        }
+#pragma unroll
+        for (int j = 0; j < RECON_CELLS * TW / 64; j++) {
+            const int i = threadIdx.x + 64 * j;
+            const W16 w = *reinterpret_cast<const W16 *>(l0 + RECON_CELLS * HS + (i / TW) * TS + (i % TW) * 16);
+            if (i < ncell * TW) ot[i] = __builtin_bit_cast(uint4, w);
+        }
+        __syncthreads();
+    }
     if constexpr (SRC == 1) {
         // Radon's 7-point rule (degree 5): the centroid, then two orbits (b, a, a) of barycentrics
         const R A1 = R(0.101286507323456338800987361915), B1 = R(0.797426985353087322398025276170);
         const R A2 = R(0.470142064105115089770441209513), B2 = R(0.059715871789769820459117580973);
         const R W0 = R(0.225), W1 = R(0.125939180544827152595683945500), W2 = R(0.132394152788506180737649387833);
-        // [point of the batch][variable][3][cell]: four points, then three
-        static_assert(4 * 6 * 3 * RECON_CELLS * (int)sizeof(R) <= LBYTES, "interior values exceed the LDS tile");
-        R *sv = reinterpret_cast<R *>(lds);
-        SrcGeo<R> geo;
-        if (valid) src_geo<R>(m, c, a, q.hs, geo);
-        // group 0: lower (h1 - mean) grad h2; 1: upper (h2 - mean) grad h1; 2 and 3: their rates
-        const int gq = wv;
-        const int ha = (gq == 0 || gq == 2) ? 3 : 0, hb = 3 - ha;  // deviation of h_a, gradient of h_b
-        const int ta = ha == 3 ? 4 : 1, tb = ha == 3 ? 1 : 4;      // momenta of layer a, of layer b
-        R acc[7] = {0, 0, 0, 0, 0, 0, 0};
-        // loops kept rolled: the reconstruction's register budget (4 waves per SIMD) is the limit
+        settle(vx);
+        settle(vy);
+        R gb2[2] = {0, 0}, f2[2] = {0, 0}, tg[2] = {0, 0}, ft[2] = {0, 0}, tm = 0;
+        const R gBx = (R)gB[0], gBy = (R)gB[1], i2 = ihs * ihs;
+        // kept rolled: unrolled, the points' common factors of the coefficients fill the registers
 #pragma unroll 1
-        for (int b = 0; b < 2; b++) {
-            const int q0 = 4 * b, nq = b == 0 ? 4 : 3;
-            __syncthreads();  // the previous contents of the space have been read
-            if (valid) {
-#pragma unroll 1
-                for (int j = 0; j < nq; j++) {
-                    const int qi = q0 + j;
-                    R l0, l1, l2;
-                    if (qi == 0) {
-                        l0 = l1 = l2 = R(1) / R(3);
-                    } else if (qi <= 3) {
-                        l0 = qi == 1 ? B1 : A1;
-                        l1 = qi == 2 ? B1 : A1;
-                        l2 = qi == 3 ? B1 : A1;
-                    } else {
-                        l0 = qi == 4 ? B2 : A2;
-                        l1 = qi == 5 ? B2 : A2;
-                        l2 = qi == 6 ? B2 : A2;
-                    }
-                    const R x = l0 * geo.vx[0] + l1 * geo.vx[1] + l2 * geo.vx[2];
-                    const R y = l0 * geo.vy[0] + l1 * geo.vy[1] + l2 * geo.vy[2];
-                    R o3[3];
-                    src_point<R>(m, v, thick, c, a, comb, geo, q.hs, x, y, o3);
-#pragma unroll
-                    for (int k = 0; k < 3; k++) sv[((j * 6 + v) * 3 + k) * RECON_CELLS + lane] = o3[k];
-                }
+        for (int qi = 0; qi < 7; qi++) {
+            R l0, l1, l2;
+            if (qi == 0) {
+                l0 = l1 = l2 = R(1) / R(3);
+            } else if (qi <= 3) {
+                l0 = qi == 1 ? B1 : A1;
+                l1 = qi == 2 ? B1 : A1;
+                l2 = qi == 3 ? B1 : A1;
+            } else {
+                l0 = qi == 4 ? B2 : A2;
+                l1 = qi == 5 ? B2 : A2;
+                l2 = qi == 6 ? B2 : A2;
             }
-            __syncthreads();
-            if (valid && gq < 4) {
-#pragma unroll 1
-                for (int j = 0; j < nq; j++) {
-                    const int qi = q0 + j;
-                    const R wq = qi == 0 ? W0 : qi <= 3 ? W1 : W2;
-                    auto at = [&](int vv, int k) { return sv[((j * 6 + vv) * 3 + k) * RECON_CELLS + lane]; };
-                    const R f = at(ha, 0), gx = at(hb, 1), gy = at(hb, 2);
-                    if (gq < 2) {
-                        acc[0] += wq * f * gx;
-                        acc[1] += wq * f * gy;
-                    } else {
-                        const R tau = -(at(ta, 0) + at(ta + 1, 0));
-                        const R gtx = -(at(tb, 1) + at(tb + 1, 1)), gty = -(at(tb, 2) + at(tb + 1, 2));
-                        acc[0] += wq * tau * gx;  // sum w tau_a grad h_b
-                        acc[1] += wq * tau * gy;
-                        acc[2] += wq * gx;        // sum w grad h_b
-                        acc[3] += wq * gy;
-                        acc[4] += wq * tau;       // mean of tau_a
-                        acc[5] += wq * f * gtx;   // sum w (h_a - mean) grad tau_b
-                        acc[6] += wq * f * gty;
-                    }
-                }
+            const R x = l0 * vx[0] + l1 * vx[1] + l2 * vx[2];
+            const R y = l0 * vy[0] + l1 * vy[1] + l2 * vy[2];
+            const R wq = qi == 0 ? W0 : qi <= 3 ? W1 : W2;
+            // own thickness: deviation and gradient (the lower layer's thickness is eta1 minus the bottom)
+            R h = theta * fit_dev(f, 0, x, y), gx = fit_px(a[0], x, y), gy = fit_py(a[0], x, y);
+            if constexpr (!FOLD<R>) {
+                gx = f.ratio[0] * gx + f.sx[0];
+                gy = f.ratio[0] * gy + f.sy[0];
             }
+            gx = fma(theta * gx, ihs, -gBx);
+            gy = fma(theta * gy, ihs, -gBy);
+            if (lower) h -= hs * (gBx * x + gBy * y);
+            // own thickness rate -div(h U) and its gradient: x-momentum's d/dx, y-momentum's d/dy
+            const R c1 = FOLD<R> ? R(1) : f.ratio[1], c2 = FOLD<R> ? R(1) : f.ratio[2];
+            const R uxx = 2 * a[1][2] + 6 * a[1][5] * x + 2 * a[1][6] * y, uxy = a[1][3] + 2 * a[1][6] * x + 2 * a[1][7] * y;
+            const R vxy = a[2][3] + 2 * a[2][6] * x + 2 * a[2][7] * y, vyy = 2 * a[2][4] + 2 * a[2][7] * x + 6 * a[2][8] * y;
+            const R s1 = FOLD<R> ? R(0) : f.sx[1], s2 = FOLD<R> ? R(0) : f.sy[2];
+            R u[6] = {(c1 * fit_px(a[1], x, y) + s1) * ihs, (c2 * fit_py(a[2], x, y) + s2) * ihs,
+                      c1 * uxx * i2, c2 * vxy * i2, c1 * uxy * i2, c2 * vyy * i2};
+            settle(u);  // each rounded before the sums
+            const R tau = -(u[0] + u[1]), tx = -(u[2] + u[3]), ty = -(u[4] + u[5]);
+            // the other layer's gradients
+            const R bx = __shfl_xor(gx, 1), by = __shfl_xor(gy, 1), btx = __shfl_xor(tx, 1), bty = __shfl_xor(ty, 1);
+            f2[0] += wq * h * bx;
+            f2[1] += wq * h * by;
+            tg[0] += wq * tau * bx;
+            tg[1] += wq * tau * by;
+            gb2[0] += wq * bx;
+            gb2[1] += wq * by;
+            tm += wq * tau;
+            ft[0] += wq * h * btx;
+            ft[1] += wq * h * bty;
+            sched_fence();
         }
-        if (valid && gq < 4) {
-            // rates: sum w (tau_a - mean tau_a) grad h_b + sum w (h_a - mean) grad tau_b
-            const R o0 = gq < 2 ? acc[0] : acc[0] - acc[4] * acc[2] + acc[5];
-            const R o1 = gq < 2 ? acc[1] : acc[1] - acc[4] * acc[3] + acc[6];
-            src[(2 * gq) * T + c] = o0;
-            src[(2 * gq + 1) * T + c] = o1;
+        if (valid) {
+            // rows 0, 1: lower (h1 - mean) grad h2; 2, 3: upper (h2 - mean) grad h1; 4..7 their rates,
+            // sum w (tau_a - mean tau_a) grad h_b + sum w (h_a - mean) grad tau_b
+            const int o = lower ? 0 : 2;
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                src[(o + i) * T + c] = f2[i];
+                src[(4 + o + i) * T + c] = tg[i] - tm * gb2[i] + ft[i];
+            }
         }
     }
 }
@@ -869,10 +997,9 @@ __global__ void k_hhat(MeshDev m, Phys p, const GpHead<R> *__restrict__ head, co
 #pragma unroll
     for (int g = 0; g < 2; g++) {
         const double Bg = m.eBgp[g * E + e];
-        const int sL = 2 * kL + g, sR = 2 * kR + 1 - g;
-        const GpHead<R> ql = head[6 * (int64_t)L + sL];
+        const GpHead<R> ql = head[rec_at(m.T, L, kL, g)];
         GpHead<R> qr = ql;
-        if (Rc >= 0) qr = head[6 * (int64_t)Rc + sR];
+        if (Rc >= 0) qr = head[rec_at(m.T, Rc, kR, 1 - g)];
 #pragma unroll
         for (int f = 0; f < 2; f++) {
             // f = 0: eta1 with the lower layer's momentum; f = 1: h2 with the upper layer's
@@ -1270,7 +1397,6 @@ __global__ void __launch_bounds__(256) k_flux(MeshDev m, Phys p, GpRecs<R> rec,
     const int32_t L = GKS_IX(m.eL[e], m.T), Rc = m.eR[e] >= 0 ? GKS_IX(m.eR[e], m.T) : m.eR[e],
                   sl = m.eslot[e];
     const int kL = GKS_IX(sl & 3, 3), kR = GKS_IX(sl >> 2, 3);
-    const int sL = 2 * kL + g, sR = 2 * kR + 1 - g;
     const R *en = tab<R>(m.en), *egB = tab<R>(m.egB);
     const R nx = en[e], ny = en[E + e], tx = -ny, ty = nx;
     const double Bg = m.eBgp[g * E + e];
@@ -1293,9 +1419,9 @@ __global__ void __launch_bounds__(256) k_flux(MeshDev m, Phys p, GpRecs<R> rec,
     for (int s = 0; s < 2; s++) {
         if (s == 1 && Rc < 0) break;
         const int64_t cell = s == 0 ? L : Rc;
-        const int slot = s == 0 ? sL : sR;
-        const GpHead<R> *hp = rec.head + 6 * cell + slot;
-        const R *rm = hp->q, *rg = rec.tail[6 * cell + slot].g;
+        const int64_t at = s == 0 ? rec_at(T, cell, kL, g) : rec_at(T, cell, kR, 1 - g);
+        const GpHead<R> *hp = rec.head + at;
+        const R *rm = hp->q, *rg = rec.tail[at].g;
         double hh = hp->h[hq];
         const R ex = rg[2 * gv], ey = rg[2 * gv + 1];  // slope of h2, or of eta1
         R hx = ex, hy = ey;
@@ -1473,36 +1599,39 @@ __global__ void __launch_bounds__(256) k_flux(MeshDev m, Phys p, GpRecs<R> rec,
 // its own side of each edge (the right cell of an edge reads eoh rows 6-7 and eom rows 24-33).
 template <typename R, int STAGE, int SRC = 0, int GM = 0>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_update(MeshDev m, Phys p, const double *__restrict__ eoh,
-                                                const R *__restrict__ eom, const double *__restrict__ Whin,
-                                                const R *__restrict__ Wmin, const R *__restrict__ gWin,
-                                                double *__restrict__ Whout, R *__restrict__ Wmout,
-                                                R *__restrict__ gWout, double *__restrict__ Wc, R *__restrict__ Gc,
+                                                const R *__restrict__ eom, const LayerW<R> *__restrict__ Win,
+                                                const LayerG<R> *__restrict__ Gin, LayerW<R> *__restrict__ Wout,
+                                                LayerG<R> *__restrict__ Gout, double *__restrict__ Wc, R *__restrict__ Gc,
                                                 const R *__restrict__ src)
 {
     constexpr int stage = STAGE;
     int64_t c = xcd_block() * blockDim.x + threadIdx.x;
     if (c >= m.T) return;
-    const int64_t T = m.T, E = m.E, TG = m.T + m.NG;
+    const int64_t T = m.T, E = m.E;
     const int sc = m.cscen ? (int)GKS_IX(m.cscen[c], m.S) : 0;
     const double dt = p.scal[2 * sc], G = p.G, chi = p.chi[sc];
     if (dt == 0.0) {
         // the scenario has reached its end time: the state stays as it is (the stage's output is
         // its input; stage 0 also leaves the carry equal to it for stage 1)
 #pragma unroll
-        for (int v = 0; v < 6; v++) {
-            const double w = stage == 0 ? ((v == 0) ? Whin[c] : (v == 3) ? Whin[TG + c] : (double)Wmin[mom_slot(v) * TG + c])
-                                        : Wc[v * T + c];
-            if (v == 0 || v == 3)
-                Whout[(v == 3 ? TG : 0) + c] = w;
-            else
-                Wmout[mom_slot(v) * TG + c] = (R)w;
-            if (stage == 0) Wc[v * T + c] = w;
+        for (int l = 0; l < 2; l++) {
+            LayerW<R> w;
+            LayerG<R> g;
+            if constexpr (stage == 0) {
+                w = Win[2 * c + l];
+                g = Gin[2 * c + l];
+                Wc[(3 * l) * T + c] = w.h;
+                Wc[(3 * l + 1) * T + c] = w.m[0];
+                Wc[(3 * l + 2) * T + c] = w.m[1];
 #pragma unroll
-            for (int d = 0; d < 2; d++) {
-                const R g = stage == 0 ? gWin[(2 * v + d) * TG + c] : Gc[(2 * v + d) * T + c];
-                gWout[(2 * v + d) * TG + c] = g;
-                if (stage == 0) Gc[(2 * v + d) * T + c] = g;
+                for (int i = 0; i < 6; i++) Gc[(6 * l + i) * T + c] = g.g[i];
+            } else {
+                w = {Wc[(3 * l) * T + c], {(R)Wc[(3 * l + 1) * T + c], (R)Wc[(3 * l + 2) * T + c]}};
+#pragma unroll
+                for (int i = 0; i < 6; i++) g.g[i] = Gc[(6 * l + i) * T + c];
             }
+            Wout[2 * c + l] = w;
+            Gout[2 * c + l] = g;
         }
         return;
     }
@@ -1577,7 +1706,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
     Lt[5] += LF[3] * (-G * gBy);
     if constexpr (SRC == 1) {
         // higher order: cell-average thicknesses, their rates from the mass fluxes
-        const double h2a = Whin[c], h1a = Whin[TG + c] - m.Bbar[c];
+        const double h2a = Win[2 * c].h, h1a = Win[2 * c + 1].h - m.Bbar[c];
         Lt[4] += -chi * G * (LF[3] * GC[1][0] + h1a * GCt[1][0] + (double)src[4 * T + c]);
         Lt[5] += -chi * G * (LF[3] * GC[1][1] + h1a * GCt[1][1] + (double)src[5 * T + c]);
         Lt[1] += -G * (LF[0] * GC[0][0] + h2a * GCt[0][0] + (double)src[6 * T + c]);
@@ -1592,7 +1721,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
         double L[6];
 #pragma unroll
         for (int v = 0; v < 6; v++) L[v] = LF[v];
-        const double h2 = Whin[c], h1 = Whin[TG + c] - m.Bbar[c];
+        const LayerW<R> wu = Win[2 * c], wl = Win[2 * c + 1];
+        const double h2 = wu.h, h1 = wl.h - m.Bbar[c];
         // bottom source h_j (0, -G B_x, -G B_y) (Sec. 3.2) and layer coupling
         // (Eq. SWE-source-discretization) from the Gauss-point mean thickness and the Green-Gauss
         // derivative of the other layer's Gauss-point thickness (central values); the higher-order
@@ -1614,42 +1744,59 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
         bool bad = false;  // a new thickness <= 0 (or NaN), or a non-finite momentum (via their sum)
         double msum = 0;
 #pragma unroll
-        for (int v = 0; v < 6; v++) {
-            const double w = (v == 0) ? Whin[c] : (v == 3) ? Whin[TG + c] : (double)Wmin[mom_slot(v) * TG + c];
-            const double ws = w + 0.5 * dt * L[v] + 0.125 * dt * dt * Lt[v];
-            if (v == 0 || v == 3)
-                Whout[(v == 3 ? TG : 0) + c] = ws;
-            else
-                Wmout[mom_slot(v) * TG + c] = (R)ws;
-            // a thickness <= 0 is bad, or with wet/dry layers one below -h_dry (a dry cell may hold
-            // a rounding residue)
-            if (v == 0) bad |= !(ws > hneg);
-            else if (v == 3) bad |= !(ws - (w - h1) > hneg);  // w - h1: the cell's bottom mean
-            else msum += ws;
-            Wc[v * T + c] = w + dt * L[v] + (dt * dt / 6.0) * Lt[v];
+        for (int l = 0; l < 2; l++) {
+            LayerW<R> o;
+            LayerG<R> og;
 #pragma unroll
-            for (int d = 0; d < 2; d++) {
-                gWout[(2 * v + d) * TG + c] = (R)(GG[v][d] + 0.5 * dt * GGt[v][d]);
-                Gc[(2 * v + d) * T + c] = (R)GG[v][d];
+            for (int q = 0; q < 3; q++) {
+                const int v = 3 * l + q;
+                const LayerW<R> &wi = l == 0 ? wu : wl;
+                const double w = q == 0 ? wi.h : (double)wi.m[q == 2];
+                const double ws = w + 0.5 * dt * L[v] + 0.125 * dt * dt * Lt[v];
+                if (q == 0)
+                    o.h = ws;
+                else
+                    o.m[q == 2] = (R)ws;
+                // a thickness <= 0 is bad, or with wet/dry layers one below -h_dry (a dry cell may hold
+                // a rounding residue)
+                if (v == 0) bad |= !(ws > hneg);
+                else if (v == 3) bad |= !(ws - (w - h1) > hneg);  // w - h1: the cell's bottom mean
+                else msum += ws;
+                Wc[v * T + c] = w + dt * L[v] + (dt * dt / 6.0) * Lt[v];
+#pragma unroll
+                for (int d = 0; d < 2; d++) {
+                    og.g[2 * q + d] = (R)(GG[v][d] + 0.5 * dt * GGt[v][d]);
+                    Gc[(2 * v + d) * T + c] = (R)GG[v][d];
+                }
             }
+            Wout[2 * c + l] = o;
+            Gout[2 * c + l] = og;
         }
         if (bad || !isfinite(msum)) atomicMin(p.bad, (unsigned long long)c);
     } else {
         bool bad = false;
         double msum = 0;
 #pragma unroll
-        for (int v = 0; v < 6; v++) {
-            const double wn = Wc[v * T + c] + (dt * dt / 3.0) * Lt[v];
-            if (v == 0 || v == 3)
-                Whout[(v == 3 ? TG : 0) + c] = wn;
-            else
-                Wmout[mom_slot(v) * TG + c] = (R)wn;
-            if (v == 0) bad |= !(wn > hneg);
-            else if (v == 3) bad |= !(wn - m.Bbar[c] > hneg);
-            else msum += wn;
+        for (int l = 0; l < 2; l++) {
+            LayerW<R> o;
+            LayerG<R> og;
 #pragma unroll
-            for (int d = 0; d < 2; d++)
-                gWout[(2 * v + d) * TG + c] = (R)((double)Gc[(2 * v + d) * T + c] + dt * GGt[v][d]);
+            for (int q = 0; q < 3; q++) {
+                const int v = 3 * l + q;
+                const double wn = Wc[v * T + c] + (dt * dt / 3.0) * Lt[v];
+                if (q == 0)
+                    o.h = wn;
+                else
+                    o.m[q == 2] = (R)wn;
+                if (v == 0) bad |= !(wn > hneg);
+                else if (v == 3) bad |= !(wn - m.Bbar[c] > hneg);
+                else msum += wn;
+#pragma unroll
+                for (int d = 0; d < 2; d++)
+                    og.g[2 * q + d] = (R)((double)Gc[(2 * v + d) * T + c] + dt * GGt[v][d]);
+            }
+            Wout[2 * c + l] = o;
+            Gout[2 * c + l] = og;
         }
         if (bad || !isfinite(msum)) atomicMin(p.bad, (unsigned long long)c);
     }
@@ -1677,26 +1824,25 @@ __device__ inline double block_max(double v, double *sh)
 }
 
 template <typename R>
-__device__ inline double wave_speed(const MeshDev &m, const Phys &p, const double *Wh, const R *Wm, int64_t c)
+__device__ inline double wave_speed(const MeshDev &m, const Phys &p, const LayerW<R> *W, int64_t c)
 {
-    const int64_t TG = m.T + m.NG;
-    const double h2 = Wh[c], h1 = Wh[TG + c] - m.Bbar[c];
+    const LayerW<R> wu = W[2 * c], wl = W[2 * c + 1];
+    const double h2 = wu.h, h1 = wl.h - m.Bbar[c];
     // velocities desingularised in thin layers (wet/dry; m / h otherwise), a dry cell may hold -0
-    const double u2 = wd_velocity(h2, Wm[c], p.h_dry), v2 = wd_velocity(h2, Wm[TG + c], p.h_dry);
-    const double u1 = wd_velocity(h1, Wm[2 * TG + c], p.h_dry), v1 = wd_velocity(h1, Wm[3 * TG + c], p.h_dry);
+    const double u2 = wd_velocity(h2, wu.m[0], p.h_dry), v2 = wd_velocity(h2, wu.m[1], p.h_dry);
+    const double u1 = wd_velocity(h1, wl.m[0], p.h_dry), v1 = wd_velocity(h1, wl.m[1], p.h_dry);
     const double s1 = sqrt(u1 * u1 + v1 * v1) + sqrt(p.G * fmax(h1, 0.0));
     const double s2 = sqrt(u2 * u2 + v2 * v2) + sqrt(p.G * fmax(h2, 0.0));
     return fmax(s1, s2);
 }
 
 template <typename R>
-__global__ void __launch_bounds__(DT_BLOCK) k_dt_partial(MeshDev m, Phys p, const double *__restrict__ Wh,
-                                                          const R *__restrict__ Wm, double *__restrict__ part)
+__global__ void __launch_bounds__(DT_BLOCK) k_dt_partial(MeshDev m, Phys p, const LayerW<R> *__restrict__ W, double *__restrict__ part)
 {
     __shared__ double sh[DT_BLOCK / 64];
     double smax = 0;
     for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < m.T; c += (int64_t)gridDim.x * blockDim.x)
-        smax = fmax(smax, wave_speed(m, p, Wh, Wm, c));
+        smax = fmax(smax, wave_speed(m, p, W, c));
     smax = block_max(smax, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = smax;
 }
@@ -1726,15 +1872,14 @@ __global__ void __launch_bounds__(DT_BLOCK) k_dt_final(MeshDev m, Phys p, const 
 // batches: one block per chunk of cells (the chunk's largest wave speed), then one block per
 // scenario over its chunks
 template <typename R>
-__global__ void __launch_bounds__(DT_BLOCK) k_dt_chunk(MeshDev m, Phys p, const double *__restrict__ Wh,
-                                                        const R *__restrict__ Wm, double *__restrict__ part)
+__global__ void __launch_bounds__(DT_BLOCK) k_dt_chunk(MeshDev m, Phys p, const LayerW<R> *__restrict__ W, double *__restrict__ part)
 {
     __shared__ double sh[DT_BLOCK / 64];
     const int ch = blockIdx.x;
     double smax = 0;
     const int64_t c0 = GKS_IX(m.cb[ch], m.T + 1), c1 = GKS_IX(m.cb[ch + 1], m.T + 1);
     for (int64_t c = c0 + threadIdx.x; c < c1; c += blockDim.x)
-        smax = fmax(smax, wave_speed(m, p, Wh, Wm, c));
+        smax = fmax(smax, wave_speed(m, p, W, c));
     smax = block_max(smax, sh);
     if (threadIdx.x == 0) part[ch] = smax;
 }
@@ -1766,15 +1911,15 @@ __global__ void k_set_dt(Phys p, double dt)
 }
 
 // per-layer mass of cells [c0, c1): fixed-order block sums (deterministic)
-__global__ void __launch_bounds__(256) k_mass_partial(MeshDev m, const double *__restrict__ Wh, int64_t c0,
+template <typename R>
+__global__ void __launch_bounds__(256) k_mass_partial(MeshDev m, const LayerW<R> *__restrict__ W, int64_t c0,
                                                       int64_t c1, double *__restrict__ part)
 {
     __shared__ double sh[2][256];
-    const int64_t TG = m.T + m.NG;
     double a = 0, b = 0;
     for (int64_t c = c0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < c1; c += (int64_t)gridDim.x * blockDim.x) {
-        a += m.area[c] * Wh[c];
-        b += m.area[c] * (Wh[TG + c] - m.Bbar[c]);
+        a += m.area[c] * W[2 * c].h;
+        b += m.area[c] * (W[2 * c + 1].h - m.Bbar[c]);
     }
     sh[0][threadIdx.x] = a;
     sh[1][threadIdx.x] = b;
@@ -1797,23 +1942,46 @@ __global__ void __launch_bounds__(256) k_mass_partial(MeshDev m, const double *_
 // value, coalesced; the host used to unpack and convert them component by component (31 ms on
 // 520,200 cells in FP64, of which the transfer over PCIe is 1.4 ms).
 template <typename R>
-__global__ void __launch_bounds__(256) k_snapshot(MeshDev m, const double *__restrict__ Wh, const R *__restrict__ Wm,
-                                                  const R *__restrict__ gW, int64_t i0, int64_t i1,
-                                                  double *__restrict__ out)
+__global__ void __launch_bounds__(256) k_snapshot(MeshDev m, const LayerW<R> *__restrict__ W, const LayerG<R> *__restrict__ G,
+                                                  int64_t i0, int64_t i1, double *__restrict__ out)
 {
     const int64_t i = i0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= i1) return;
-    const int64_t T = m.T, TG = m.T + m.NG, row = i / T, c = i - row * T;
+    const int64_t T = m.T, row = i / T, c = i - row * T;
     double x;
     if (row < 6) {
-        const int v = (int)row;
-        x = v == 0 ? Wh[c] : v == 3 ? Wh[TG + c] - m.Bbar[c] : (double)Wm[mom_slot(v) * TG + c];
+        const int l = row >= 3, q = (int)row - 3 * l;
+        const LayerW<R> &w = W[2 * c + l];
+        x = q == 0 ? (l ? w.h - m.Bbar[c] : w.h) : (double)w.m[q - 1];
     } else {
-        x = gW[(row - 6) * TG + c];
-        if (row == 12) x -= m.gB[c];
-        if (row == 13) x -= m.gB[T + c];
+        const int l = row >= 12, q = (int)row - 6 - 6 * l;
+        x = G[2 * c + l].g[q];
+        if (l && q < 2) x -= m.gB[q * T + c];
     }
     out[i - i0] = x;
+}
+
+// Rows of the checkpoint's arrays, between the device's layout and the checkpoint's component-major
+// one: h2 and eta1 [2][TG] in double, the momenta [4][TG], the gradients [12][TG]; the kernel moves values
+// [i0, i1) of the 18 TG, TO_STATE from `raw` into the state, else the other way.  raw holds the first
+// 2 TG values as doubles and the rest as R, from byte 16 TG on.
+template <typename R, bool TO_STATE>
+__global__ void __launch_bounds__(256) k_checkpoint(MeshDev m, LayerW<R> *__restrict__ W, LayerG<R> *__restrict__ G,
+                                                    void *__restrict__ raw)
+{
+    const int64_t TG = m.T + m.NG, i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= 18 * TG) return;
+    const int64_t row = i / TG, c = i - row * TG;
+    double *h = static_cast<double *>(raw);
+    R *q = reinterpret_cast<R *>(h + 2 * TG);
+    if (row < 2) {
+        double &x = W[2 * c + row].h;
+        if constexpr (TO_STATE) x = h[i]; else h[i] = x;
+    } else {
+        const int64_t j = i - 2 * TG;
+        R &x = row < 6 ? W[2 * c + (row - 2) / 2].m[row & 1] : G[2 * c + (row - 6) / 6].g[(row - 6) % 6];
+        if constexpr (TO_STATE) x = q[j]; else q[j] = x;
+    }
 }
 
 // Per-step diagnostics of a scenario's cells [c0, c1) (Sec. 3.2's well-balance property: a lake
@@ -1822,16 +1990,15 @@ __global__ void __launch_bounds__(256) k_snapshot(MeshDev m, const double *__res
 // levels eta1 = h1 + B and eta2 = eta1 + h2, as six maxima (the minima negated); the host takes
 // the maxima over the blocks.  Grid-stride over the cells.
 template <typename R>
-__global__ void __launch_bounds__(256) k_diag_partial(MeshDev m, const double *__restrict__ Wh,
-                                                      const R *__restrict__ Wm, int64_t c0, int64_t c1,
-                                                      double h_dry, double *__restrict__ part)
+__global__ void __launch_bounds__(256) k_diag_partial(MeshDev m, const LayerW<R> *__restrict__ W, int64_t c0,
+                                                      int64_t c1, double h_dry, double *__restrict__ part)
 {
     __shared__ double sh[6][256];
-    const int64_t TG = m.T + m.NG;
     double v[6] = {0.0, 0.0, -HUGE_VAL, -HUGE_VAL, -HUGE_VAL, -HUGE_VAL};
     for (int64_t c = c0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < c1; c += (int64_t)gridDim.x * blockDim.x) {
-        const double h2 = Wh[c], e1 = Wh[TG + c], h1 = e1 - m.Bbar[c];
-        const double m2x = Wm[c], m2y = Wm[TG + c], m1x = Wm[2 * TG + c], m1y = Wm[3 * TG + c];
+        const LayerW<R> wu = W[2 * c], wl = W[2 * c + 1];
+        const double h2 = wu.h, e1 = wl.h, h1 = e1 - m.Bbar[c];
+        const double m2x = wu.m[0], m2y = wu.m[1], m1x = wl.m[0], m1y = wl.m[1];
         v[0] = fmax(v[0], wd_velocity(h2, sqrt(m2x * m2x + m2y * m2y), h_dry));
         v[1] = fmax(v[1], wd_velocity(h1, sqrt(m1x * m1x + m1y * m1y), h_dry));
         v[2] = fmax(v[2], e1);

@@ -119,6 +119,9 @@ __global__ void k_weights_bf16(const float *__restrict__ P, short *__restrict__ 
 // then hs times the gradients of the cell and its face neighbours, in the bulk precision):
 // x[l] = rhs[l] / s with s = max_l |rhs[l]| + 1e-12 |Q0| (l < 17), x[17] = log10(s / h) / 4 with
 // h the layer thickness
+__device__ inline float thick_feature(double rhs, double is) { return (float)(rhs * is); }
+__device__ inline float size_feature(double s, double h) { return (float)(log10(s / h) * 0.25); }
+
 template <typename R>
 __device__ inline void thick_features(const R *rhs, double Q0, double h, float *x)
 {
@@ -128,8 +131,8 @@ __device__ inline void thick_features(const R *rhs, double Q0, double h, float *
     s += 1e-12 * fabs(Q0);
     const double is = 1.0 / s;
 #pragma unroll
-    for (int l = 0; l < 17; l++) x[l] = (float)((double)rhs[l] * is);
-    x[17] = (float)(log10(s / h) * 0.25);
+    for (int l = 0; l < 17; l++) x[l] = thick_feature((double)rhs[l], is);
+    x[17] = size_feature(s, h);
 }
 
 // largest stencil difference of one variable
