@@ -55,8 +55,7 @@ def algorithmic_bytes(T, E, NG, prec):
         "recon": T * (2 * d + 4 * r + 12 * r + 153 * r + 13 * r + 4 * 9 + 12 * d + 96 * r + 2 * r),
         # every record once, weights and plane gradients once per cell; edge tables; outputs
         "flux": T * (12 * d + 96 * r + 2 * r + 4 * d) + E * (4 * 3 + 2 * r + 2 * d + 2 * r + 6 * d + 24 * r),
-        "hhat": T * (12 * d + 24 * r) + E * (4 * 3 + 2 * r + 2 * d + 2 * d),
-        "plane": T * (4 * 3 + 6 * d + 4 * d) + E * 2 * d,
+        "plane": T * (12 * d + 24 * r + 4 * 3 + 6 * d + 4 * d) + E * (4 * 3 + 2 * r + 2 * d),
         # geometry, edge outputs once (the second stage reads only the interface and central
         # thicknesses, the thickness fluxes and the time derivatives), state / carry (average of
         # the two stages)
@@ -163,8 +162,8 @@ def kernel_roofline(st, mesh, steps, prec):
         if n:
             avg = tot / n
             kernels[k] = {"avg_ms": round(avg, 5), "launches": n}
-            # the force-model kernels work only next to cells whose weights are not linear
-            if k in alg and k not in ("hhat", "plane"):
+            # the force-model kernel works only next to cells whose weights are not linear
+            if k in alg and k != "plane":
                 kernels[k]["alg_GBs"] = round(alg[k] / (avg / 1e3) / 1e9, 1)
     dom = max((k for k in kernels if "alg_GBs" in kernels[k]), key=lambda k: kernels[k]["avg_ms"] * kernels[k]["launches"])
     avg = kernels[dom]["avg_ms"]

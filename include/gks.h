@@ -260,8 +260,8 @@ gks_status gks_state_buffer(const gks_state *st, int32_t which, void *dst, int64
 typedef enum {
     GKS_KERNEL_GHOST = 0,   /* mirror ghost cells refreshed from their source cells */
     GKS_KERNEL_RECON = 1,   /* compact reconstruction at the Gauss points (Sec. 3.4) */
-    GKS_KERNEL_HHAT = 2,    /* edge-centre heights of the force model (Sec. 2.3) */
-    GKS_KERNEL_PLANE = 3,   /* plane gradient of the force model (Sec. 2.3) */
+    GKS_KERNEL_HHAT = 2,    /* no launches: the edge-centre heights are formed with the planes */
+    GKS_KERNEL_PLANE = 3,   /* edge-centre heights and plane gradient of the force model (Sec. 2.3) */
     GKS_KERNEL_FLUX = 4,    /* gas-kinetic evolution at the Gauss points (Sec. 2.2) */
     GKS_KERNEL_UPDATE = 5,  /* gather, sources, S2O4 stage update (Sec. 3.1-3.3) */
     GKS_KERNEL_DT = 6,      /* CFL time step (Sec. 4) */

@@ -109,12 +109,11 @@ struct gks_state {
     hipStream_t stream = nullptr;
     // LayerW[TG][2] and behind it in the same allocation LayerG[TG][2]
     void *W[2] = {nullptr, nullptr}, *gW[2] = {nullptr, nullptr};
-    double *Wc = nullptr, *hmid = nullptr, *gP1 = nullptr;
+    double *Wc = nullptr, *gP1 = nullptr;
     double *eoh = nullptr;
     void *Gc = nullptr, *rec = nullptr, *r0 = nullptr, *eom = nullptr;  // rec: GpRec[6T]
     double *scal = nullptr, *part = nullptr, *chi = nullptr, *tend = nullptr;
     uint8_t *smooth = nullptr;  // skip mask of the reconstruction (learned indicator)
-    uint8_t *need = nullptr;    // cells whose plane gradient of the force model is used
     unsigned long long *bad = nullptr;  // first cell updated to a non-finite / non-positive state
     bool src4 = false;          // higher-order layer coupling
     bool gm1 = false;           // discontinuous interface values in the gradient update
@@ -277,15 +276,10 @@ void launch_stage(gks_state *s, int stage, hipStream_t st)
         else
             launch_recon<R, 0>(s, stage, st, Win, gWin);
     });
-    timed(s, st, GKS_KERNEL_HHAT, [&] {
-        const int b = s->bs[GKS_KERNEL_HHAT];
-        hipLaunchKernelGGL(gks::k_need<R>, dim3(blocks(m.T, b)), dim3(b), 0, st, m, (const R *)s->r0, s->need);
-        hipLaunchKernelGGL(gks::k_hhat<R>, dim3(blocks(m.E, b)), dim3(b), 0, st, m, s->p,
-                           (const gks::GpHead<R> *)s->rec, s->need, s->hmid);
-    });
     timed(s, st, GKS_KERNEL_PLANE, [&] {
         const int b = s->bs[GKS_KERNEL_PLANE];
-        hipLaunchKernelGGL(gks::k_plane, dim3(blocks(m.T, b)), dim3(b), 0, st, m, s->need, s->hmid, s->gP1);
+        hipLaunchKernelGGL(gks::k_plane<R>, dim3(blocks(4 * m.T, b)), dim3(b), 0, st, m, s->p,
+                           (const gks::GpHead<R> *)s->rec, (const R *)s->r0, s->gP1);
     });
     timed(s, st, GKS_KERNEL_FLUX, [&] {
         if (s->p.alpha_mode == 0) {
@@ -792,8 +786,8 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
             size_t bytes;
         } bufs[] = {{&s->W[0], w_bytes(prec, TG) + 12 * uTG * rs}, {&s->W[1], w_bytes(prec, TG) + 12 * uTG * rs},
                     {(void **)&s->Wc, 6 * uT * 8}, {&s->Gc, 12 * uT * rs}, {&s->rec, 6 * uT * rec_bytes(prec)},
-                    {&s->r0, 2 * uT * rs}, {(void **)&s->hmid, 2 * uE * 8},
-                    {(void **)&s->gP1, 4 * uT * 8}, {(void **)&s->need, uT}, {(void **)&s->eoh, (s->gm1 ? 8 : 6) * uE * 8},
+                    {&s->r0, 2 * uT * rs},
+                    {(void **)&s->gP1, 4 * uT * 8}, {(void **)&s->eoh, (s->gm1 ? 8 : 6) * uE * 8},
                     {&s->eom, (s->gm1 ? 34 : 24) * uE * rs},
                     {(void **)&s->scal, 2 * uS * 8}, {(void **)&s->part, 2 * (size_t)std::max<int64_t>(std::max(s->nparts, 1024), mesh->d64.NCH) * 8},
                     {(void **)&s->chi, uS * 8}, {(void **)&s->tend, uS * 8}, {(void **)&s->bad, 8},
@@ -1796,7 +1790,7 @@ extern "C" gks_status gks_autotune(gks_state *s, int32_t reps, int32_t *chosen)
         if (r == GKS_OK) {
             copy(false);
             drop_graph(s);
-            const int tuned[5] = {GKS_KERNEL_GHOST, GKS_KERNEL_HHAT, GKS_KERNEL_PLANE, GKS_KERNEL_FLUX, GKS_KERNEL_UPDATE};
+            const int tuned[4] = {GKS_KERNEL_GHOST, GKS_KERNEL_PLANE, GKS_KERNEL_FLUX, GKS_KERNEL_UPDATE};
             const int cand[3] = {64, 128, 256};
             for (int k : tuned) {
                 if (k == GKS_KERNEL_GHOST && h.ng == 0) continue;

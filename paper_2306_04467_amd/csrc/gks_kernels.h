@@ -958,99 +958,71 @@ __global__ void __launch_bounds__(64, (sizeof(R) == 8 ? 3 : 4)) k_recon(MeshDev 
 }
 
 // --------------------------------------------------------------------------------------------
-// interface force modelling (Sec. 2.3): edge-centre height of eta1 (lower-layer velocity) and of
-// h2 (upper-layer velocity) from the two Gauss points' convex combinations (FP64: cheap, and the
-// plane through them must be flat at rest)
+// interface force modelling (Sec. 2.3): gradient of the plane through the edge-centre heights of eta1
+// (lower-layer velocity) and of h2 (upper-layer velocity), each from the two Gauss points' convex
+// combinations (FP64: cheap, and the plane through them must be flat at rest)
 
-// Cells whose plane gradient the flux can read: the force model blends it in with weight 1 - w,
+// Only cells whose plane gradient the flux can read: the force model blends it in with weight 1 - w,
 // w = min(1, omega0/d0 of both sides) taken as 1 within 1e-12 of it, so only next to a cell whose
 // weight ratio is below 1 - 1e-12.  A face neighbour beyond a wall is the cell's own mirror image.
+//
+// Four lanes a cell, one for each Gauss point of an edge (bit 0) and field (bit 1), over the three edges;
+// Green-Gauss, exact for planes.  Bound by latency: a chain of dependent reads (stencil, weights; edge,
+// cells, records) and the error function.  An edge between two such cells is evaluated for both of them,
+// which costs less than the heights' way through memory and two more launches: between events, three
+// kernels (weights to a mark per cell, heights per edge, planes per cell) took 18.7 us a stage at 800
+// cells FP64 where this one takes 9.5, 20.3 / 11.6 at 80k, 34.2 / 27.0 at 520k.
 template <typename R>
-__global__ void k_need(MeshDev m, const R *__restrict__ r0, uint8_t *__restrict__ need)
+__global__ void __launch_bounds__(256) k_plane(MeshDev m, Phys p, const GpHead<R> *__restrict__ head,
+                                               const R *__restrict__ r0, double *__restrict__ gP1)
 {
-    const int64_t c = xcd_block() * blockDim.x + threadIdx.x;
-    if (c >= m.T) return;
-    const int64_t T = m.T;
-    bool bad = (double)r0[c] < W_ONE || (double)r0[T + c] < W_ONE;
-#pragma unroll
-    for (int l = 0; l < 3; l++) {
-        const int32_t i = GKS_IX(m.sten[l * T + c], T + m.NG);
-        if (i < T) bad = bad || (double)r0[i] < W_ONE || (double)r0[T + i] < W_ONE;
-    }
-    need[c] = bad ? 1 : 0;
-}
-
-template <typename R>
-__global__ void k_hhat(MeshDev m, Phys p, const GpHead<R> *__restrict__ head, const uint8_t *__restrict__ need,
-                       double *__restrict__ hmid)
-{
-    int64_t e = xcd_block() * blockDim.x + threadIdx.x;
-    if (e >= m.E) return;
-    const int64_t E = m.E;
-    const int32_t L = GKS_IX(m.eL[e], m.T), Rc = m.eR[e] >= 0 ? GKS_IX(m.eR[e], m.T) : m.eR[e],
-                  sl = m.eslot[e];
-    if (!need[L] && (Rc < 0 || !need[Rc])) return;  // no plane gradient uses this edge
-    const int kL = GKS_IX(sl & 3, 3), kR = GKS_IX(sl >> 2, 3);
-    const R *en = tab<R>(m.en);
-    const double nx = en[e], ny = en[E + e];
-    double acc0 = 0, acc1 = 0;
-#pragma unroll
-    for (int g = 0; g < 2; g++) {
-        const double Bg = m.eBgp[g * E + e];
-        const GpHead<R> ql = head[rec_at(m.T, L, kL, g)];
-        GpHead<R> qr = ql;
-        if (Rc >= 0) qr = head[rec_at(m.T, Rc, kR, 1 - g)];
-#pragma unroll
-        for (int f = 0; f < 2; f++) {
-            // f = 0: eta1 with the lower layer's momentum; f = 1: h2 with the upper layer's
-            const int hq = f == 0 ? 1 : 0, mq = f == 0 ? 2 : 0;
-            // a dry side (thickness at or below h_dry, or not positive) has no velocity
-            const double zl = ql.h[hq];
-            const double hl = f == 0 ? zl - Bg : zl;
-            const double unl = (hl > p.h_dry && hl > 0) ? ((double)ql.q[mq] * nx + (double)ql.q[mq + 1] * ny) / hl : 0.0;
-            double zr, hr, unr;
-            if (Rc >= 0) {
-                zr = qr.h[hq];
-                hr = f == 0 ? zr - Bg : zr;
-                unr = (hr > p.h_dry && hr > 0) ? ((double)qr.q[mq] * nx + (double)qr.q[mq + 1] * ny) / hr : 0.0;
-            } else {  // mirror state across a wall; the same state across a free boundary
-                zr = zl;
-                hr = hl;
-                unr = Rc == -1 ? -unl : unl;
-            }
-            // reading: xi is the kinetic fraction of particles moving from left to right (one half
-            // when both sides are dry)
-            const double lb = 2.0 / (p.G * (hl + hr));
-            const double xi = (hl + hr > 0) ? 0.5 * erfc(-sqrt(lb) * 0.5 * (unl + unr)) : 0.5;
-            const double hh = xi * zl + (1 - xi) * zr;
-            if (f == 0) acc0 += 0.5 * hh; else acc1 += 0.5 * hh;
-        }
-    }
-    hmid[e] = acc0;
-    hmid[E + e] = acc1;
-}
-
-// gradient of the plane through the three edge-centre heights (Green-Gauss, exact for planes)
-__global__ void k_plane(MeshDev m, const uint8_t *__restrict__ need, const double *__restrict__ hmid,
-                        double *__restrict__ gP1)
-{
-    int64_t c = xcd_block() * blockDim.x + threadIdx.x;
-    if (c >= m.T || !need[c]) return;
+    const int64_t idx = xcd_block() * blockDim.x + threadIdx.x, c = idx >> 2;
+    if (c >= m.T) return;  // the lanes of a cell leave together, here and below
+    const int j = idx & 3, g = j & 1, f = j >> 1;
     const int64_t T = m.T, E = m.E;
-    double s[4] = {0, 0, 0, 0};
+    // lane 0 looks at the cell's own weights, the others at a face neighbour's
+    const int64_t i = j == 0 ? c : (int64_t)GKS_IX(m.sten[(j - 1) * T + c], T + m.NG);
+    int need = i < T && ((double)r0[i] < W_ONE || (double)r0[T + i] < W_ONE);
+    need |= __shfl_xor(need, 1);
+    need |= __shfl_xor(need, 2);
+    if (!need) return;
+    // field 0: eta1 with the lower layer's momentum; 1: h2 with the upper layer's
+    const int hq = f == 0 ? 1 : 0, mq = f == 0 ? 2 : 0;
+    const R *en = tab<R>(m.en);
+    double sx = 0, sy = 0;
 #pragma unroll
     for (int k = 0; k < 3; k++) {
         const int32_t code = m.cedge[k * T + c];
-        const int64_t e = GKS_IX(code >= 0 ? code : ~code, m.E);
-        const double gx = m.gg[(2 * k) * T + c], gy = m.gg[(2 * k + 1) * T + c];
-        const double h0 = hmid[e], h1 = hmid[E + e];
-        s[0] += gx * h0;
-        s[1] += gy * h0;
-        s[2] += gx * h1;
-        s[3] += gy * h1;
+        const int64_t e = GKS_IX(code >= 0 ? code : ~code, E);
+        const int32_t L = GKS_IX(m.eL[e], T), Rc = m.eR[e] >= 0 ? GKS_IX(m.eR[e], T) : m.eR[e], sl = m.eslot[e];
+        const double nx = en[e], ny = en[E + e], Bg = m.eBgp[g * E + e];
+        const GpHead<R> ql = head[rec_at(T, L, GKS_IX(sl & 3, 3), g)];
+        GpHead<R> qr = ql;
+        if (Rc >= 0) qr = head[rec_at(T, Rc, GKS_IX(sl >> 2, 3), 1 - g)];
+        // a dry side (thickness at or below h_dry, or not positive) has no velocity
+        const double zl = ql.h[hq];
+        const double hl = f == 0 ? zl - Bg : zl;
+        const double unl = (hl > p.h_dry && hl > 0) ? ((double)ql.q[mq] * nx + (double)ql.q[mq + 1] * ny) / hl : 0.0;
+        double zr, hr, unr;
+        if (Rc >= 0) {
+            zr = qr.h[hq];
+            hr = f == 0 ? zr - Bg : zr;
+            unr = (hr > p.h_dry && hr > 0) ? ((double)qr.q[mq] * nx + (double)qr.q[mq + 1] * ny) / hr : 0.0;
+        } else {  // mirror state across a wall; the same state across a free boundary
+            zr = zl;
+            hr = hl;
+            unr = Rc == -1 ? -unl : unl;
+        }
+        // reading: xi is the kinetic fraction of particles moving from left to right (one half
+        // when both sides are dry)
+        const double lb = 2.0 / (p.G * (hl + hr));
+        const double xi = (hl + hr > 0) ? 0.5 * erfc(-sqrt(lb) * 0.5 * (unl + unr)) : 0.5;
+        const double hh = xi * zl + (1 - xi) * zr;
+        const double h = 0.5 * hh + 0.5 * __shfl_xor(hh, 1);
+        sx += m.gg[(2 * k) * T + c] * h;
+        sy += m.gg[(2 * k + 1) * T + c] * h;
     }
-#pragma unroll
-    for (int i = 0; i < 4; i++) gP1[i * T + c] = s[i];
+    gP1[(2 * f + g) * T + c] = g == 0 ? sx : sy;
 }
 
 // --------------------------------------------------------------------------------------------
