@@ -241,10 +241,10 @@ void launch_update_gm(gks_state *s, int stage, hipStream_t st, const gks::LayerW
     const int b = s->bs[GKS_KERNEL_UPDATE];
     const R *src = SRC ? (const R *)s->src : nullptr;
     if (stage == 0)
-        hipLaunchKernelGGL((gks::k_update<R, 0, SRC, GM>), dim3(blocks(m.T, b)), dim3(b), 0, st, m, s->p, s->eoh,
+        hipLaunchKernelGGL((gks::k_update<R, 0, SRC, GM>), dim3(blocks(2 * m.T, b)), dim3(b), 0, st, m, s->p, s->eoh,
                            (const R *)s->eom, Win, gWin, Wout, gWout, s->Wc, (R *)s->Gc, src);
     else
-        hipLaunchKernelGGL((gks::k_update<R, 1, SRC, GM>), dim3(blocks(m.T, b)), dim3(b), 0, st, m, s->p, s->eoh,
+        hipLaunchKernelGGL((gks::k_update<R, 1, SRC, GM>), dim3(blocks(2 * m.T, b)), dim3(b), 0, st, m, s->p, s->eoh,
                            (const R *)s->eom, Win, gWin, Wout, gWout, s->Wc, (R *)s->Gc, src);
 }
 
@@ -262,14 +262,9 @@ template <typename R>
 void launch_stage(gks_state *s, int stage, hipStream_t st)
 {
     const gks::MeshDev &m = s->md;
-    const int in = stage == 0 ? 0 : 1, out = 1 - in;
+    const int in = stage == 0 ? 0 : 1, out = 1 - in;  // the input's ghosts are up to date
     gks::LayerW<R> *Win = (gks::LayerW<R> *)s->W[in], *Wout = (gks::LayerW<R> *)s->W[out];
     gks::LayerG<R> *gWin = (gks::LayerG<R> *)s->gW[in], *gWout = (gks::LayerG<R> *)s->gW[out];
-    if (m.NG > 0)
-        timed(s, st, GKS_KERNEL_GHOST, [&] {
-            const int b = s->bs[GKS_KERNEL_GHOST];
-            hipLaunchKernelGGL(gks::k_ghost_fill<R>, dim3(blocks(m.NG, b)), dim3(b), 0, st, m, Win, gWin);
-        });
     timed(s, st, GKS_KERNEL_RECON, [&] {
         if (s->src4)
             launch_recon<R, 1>(s, stage, st, Win, gWin);
@@ -381,6 +376,16 @@ gks_status upload_mesh(gks_mesh *m)
     up(h.eR, &d.eR);
     up(h.eslot, &d.eslot);
     up(h.gsrc, &d.gsrc);
+    {
+        // each cell's ghosts, for the kernel that updates the cell
+        std::vector<int32_t> gfirst((size_t)h.nt + 1, 0), gof((size_t)h.ng);
+        for (int64_t g = 0; g < h.ng; g++) gfirst[(size_t)h.gsrc[g] + 1]++;
+        for (int64_t c = 0; c < h.nt; c++) gfirst[(size_t)c + 1] += gfirst[(size_t)c];
+        std::vector<int32_t> next(gfirst.begin(), gfirst.end() - 1);
+        for (int64_t g = 0; g < h.ng; g++) gof[(size_t)next[(size_t)h.gsrc[g]]++] = (int32_t)g;
+        up(gfirst, &d.gfirst);
+        up(gof, &d.gof);
+    }
     up(h.scell, &d.scell);
     up(h.cand, &d.cand);
     const double *M = nullptr, *hs = nullptr, *vtx = nullptr, *nbc = nullptr, *en = nullptr, *egB = nullptr;
@@ -637,6 +642,26 @@ void move_checkpoint(const gks_state *s, bool to_state, void *raw)
     if (s->prec == GKS_FP64) go(double()); else go(float());
 }
 
+// ghost cells of a state that was written from the host; every update after that writes them itself
+gks_status fill_ghosts(gks_state *s)
+{
+    const gks::MeshDev &m = s->md;
+    if (m.NG == 0) return GKS_OK;
+    timed(s, s->stream, GKS_KERNEL_GHOST, [&] {
+        const int b = s->bs[GKS_KERNEL_GHOST];
+        const dim3 g(blocks(m.NG, b)), t(b);
+        if (s->prec == GKS_FP64)
+            hipLaunchKernelGGL(gks::k_ghost_fill<double>, g, t, 0, s->stream, m, (gks::LayerW<double> *)s->W[0],
+                               (gks::LayerG<double> *)s->gW[0]);
+        else
+            hipLaunchKernelGGL(gks::k_ghost_fill<float>, g, t, 0, s->stream, m, (gks::LayerW<float> *)s->W[0],
+                               (gks::LayerG<float> *)s->gW[0]);
+    });
+    HIP_OK(hipGetLastError());
+    HIP_OK(hipStreamSynchronize(s->stream));
+    return GKS_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -828,7 +853,7 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
             HIP_OK(hipMemcpy(s->bad, &none, 8, hipMemcpyHostToDevice));
             HIP_OK(hipMemset(s->W[1], 0, w_bytes(prec, TG)));
             HIP_OK(hipMemset(s->gW[1], 0, 12 * TG * rs));
-            return GKS_OK;
+            return fill_ghosts(s);
         }();
         if (r != GKS_OK) {
             gks_state_destroy(s);
@@ -1204,6 +1229,8 @@ gks_status gks_state_load(gks_state *s, const void *blob, int64_t bytes)
         HIP_OK(hipMemcpy(s->W[1], p, raw_bytes, hipMemcpyHostToDevice));
         move_checkpoint(s, true, s->W[1]);
         HIP_OK(hipGetLastError());
+        const gks_status filled = fill_ghosts(s);  // also where the checkpoint's ghosts are older than its cells
+        if (filled != GKS_OK) return filled;
         HIP_OK(hipStreamSynchronize(s->stream));
         p += raw_bytes;
         HIP_OK(hipMemcpy(s->scal, p, 2 * (size_t)h.S * 8, hipMemcpyHostToDevice));
@@ -1306,21 +1333,10 @@ gks_status state_alloc(gks_state *s, void **p, size_t bytes)
     return GKS_OK;
 }
 
-// refresh the ghost cells of the latest state (they are otherwise refreshed at the start of a stage)
-template <typename R>
-void ghost_latest(gks_state *s, int b)
-{
-    const gks::MeshDev &m = s->md;
-    if (m.NG > 0)
-        hipLaunchKernelGGL(gks::k_ghost_fill<R>, dim3(blocks(m.NG, 256)), dim3(256), 0, s->stream, m,
-                           (gks::LayerW<R> *)s->W[b], (gks::LayerG<R> *)s->gW[b]);
-}
-
 template <typename R>
 void launch_features(gks_state *s, float *X)
 {
     const int b = s->half ? 1 : 0;
-    ghost_latest<R>(s, b);
     hipLaunchKernelGGL(gks::k_features<R>, dim3(blocks(s->md.T, 256)), dim3(256), 0, s->stream, s->md, s->p.G,
                        (const gks::LayerW<R> *)s->W[b], (const gks::LayerG<R> *)s->gW[b], X);
 }
@@ -1330,7 +1346,6 @@ void launch_labels(gks_state *s, double tol)
 {
     const gks::MeshDev &m = s->md;
     const int b = s->half ? 1 : 0;
-    ghost_latest<R>(s, b);
     gks::Phys pn = s->p, pl = s->p;
     pn.linear = 0;
     pl.linear = 1;
@@ -1473,13 +1488,11 @@ gks_status gks_indicator_eval(gks_state *s, float *logits, uint8_t *mask, int64_
         const gks::MeshDev &m = s->md;
         const int b = s->half ? 1 : 0;
         if (s->prec == GKS_FP64) {
-            ghost_latest<double>(s, b);
             hipLaunchKernelGGL(gks::k_indicator<double>, dim3(blocks(m.T, 32 * gks::IND_WAVES)),
                                dim3(64 * gks::IND_WAVES), 0, s->stream, m, s->p.G, (const gks::LayerW<double> *)s->W[b],
                                (const gks::LayerG<double> *)s->gW[b], s->ind_W1b, s->ind_W2b, s->ind_P, s->ind_thr, s->smooth,
                                s->ind_logit);
         } else {
-            ghost_latest<float>(s, b);
             hipLaunchKernelGGL(gks::k_indicator<float>, dim3(blocks(m.T, 32 * gks::IND_WAVES)),
                                dim3(64 * gks::IND_WAVES), 0, s->stream, m, s->p.G, (const gks::LayerW<float> *)s->W[b],
                                (const gks::LayerG<float> *)s->gW[b], s->ind_W1b, s->ind_W2b, s->ind_P, s->ind_thr, s->smooth,
@@ -1790,10 +1803,9 @@ extern "C" gks_status gks_autotune(gks_state *s, int32_t reps, int32_t *chosen)
         if (r == GKS_OK) {
             copy(false);
             drop_graph(s);
-            const int tuned[4] = {GKS_KERNEL_GHOST, GKS_KERNEL_PLANE, GKS_KERNEL_FLUX, GKS_KERNEL_UPDATE};
+            const int tuned[3] = {GKS_KERNEL_PLANE, GKS_KERNEL_FLUX, GKS_KERNEL_UPDATE};
             const int cand[3] = {64, 128, 256};
             for (int k : tuned) {
-                if (k == GKS_KERNEL_GHOST && h.ng == 0) continue;
                 double best = 1e300;
                 int pick = s->bs[k];
                 for (int b : cand) {

@@ -39,6 +39,7 @@ struct MeshDev {
     const float *igeo;              // [6][T] indicator geometry
     const uint8_t *cand;            // [T] plane candidates of the nonlinear reconstruction (bits 0..2)
     const int32_t *cedge, *sten, *eL, *eR, *eslot, *gsrc;
+    const int32_t *gfirst, *gof;    // ghosts gof[gfirst[c] .. gfirst[c + 1]) mirror cell c
     const int32_t *cscen, *escen;   // scenario of each cell / edge, nullptr when S == 1
     // batches: the cells cut into chunks that never straddle two scenarios, chunk c covering
     // [cb[c], cb[c + 1]); scenario s owns chunks [sc0[s], sc0[s + 1])
@@ -180,29 +181,35 @@ __host__ __device__ inline int64_t rec_at(int64_t T, int64_t c, int k, int g) { 
 // --------------------------------------------------------------------------------------------
 // ghost mirror cells: state of the source cell seen through an orthogonal map
 
+// layer l of ghost cell g from that of its source cell
 template <typename R>
-__global__ void k_ghost_fill(MeshDev m, LayerW<R> *__restrict__ W, LayerG<R> *__restrict__ G)
+__device__ inline void mirror(const MeshDev &m, int64_t g, int l, const LayerW<R> &w, const LayerG<R> &q,
+                              LayerW<R> *__restrict__ W, LayerG<R> *__restrict__ G)
 {
-    int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= m.NG) return;
-    const int64_t s = GKS_IX(m.gsrc[g], m.T), d = m.T + g, NG = m.NG;
+    const int64_t d = m.T + g, NG = m.NG;
     // R (a b; c e) maps gradient directions, V (va vb; vc ve) momentum vectors: V = R across a
     // wall, V = I across a free boundary (each component extended evenly)
     const double a = m.gR[g], b = m.gR[NG + g], c = m.gR[2 * NG + g], e = m.gR[3 * NG + g];
     const double va = m.gR[4 * NG + g], vb = m.gR[5 * NG + g], vc = m.gR[6 * NG + g], ve = m.gR[7 * NG + g];
+    const double mx = w.m[0], my = w.m[1], hx = q.g[0], hy = q.g[1];
+    W[2 * d + l] = {w.h, {(R)(va * mx + vb * my), (R)(vc * mx + ve * my)}};
+    // momentum gradient G[i][j] = d m_i / d x_j  ->  V G R^T
+    const double g00 = q.g[2], g01 = q.g[3], g10 = q.g[4], g11 = q.g[5];
+    const double r00 = va * g00 + vb * g10, r01 = va * g01 + vb * g11;
+    const double r10 = vc * g00 + ve * g10, r11 = vc * g01 + ve * g11;
+    G[2 * d + l] = {{(R)(a * hx + b * hy), (R)(c * hx + e * hy), (R)(r00 * a + r01 * b), (R)(r00 * c + r01 * e),
+                     (R)(r10 * a + r11 * b), (R)(r10 * c + r11 * e)}};
+}
+
+// all ghosts of a state that did not come from k_update, which writes them along with its cells
+template <typename R>
+__global__ void __launch_bounds__(256) k_ghost_fill(MeshDev m, LayerW<R> *__restrict__ W, LayerG<R> *__restrict__ G)
+{
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= m.NG) return;
+    const int64_t s = GKS_IX(m.gsrc[g], m.T);
 #pragma unroll
-    for (int l = 0; l < 2; l++) {
-        const LayerW<R> w = W[2 * s + l];
-        const LayerG<R> q = G[2 * s + l];
-        const double mx = w.m[0], my = w.m[1], hx = q.g[0], hy = q.g[1];
-        W[2 * d + l] = {w.h, {(R)(va * mx + vb * my), (R)(vc * mx + ve * my)}};
-        // momentum gradient G[i][j] = d m_i / d x_j  ->  V G R^T
-        const double g00 = q.g[2], g01 = q.g[3], g10 = q.g[4], g11 = q.g[5];
-        const double r00 = va * g00 + vb * g10, r01 = va * g01 + vb * g11;
-        const double r10 = vc * g00 + ve * g10, r11 = vc * g01 + ve * g11;
-        G[2 * d + l] = {{(R)(a * hx + b * hy), (R)(c * hx + e * hy), (R)(r00 * a + r01 * b), (R)(r00 * c + r01 * e),
-                         (R)(r10 * a + r11 * b), (R)(r10 * c + r11 * e)}};
-    }
+    for (int l = 0; l < 2; l++) mirror(m, g, l, W[2 * s + l], G[2 * s + l], W, G);
 }
 
 // --------------------------------------------------------------------------------------------
@@ -1569,208 +1576,186 @@ __global__ void __launch_bounds__(256) k_flux(MeshDev m, Phys p, GpRecs<R> rec,
 // mean, its rate from the cell's mass flux, plus the interior correction src[8][T] of k_recon.
 // GM = 1: the discontinuous reading of the gradient update: a cell takes the interface values of
 // its own side of each edge (the right cell of an edge reads eoh rows 6-7 and eom rows 24-33).
+//
+// Two lanes a cell, lane l layer l (0 upper, 1 lower), the other layer's slopes by a swap in the pair; a
+// cell's lanes also write its ghosts in the new state, so that the next stage starts with the
+// reconstruction.  Bound by memory where the mesh is large: 460 MB at 520k cells FP64 in the first
+// stage, 97 us at the rate of a large copy; the two stages take 108.7 us on average, between events,
+// where one thread a cell and a kernel for the ghosts took 104.3 and 8.9 (180k FP32: 26.8, 25.1 + 6.7;
+// 10k FP64: 9.1, 9.7 + 6.8).  With the ghosts written by one thread a cell, it spills (134.9, 28.5, 14.4);
+// the edges' values in blocks of 16 edges instead of rows change nothing (112.0, 73.0 at 520k FP32 / 72.9).
 template <typename R, int STAGE, int SRC = 0, int GM = 0>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k_update(MeshDev m, Phys p, const double *__restrict__ eoh,
-                                                const R *__restrict__ eom, const LayerW<R> *__restrict__ Win,
-                                                const LayerG<R> *__restrict__ Gin, LayerW<R> *__restrict__ Wout,
-                                                LayerG<R> *__restrict__ Gout, double *__restrict__ Wc, R *__restrict__ Gc,
-                                                const R *__restrict__ src)
+__global__ void __launch_bounds__(256) k_update(MeshDev m, Phys p, const double *__restrict__ eoh, const R *__restrict__ eom,
+                                                const LayerW<R> *__restrict__ Win, const LayerG<R> *__restrict__ Gin,
+                                                LayerW<R> *__restrict__ Wout, LayerG<R> *__restrict__ Gout,
+                                                double *__restrict__ Wc, R *__restrict__ Gc, const R *__restrict__ src)
 {
-    constexpr int stage = STAGE;
-    int64_t c = xcd_block() * blockDim.x + threadIdx.x;
+    const int64_t idx = xcd_block() * blockDim.x + threadIdx.x, c = idx >> 1;
+    const int l = idx & 1;
+    const bool lower = l == 1;
     if (c >= m.T) return;
     const int64_t T = m.T, E = m.E;
     const int sc = m.cscen ? (int)GKS_IX(m.cscen[c], m.S) : 0;
-    const double dt = p.scal[2 * sc], G = p.G, chi = p.chi[sc];
+    const double dt = p.scal[2 * sc], G = p.G;
+    LayerW<R> w;  // the stage's output
+    LayerG<R> g;
     if (dt == 0.0) {
         // the scenario has reached its end time: the state stays as it is (the stage's output is
         // its input; stage 0 also leaves the carry equal to it for stage 1)
+        if constexpr (STAGE == 0) {
+            w = Win[idx];
+            g = Gin[idx];
+            Wc[idx] = w.h;
+            Wc[2 * T + idx] = w.m[0];
+            Wc[4 * T + idx] = w.m[1];
 #pragma unroll
-        for (int l = 0; l < 2; l++) {
-            LayerW<R> w;
-            LayerG<R> g;
-            if constexpr (stage == 0) {
-                w = Win[2 * c + l];
-                g = Gin[2 * c + l];
-                Wc[(3 * l) * T + c] = w.h;
-                Wc[(3 * l + 1) * T + c] = w.m[0];
-                Wc[(3 * l + 2) * T + c] = w.m[1];
-#pragma unroll
-                for (int i = 0; i < 6; i++) Gc[(6 * l + i) * T + c] = g.g[i];
-            } else {
-                w = {Wc[(3 * l) * T + c], {(R)Wc[(3 * l + 1) * T + c], (R)Wc[(3 * l + 2) * T + c]}};
-#pragma unroll
-                for (int i = 0; i < 6; i++) g.g[i] = Gc[(6 * l + i) * T + c];
-            }
-            Wout[2 * c + l] = w;
-            Gout[2 * c + l] = g;
-        }
-        return;
-    }
-    double LF[6] = {0}, LFt[6] = {0}, GG[6][2] = {{0}}, GGt[6][2] = {{0}}, hs[2] = {0, 0}, hts[2] = {0, 0};
-    // smallest acceptable new thickness, exclusive: 0, or -h_dry with wet/dry layers
-    const double hneg = p.h_dry > 0 ? -p.h_dry : 0.0;
-    double GC[2][2] = {{0, 0}}, GCt[2][2] = {{0, 0}};  // [0] lower, [1] upper: central thicknesses
-#pragma unroll
-    for (int k = 0; k < 3; k++) {
-        const int32_t code = m.cedge[k * T + c];
-        const int64_t e = GKS_IX(code >= 0 ? code : ~code, m.E);
-        const double f = m.fl[k * T + c], gx = m.gg[(2 * k) * T + c], gy = m.gg[(2 * k + 1) * T + c];
-        // rows of this cell's interface values: shared, or those of its own side (GM = 1)
-        const int64_t ho = (GM == 1 && code < 0) ? 4 * E : 0, mo = (GM == 1 && code < 0) ? 12 * E : 0;
-        const double Hu = eoh[2 * E + ho + e], Hl = eoh[3 * E + ho + e];
-        double Wb[6];
-        Wb[0] = Hu;
-        Wb[3] = Hl;
-        if constexpr (stage == 0) {
-            Wb[1] = eom[12 * E + mo + e];
-            Wb[2] = eom[13 * E + mo + e];
-            Wb[4] = eom[14 * E + mo + e];
-            Wb[5] = eom[15 * E + mo + e];
-        }
-#pragma unroll
-        for (int v = 0; v < 6; v++) {
-            const bool mass = v == 0 || v == 3;
-            if (stage == 0 || mass) {
-                LF[v] -= f * (double)eom[(int64_t)v * E + e];
-                GG[v][0] += gx * Wb[v];
-                GG[v][1] += gy * Wb[v];
-            }
-            const double Ft = eom[(int64_t)(6 + v) * E + e];
-            const double Wbt = eom[(int64_t)(16 + v) * E + mo + e];
-            LFt[v] -= f * Ft;
-            GGt[v][0] += gx * Wbt;
-            GGt[v][1] += gy * Wbt;
-        }
-        if constexpr (stage == 0) {
-            // hydrostatic part of the normal momentum flux, along the outward normal
-            const double Pu = eoh[e], Pl = eoh[E + e];
-            LF[1] -= gx * Pu;
-            LF[2] -= gy * Pu;
-            LF[4] -= gx * Pl;
-            LF[5] -= gy * Pl;
-        }
-        const double Cu = eoh[4 * E + e], Cl = eoh[5 * E + e];
-        const double Ctu = eom[22 * E + e], Ctl = eom[23 * E + e];
-        GC[1][0] += gx * Cu;
-        GC[1][1] += gy * Cu;
-        GC[0][0] += gx * Cl;
-        GC[0][1] += gy * Cl;
-        GCt[1][0] += gx * Ctu;
-        GCt[1][1] += gy * Ctu;
-        GCt[0][0] += gx * Ctl;
-        GCt[0][1] += gy * Ctl;
-        hs[1] += Cu;
-        hs[0] += Cl;
-        hts[1] += Ctu;
-        hts[0] += Ctl;
-    }
-    const double third = 1.0 / 3.0;
-    hs[0] *= third; hs[1] *= third; hts[0] *= third; hts[1] *= third;  // [0] lower, [1] upper
-    const double gBx = m.gB[c], gBy = m.gB[T + c];
-    double Lt[6];
-#pragma unroll
-    for (int v = 0; v < 6; v++) Lt[v] = LFt[v];
-    // bottom source rate via the thickness rates; layer coupling rate by the product rule
-    Lt[1] += LF[0] * (-G * gBx);
-    Lt[2] += LF[0] * (-G * gBy);
-    Lt[4] += LF[3] * (-G * gBx);
-    Lt[5] += LF[3] * (-G * gBy);
-    if constexpr (SRC == 1) {
-        // higher order: cell-average thicknesses, their rates from the mass fluxes
-        const double h2a = Win[2 * c].h, h1a = Win[2 * c + 1].h - m.Bbar[c];
-        Lt[4] += -chi * G * (LF[3] * GC[1][0] + h1a * GCt[1][0] + (double)src[4 * T + c]);
-        Lt[5] += -chi * G * (LF[3] * GC[1][1] + h1a * GCt[1][1] + (double)src[5 * T + c]);
-        Lt[1] += -G * (LF[0] * GC[0][0] + h2a * GCt[0][0] + (double)src[6 * T + c]);
-        Lt[2] += -G * (LF[0] * GC[0][1] + h2a * GCt[0][1] + (double)src[7 * T + c]);
-    } else {
-        Lt[4] += -chi * G * (hts[0] * GC[1][0] + hs[0] * GCt[1][0]);
-        Lt[5] += -chi * G * (hts[0] * GC[1][1] + hs[0] * GCt[1][1]);
-        Lt[1] += -G * (hts[1] * GC[0][0] + hs[1] * GCt[0][0]);
-        Lt[2] += -G * (hts[1] * GC[0][1] + hs[1] * GCt[0][1]);
-    }
-    if constexpr (stage == 0) {
-        double L[6];
-#pragma unroll
-        for (int v = 0; v < 6; v++) L[v] = LF[v];
-        const LayerW<R> wu = Win[2 * c], wl = Win[2 * c + 1];
-        const double h2 = wu.h, h1 = wl.h - m.Bbar[c];
-        // bottom source h_j (0, -G B_x, -G B_y) (Sec. 3.2) and layer coupling
-        // (Eq. SWE-source-discretization) from the Gauss-point mean thickness and the Green-Gauss
-        // derivative of the other layer's Gauss-point thickness (central values); the higher-order
-        // form takes the cell average and adds the interior correction
-        if constexpr (SRC == 1) {
-            L[1] += h2 * (-G * gBx) - G * (h2 * GC[0][0] + (double)src[2 * T + c]);
-            L[2] += h2 * (-G * gBy) - G * (h2 * GC[0][1] + (double)src[3 * T + c]);
-            L[4] += h1 * (-G * gBx) - chi * G * (h1 * GC[1][0] + (double)src[c]);
-            L[5] += h1 * (-G * gBy) - chi * G * (h1 * GC[1][1] + (double)src[T + c]);
+            for (int i = 0; i < 6; i++) Gc[2 * i * T + idx] = g.g[i];
         } else {
-            L[1] += h2 * (-G * gBx) - G * hs[1] * GC[0][0];
-            L[2] += h2 * (-G * gBy) - G * hs[1] * GC[0][1];
-            L[4] += h1 * (-G * gBx) - chi * G * hs[0] * GC[1][0];
-            L[5] += h1 * (-G * gBy) - chi * G * hs[0] * GC[1][1];
+            w = {Wc[idx], {(R)Wc[2 * T + idx], (R)Wc[4 * T + idx]}};
+#pragma unroll
+            for (int i = 0; i < 6; i++) g.g[i] = Gc[2 * i * T + idx];
         }
-        // the state carries grad(eta1) = grad(h1) + grad(B)
-        GG[3][0] += gBx;
-        GG[3][1] += gBy;
+    } else {
+        // K: what couples the other layer's thickness into this one, G or chi G
+        const double K = lower ? p.chi[sc] * G : G;
+        double LF[3] = {0}, LFt[3] = {0}, GG[3][2] = {{0}}, GGt[3][2] = {{0}}, hs = 0, hts = 0;
+        // smallest acceptable new thickness, exclusive: 0, or -h_dry with wet/dry layers
+        const double hneg = p.h_dry > 0 ? -p.h_dry : 0.0;
+        double GC[2] = {0, 0}, GCt[2] = {0, 0};  // central thickness
+        const double *eh = eoh + l * E;
+        const R *e1 = eom + (22 + l) * E, *e2 = eom + (12 + 2 * l) * E, *e3 = eom + 3 * l * E;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            const int32_t code = m.cedge[k * T + c];
+            const int64_t e = GKS_IX(code >= 0 ? code : ~code, m.E);
+            const double f = m.fl[k * T + c], gx = m.gg[(2 * k) * T + c], gy = m.gg[(2 * k + 1) * T + c];
+            // rows of this cell's interface values: shared, or those of its own side (GM = 1)
+            const int64_t ho = (GM == 1 && code < 0) ? 4 * E : 0, mo = (GM == 1 && code < 0) ? 12 * E : 0;
+            double Wb[3];
+            Wb[0] = eh[2 * E + ho + e];
+            if constexpr (STAGE == 0) {
+                Wb[1] = e2[mo + e];
+                Wb[2] = e2[E + mo + e];
+            }
+#pragma unroll
+            for (int q = 0; q < 3; q++) {
+                if (STAGE == 0 || q == 0) {
+                    LF[q] -= f * (double)e3[q * E + e];
+                    GG[q][0] += gx * Wb[q];
+                    GG[q][1] += gy * Wb[q];
+                }
+                const double Ft = e3[(6 + q) * E + e];
+                const double Wbt = e3[(16 + q) * E + mo + e];
+                LFt[q] -= f * Ft;
+                GGt[q][0] += gx * Wbt;
+                GGt[q][1] += gy * Wbt;
+            }
+            if constexpr (STAGE == 0) {
+                // hydrostatic part of the normal momentum flux, along the outward normal
+                const double P = eh[e];
+                LF[1] -= gx * P;
+                LF[2] -= gy * P;
+            }
+            const double C = eh[4 * E + e], Ct = e1[e];
+            GC[0] += gx * C;
+            GC[1] += gy * C;
+            GCt[0] += gx * Ct;
+            GCt[1] += gy * Ct;
+            hs += C;
+            hts += Ct;
+        }
+        const double third = 1.0 / 3.0;
+        hs *= third;
+        hts *= third;
+        // the other layer's slopes
+#pragma unroll
+        for (int d = 0; d < 2; d++) {
+            GC[d] = __shfl_xor(GC[d], 1);
+            GCt[d] = __shfl_xor(GCt[d], 1);
+        }
+        const double gBx = m.gB[c], gBy = m.gB[T + c];
+        // rows of the interior correction: 0, 1 lower, 2, 3 upper, 4 .. 7 their rates
+        const R *sr = SRC == 1 ? src + (lower ? 0 : 2) * T + c : nullptr;
+        const double Bb = lower ? m.Bbar[c] : 0.0;
+        LayerW<R> wi;
+        double h = 0;
+        if constexpr (STAGE == 0 || SRC == 1) {
+            wi = Win[idx];
+            h = wi.h - Bb;
+        }
+        // bottom source rate via the thickness rates; layer coupling rate by the product rule
+        double Lt[3] = {LFt[0], LFt[1], LFt[2]};
+        Lt[1] += LF[0] * (-G * gBx);
+        Lt[2] += LF[0] * (-G * gBy);
+        if constexpr (SRC == 1) {
+            // higher order: cell-average thicknesses, their rates from the mass fluxes
+            Lt[1] += -K * (LF[0] * GC[0] + h * GCt[0] + (double)sr[4 * T]);
+            Lt[2] += -K * (LF[0] * GC[1] + h * GCt[1] + (double)sr[5 * T]);
+        } else {
+            Lt[1] += -K * (hts * GC[0] + hs * GCt[0]);
+            Lt[2] += -K * (hts * GC[1] + hs * GCt[1]);
+        }
         bool bad = false;  // a new thickness <= 0 (or NaN), or a non-finite momentum (via their sum)
         double msum = 0;
-#pragma unroll
-        for (int l = 0; l < 2; l++) {
-            LayerW<R> o;
-            LayerG<R> og;
+        if constexpr (STAGE == 0) {
+            double L[3] = {LF[0], LF[1], LF[2]};
+            // bottom source h_j (0, -G B_x, -G B_y) (Sec. 3.2) and layer coupling
+            // (Eq. SWE-source-discretization) from the Gauss-point mean thickness and the Green-Gauss
+            // derivative of the other layer's Gauss-point thickness (central values); the higher-order
+            // form takes the cell average and adds the interior correction
+            if constexpr (SRC == 1) {
+                L[1] += h * (-G * gBx) - K * (h * GC[0] + (double)sr[0]);
+                L[2] += h * (-G * gBy) - K * (h * GC[1] + (double)sr[T]);
+            } else {
+                L[1] += h * (-G * gBx) - K * hs * GC[0];
+                L[2] += h * (-G * gBy) - K * hs * GC[1];
+            }
+            if (lower) {  // the state carries grad(eta1) = grad(h1) + grad(B)
+                GG[0][0] += gBx;
+                GG[0][1] += gBy;
+            }
+            const double bot = wi.h - h;  // the cell's bottom mean (lower layer)
 #pragma unroll
             for (int q = 0; q < 3; q++) {
-                const int v = 3 * l + q;
-                const LayerW<R> &wi = l == 0 ? wu : wl;
-                const double w = q == 0 ? wi.h : (double)wi.m[q == 2];
-                const double ws = w + 0.5 * dt * L[v] + 0.125 * dt * dt * Lt[v];
+                const double wv = q == 0 ? wi.h : (double)wi.m[q == 2];
+                const double ws = wv + 0.5 * dt * L[q] + 0.125 * dt * dt * Lt[q];
                 if (q == 0)
-                    o.h = ws;
+                    w.h = ws;
                 else
-                    o.m[q == 2] = (R)ws;
+                    w.m[q == 2] = (R)ws;
                 // a thickness <= 0 is bad, or with wet/dry layers one below -h_dry (a dry cell may hold
                 // a rounding residue)
-                if (v == 0) bad |= !(ws > hneg);
-                else if (v == 3) bad |= !(ws - (w - h1) > hneg);  // w - h1: the cell's bottom mean
+                if (q == 0) bad = !(ws - bot > hneg);
                 else msum += ws;
-                Wc[v * T + c] = w + dt * L[v] + (dt * dt / 6.0) * Lt[v];
+                Wc[2 * q * T + idx] = wv + dt * L[q] + (dt * dt / 6.0) * Lt[q];
 #pragma unroll
                 for (int d = 0; d < 2; d++) {
-                    og.g[2 * q + d] = (R)(GG[v][d] + 0.5 * dt * GGt[v][d]);
-                    Gc[(2 * v + d) * T + c] = (R)GG[v][d];
+                    g.g[2 * q + d] = (R)(GG[q][d] + 0.5 * dt * GGt[q][d]);
+                    Gc[2 * (2 * q + d) * T + idx] = (R)GG[q][d];
                 }
             }
-            Wout[2 * c + l] = o;
-            Gout[2 * c + l] = og;
-        }
-        if (bad || !isfinite(msum)) atomicMin(p.bad, (unsigned long long)c);
-    } else {
-        bool bad = false;
-        double msum = 0;
-#pragma unroll
-        for (int l = 0; l < 2; l++) {
-            LayerW<R> o;
-            LayerG<R> og;
+        } else {
 #pragma unroll
             for (int q = 0; q < 3; q++) {
-                const int v = 3 * l + q;
-                const double wn = Wc[v * T + c] + (dt * dt / 3.0) * Lt[v];
+                const double wn = Wc[2 * q * T + idx] + (dt * dt / 3.0) * Lt[q];
                 if (q == 0)
-                    o.h = wn;
+                    w.h = wn;
                 else
-                    o.m[q == 2] = (R)wn;
-                if (v == 0) bad |= !(wn > hneg);
-                else if (v == 3) bad |= !(wn - m.Bbar[c] > hneg);
+                    w.m[q == 2] = (R)wn;
+                if (q == 0) bad = !(wn - Bb > hneg);
                 else msum += wn;
 #pragma unroll
                 for (int d = 0; d < 2; d++)
-                    og.g[2 * q + d] = (R)((double)Gc[(2 * v + d) * T + c] + dt * GGt[v][d]);
+                    g.g[2 * q + d] = (R)((double)Gc[2 * (2 * q + d) * T + idx] + dt * GGt[q][d]);
             }
-            Wout[2 * c + l] = o;
-            Gout[2 * c + l] = og;
         }
         if (bad || !isfinite(msum)) atomicMin(p.bad, (unsigned long long)c);
+    }
+    Wout[idx] = w;
+    Gout[idx] = g;
+    if (m.NG > 0) {
+        const int32_t j1 = m.gfirst[c + 1];
+        for (int32_t j = m.gfirst[c]; j < j1; j++) mirror(m, GKS_IX(m.gof[GKS_IX(j, m.NG)], m.NG), l, w, g, Wout, Gout);
     }
 }
 
