@@ -216,11 +216,12 @@ void launch_flux_gm(gks_state *s, hipStream_t st)
 {
     const gks::MeshDev &m = s->md;
     const int b = s->bs[GKS_KERNEL_FLUX];
+    const dim3 g(blocks(gks::LAYER_WAVES<R> ? 128 * ((m.E + 31) / 32) : 4 * m.E, b));
     if (s->p.h_dry > 0)
-        hipLaunchKernelGGL((gks::k_flux<R, AM, STAGE, GM, 1>), dim3(blocks(4 * m.E, b)), dim3(b), 0, st, m, s->p,
+        hipLaunchKernelGGL((gks::k_flux<R, AM, STAGE, GM, 1>), g, dim3(b), 0, st, m, s->p,
                            recs_of<R>(s->rec, m.T), (const R *)s->r0, s->gP1, s->eoh, (R *)s->eom);
     else
-        hipLaunchKernelGGL((gks::k_flux<R, AM, STAGE, GM, 0>), dim3(blocks(4 * m.E, b)), dim3(b), 0, st, m, s->p,
+        hipLaunchKernelGGL((gks::k_flux<R, AM, STAGE, GM, 0>), g, dim3(b), 0, st, m, s->p,
                            recs_of<R>(s->rec, m.T), (const R *)s->r0, s->gP1, s->eoh, (R *)s->eom);
 }
 

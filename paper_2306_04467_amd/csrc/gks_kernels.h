@@ -1335,6 +1335,178 @@ __host__ __device__ inline bool gks_point(const SideL<R> &sl, const SideL<R> &sr
     return false;
 }
 
+// The same in FP64, with fewer operations: BOT = 0 leaves out the bottom's moments (the upper layer, whose
+// bottom slope is zero), and at the interface
+//   the half-space moments of the two sides' slopes about the one Maxwellian are taken as the full-space
+//   moments of their mean (closed forms) plus the moments D = M(u > 0) - M(u < 0) of half their
+//   difference: two sets of polynomial moments instead of four;
+//   the bottom, the same on both sides, is left with its full-space moments -S (1, U, V) and
+//   -S (U, U^2 + 2 th, U V), S = gB . (U, V), instead of four sets of half-space ones;
+//   the well-balance weights of the acceleration apply to the difference alone as it stands.
+// FP32 keeps the form above: any other order of its operations moves the results by the amplified rounding
+// of a few obtuse cells (Fit).
+template <int AM, int WD, int BOT>
+__device__ inline bool gks_point64(const SideL<double> &sl, const SideL<double> &sr, double hbase, double gBn, double gBt, double G, double eps,
+                                 double eps_num, double dt, double *F0, double *Ft, double *Wb, double *Wbt, bool order1,
+                                 double h_dry)
+{
+    typedef double R;
+    // reciprocals formed once (lam = 1/(G h)); 1/(2 sqrt(pi lam)) = sqrt(lam) th / sqrt(pi)
+    const R iG = div_(R(1), G), ihL = sl.ih, ihR = sr.ih;
+    const R lamL = iG * ihL, lamR = iG * ihR;
+    const R thL = R(0.5) * G * sl.h, thR = R(0.5) * G * sr.h;
+    const R ispi = R(0.56418958354775628695);  // 1/sqrt(pi)
+    R ML[6], MR[6], eL, eR;
+    // half-space masses from one error function per Gaussian: 1/2 erfc(-x) = 1/2 (1 + erf(x))
+    // (exactly 1/2 at rest; where erf(x) is close to -1 the lost relative digits of the tiny mass
+    // are below the absolute rounding of the moments it enters)
+    {
+        const R sq = sqrt_(lamL);
+        eL = erf_(sq * sl.U);  // 2 (M0 - 1/2)
+        const R m0 = R(0.5) + R(0.5) * eL;
+        const R ex = exp_(-lamL * sl.U * sl.U) * sq * thL * ispi;
+        u_moments(sl.U, thL, m0, sl.U * m0 + ex, ML);
+    }
+    {
+        const R sq = sqrt_(lamR);
+        eR = -erf_(sq * sr.U);
+        const R m0 = R(0.5) + R(0.5) * eR;  // 1/2 erfc(x)
+        const R ex = exp_(-lamR * sr.U * sr.U) * sq * thR * ispi;
+        u_moments(sr.U, thR, m0, sr.U * m0 - ex, MR);
+    }
+    // interface equilibrium state: thickness as an FP64 base plus a deviation that is 0 at rest
+    const R hdev = R(0.5) * (sl.h * eL + sr.h * eR);
+    if constexpr (WD) {
+        if (!(hbase + (double)hdev > h_dry)) {  // no particles at the interface
+#pragma unroll
+            for (int i = 0; i < 3; i++) F0[i] = Ft[i] = Wb[i] = Wbt[i] = R(0);
+            return true;
+        }
+    }
+    const R hb = (R)(hbase + (double)hdev);
+    const R wb1 = sum_products(sl.h, ML[1], sr.h, MR[1]);
+    const R wb2 = sum_products(sl.h * ML[0], sl.V, sr.h * MR[0], sr.V);
+    // brackets of the initial (side) distributions first, so that the sides' moments are dead
+    // before the interface equilibrium's are formed.  B4 = (.., D4 + P + B4p, ..)
+    R B4[3], B5[3], t1[3], t2[3];
+    B4[0] = wb1;
+    // normal momentum: h U M1 parts plus the pressure-like part's excess over 1/2 G hb^2
+    // (h^2 M0 summed over the sides minus hb^2: exactly zero at rest)
+    {
+        const R sq2 = sum_products(sl.h * sl.h, ML[0], sr.h * sr.h, MR[0]);
+        const R hb2 = sum_products(hb, hb, R(0), R(0));
+        B4[1] = sum_products(sl.h * sl.U, ML[1], sr.h * sr.U, MR[1]) + R(0.5) * G * (sq2 - hb2);
+    }
+    B4[2] = sum_products(sl.h * ML[1], sl.V, sr.h * MR[1], sr.V);
+    {
+        const Slope<double> aL = slope_of(sl, ihL, sl.U, sl.V, lamL), aR = slope_of(sr, ihR, sr.U, sr.V, lamR);
+        poly_moments(aL, sl.pn, sl.pt, sl.h, sl.U, sl.V, lamL, thL, ML, 1, t1);
+        poly_moments(aR, sr.pn, sr.pt, sr.h, sr.U, sr.V, lamR, thR, MR, 1, t2);
+        if constexpr (BOT) {
+            bottom_moments(gBn, gBt, sl.U, sl.V, lamL, thL, ML, 1, t1);
+            bottom_moments(gBn, gBt, sr.U, sr.V, lamR, thR, MR, 1, t2);
+        }
+        settle(t1);
+        settle(t2);
+#pragma unroll
+        for (int i = 0; i < 3; i++) B5[i] = t1[i] + t2[i];
+        if constexpr (AM == 1) {
+            // the paper's constants on the initial distributions' acceleration moments: (3/4 - 1) on
+            // <u u>, (1/4 - 1) on <u v>; the moments are -2 Phi_n N1_2 / G and
+            // -2 (V Phi_n N1_1 + th Phi_t M_1) / G over each side's own half Maxwellian
+            const R pLn = sl.pn - G * gBn, pLt = sl.pt - G * gBt, pRn = sr.pn - G * gBn, pRt = sr.pt - G * gBt;
+            const R L1 = ML[2] - sl.U * ML[1], L2 = ML[3] - sl.U * ML[2];
+            const R R1 = MR[2] - sr.U * MR[1], R2 = MR[3] - sr.U * MR[2];
+            B5[1] += R(0.5) * iG * sum_products(pLn, L2, pRn, R2);
+            B5[2] += R(1.5) * iG * (sl.V * pLn * L1 + thL * pLt * ML[1] + sr.V * pRn * R1 + thR * pRt * MR[1]);
+        }
+    }
+    const R ihb = div_(R(1), hb);
+    const R Ub = wb1 * ihb, Vb = wb2 * ihb;
+    const R lamb = iG * ihb, thb = R(0.5) * G * hb;
+    // brackets multiplying the five time coefficients; B1 and B4 split into a hydrostatic part
+    // and the rest.  B1 = (hb Ub, hb Ub^2 + P, hb Ub Vb), the pressure removed
+    R B1[3], B2[3], B3[3], wt[3];
+    const R sq = sqrt_(lamb), eb = erf_(sq * Ub);
+    const R ex = exp_(-lamb * Ub * Ub) * sq * thb * ispi;
+    R D[6];
+    u_moments(Ub, thb, eb, Ub * eb + 2 * ex, D);
+    const Slope<double> bL = slope_of(sl, ihb, Ub, Vb, lamb), bR = slope_of(sr, ihb, Ub, Vb, lamb);
+    const Slope<double> d = {R(0.5) * (bL.an - bR.an), R(0.5) * (bL.bn - bR.bn), R(0.5) * (bL.gn - bR.gn),
+                        R(0.5) * (bL.at - bR.at), R(0.5) * (bL.bt - bR.bt), R(0.5) * (bL.gt - bR.gt)};
+    const R an = bL.an - d.an, bn = bL.bn - d.bn, gn = bL.gn - d.gn, at = bL.at - d.at, bt = bL.bt - d.bt, gt = bL.gt - d.gt;
+    const R dpn = R(0.5) * (sl.pn - sr.pn), dpt = R(0.5) * (sl.pt - sr.pt);
+    const R pn = sl.pn - dpn, pt = sl.pt - dpt;
+    const R fn = bt * Vb - 2 * lamb * pn, w = gt * Vb - 2 * lamb * pt, atV = at * Vb;
+    const R UU = Ub * Ub, UUt = UU + thb, UU4 = 2 * UU + 4 * thb, at4 = 4 * thb * at;
+    const R S = BOT ? gBn * Ub + gBt * Vb : R(0), hth = hb * thb;
+    const R q0 = hth * (2 * (Ub * an + atV) + bn + gt);
+    const R q1 = hth * (UU4 * an + Ub * (2 * (atV + bn) + gt) + fn);
+    const R q2 = hth * (Ub * (UU4 + 8 * thb) * an + UU4 * atV + UUt * (3 * bn + gt) + 2 * Ub * fn);
+    const R v0 = hth * (gn * Ub + w + at4), v1 = hth * (gn * UUt + Ub * (w + at4) + bt * thb);
+    B1[0] = hb * Ub;
+    B1[1] = hb * UU;
+    B1[2] = hb * Ub * Vb;
+    // time slope of the interface equilibrium from compatibility, and the bracket of the slopes
+    poly_moments(d, dpn, dpt, hb, Ub, Vb, lamb, thb, D, 0, t1);
+    poly_moments(d, dpn, dpt, hb, Ub, Vb, lamb, thb, D, 1, t2);
+    wt[0] = S - (t1[0] + q0);
+    wt[1] = S * Ub - (t1[1] + q1);
+    wt[2] = S * Vb - (t1[2] + (Vb * q0 + v0));
+    B2[0] = t2[0] + q1 - S * Ub;
+    B2[1] = t2[1] + q2 - S * (UUt + thb);
+    B2[2] = t2[2] + (Vb * q1 + v1) - S * Ub * Vb;
+    // the well-balance weights of the acceleration
+    const R D1 = D[2] - Ub * D[1], D2 = D[3] - Ub * D[2];
+    if constexpr (AM == 0) {
+        wt[0] -= iG * dpn * ex;
+        const R q = R(-0.5) * iG;
+        B2[1] += q * dpn * D2;
+        B2[2] += q * (Vb * dpn * D1 + thb * dpt * D[1]);
+    } else {
+        const R gn2 = pn - G * gBn, gt2 = pt - G * gBt;
+        B2[1] += R(0.5) * iG * (2 * Ub * thb * gn2 + dpn * D2);
+        B2[2] += R(1.5) * iG * (Vb * (thb * gn2 + dpn * D1) + thb * (Ub * gt2 + dpt * D[1]));
+    }
+    {
+        const R aA = lamb * wt[0] * ihb;
+        const R bA = 2 * lamb * (wt[1] - Ub * wt[0]) * ihb;
+        const R gA = 2 * lamb * (wt[2] - Vb * wt[0]) * ihb;
+        const R mA = 2 * aA * thb;  // <A>
+        B3[0] = hb * (Ub * mA + bA * thb);
+        B3[1] = hb * (Ub * Ub * mA + 2 * Ub * bA * thb + 4 * aA * thb * thb);
+        B3[2] = hb * (Ub * Vb * mA + Ub * gA * thb + Vb * bA * thb);
+    }
+    // collision time (Sec. 4) in units of dt, and the weights of F(dt), F(dt/2) giving the flux and
+    // its time derivative; c01 + c04 = 1 and ct1 + ct4 = 0 exactly (the hydrostatic part of B1 and B4
+    // carries weight 1 in F0 and 0 in Ft)
+    const R pl = sl.h * sl.h, pr = sr.h * sr.h;
+    const R r = eps + eps_num * fabs(div_(pl - pr, pl + pr));
+    const R E2 = exp_(div_(R(-0.5), r)), E1 = E2 * E2, a1 = 1 - E1, a2 = 1 - E2;
+    // first order: the step's mean flux, c01 + c04 = 1 still, no time derivative
+    const bool o1 = WD && order1;
+    const R c04 = o1 ? r * a1 : r * (4 * a2 - a1), c01 = 1 - c04;
+    const R ct1 = o1 ? R(0) : 4 * r * (2 * a2 - a1), ct4 = -ct1;
+    const R c02 = -r + r * r * (8 * a2 - 2 * a1) - 2 * r * E2 + r * E1;
+    const R ct2 = 4 * (2 * r * r * (a1 - 2 * a2) + r * (E2 - E1));
+    const R c03 = -r + r * r * (4 * a2 - a1), ct3 = 4 * (R(0.25) + r * r * (a1 - 2 * a2));
+    const R c05 = r * (2 + 4 * r) * E2 - r * (1 + r) * E1 - 3 * r * r;
+    const R ct5 = 4 * (r * (1 + r) * E1 - r * (1 + 2 * r) * E2 + r * r);
+    const R idt = div_(R(1), dt);
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        F0[i] = c01 * B1[i] + c04 * B4[i] + dt * (c02 * B2[i] + c03 * B3[i] + c05 * B5[i]);
+        Ft[i] = (ct1 * B1[i] + ct4 * B4[i]) * idt + ct2 * B2[i] + ct3 * B3[i] + ct5 * B5[i];
+    }
+    Wb[0] = hdev;
+    Wb[1] = wb1;
+    Wb[2] = wb2;
+    Wbt[0] = wt[0];
+    Wbt[1] = wt[1];
+    Wbt[2] = wt[2];
+    return false;
+}
+
 // Time derivative of one side's own state (h, m.n, m.t in the local frame) from the shallow-water
 // equations on that side's data: minus the derivative of the normal and tangential fluxes plus
 // h times the acceleration; the pressure term takes the slope of the level (eta1 for the lower
@@ -1348,7 +1520,17 @@ __device__ inline void side_rate(const SideL<R> &q, R G, R *o)
     o[2] = -(U * q.mtn + V * q.mnn - U * V * q.hn) - (R(2) * V * q.mtt - V * V * q.ht + G * h * q.et) + h * q.pt;
 }
 
+// whether a wave of k_flux holds 32 edges of one layer (FP64: the layers take different paths through
+// gks_point64) or 16 edges of both
+template <typename R>
+constexpr bool LAYER_WAVES = sizeof(R) == 8;
+
 // one thread per (edge, Gauss point, layer); the two Gauss points of an edge are adjacent lanes
+//
+// Bound by latency and by the rate of issue: three waves a SIMD (152 registers in FP64), half of the
+// time with no instruction ready, at 690 MB a launch on 520k cells in FP64 (132 us at the rate of a
+// large copy).  The two stages on average, FP64: 520k cells 191 us with gks_point and both layers in
+// a wave, 174 so; 800 cells 7.8, 6.5.  At 128 registers for four waves it spills (209).
 // STAGE 1 (the second stage) writes only what the second update reads: the mass fluxes, the time
 // derivatives, the interface thicknesses and the coupling's Gauss-point thicknesses and rates; the
 // momentum fluxes, the hydrostatic terms and the interface momenta keep the first stage's values.
@@ -1357,210 +1539,31 @@ __device__ inline void side_rate(const SideL<R> &q, R G, R *o)
 // the interface state, right side in eoh rows 6-7 and eom rows 24-33)
 // WD = 1: wet/dry layers (Phys::h_dry > 0): vacuum sides, first-order band edges, dry interfaces;
 // a template argument so that the wet-only path carries none of it
+template <typename R, int AM, int STAGE, int GM, int WD, int LAY>
+__device__ inline void flux_at(const MeshDev &m, const Phys &p, const GpRecs<R> &rec, const R *__restrict__ r0,
+                               const double *__restrict__ gP1, double *__restrict__ eoh, R *__restrict__ eom, int64_t idx)
+{
+    const int g = idx & 1, lay = LAY;
+    const int64_t e = (idx >> 7) * 32 + ((idx & 63) >> 1);
+#include "gks_flux_body.h"
+}
+
 template <typename R, int AM, int STAGE, int GM = 0, int WD = 0>
 __global__ void __launch_bounds__(256) k_flux(MeshDev m, Phys p, GpRecs<R> rec,
                                               const R *__restrict__ r0, const double *__restrict__ gP1,
                                               double *__restrict__ eoh, R *__restrict__ eom)
 {
     const int64_t idx = xcd_block() * blockDim.x + threadIdx.x;
-    const int64_t e = idx >> 2;
-    const int g = idx & 1, lay = (idx >> 1) & 1;  // lay 0: lower layer (h1), 1: upper (h2)
-    if (e >= m.E) return;
-    const int64_t T = m.T, E = m.E;
-    const int sc = m.escen ? (int)GKS_IX(m.escen[e], m.S) : 0;
-    const R dt = (R)p.scal[2 * sc];
-    // a scenario that has reached its end time takes zero-length steps: nothing to evolve (both
-    // lanes of a Gauss-point pair belong to the same edge and leave together)
-    if (p.scal[2 * sc] == 0.0) return;
-    const R chi = (R)p.chi[sc], G = (R)p.G;
-    const int32_t L = GKS_IX(m.eL[e], m.T), Rc = m.eR[e] >= 0 ? GKS_IX(m.eR[e], m.T) : m.eR[e],
-                  sl = m.eslot[e];
-    const int kL = GKS_IX(sl & 3, 3), kR = GKS_IX(sl >> 2, 3);
-    const R *en = tab<R>(m.en), *egB = tab<R>(m.egB);
-    const R nx = en[e], ny = en[E + e], tx = -ny, ty = nx;
-    const double Bg = m.eBgp[g * E + e];
-    const R gBx = egB[e], gBy = egB[E + e];
-    const int hq = lay == 0 ? 1 : 0;   // own thickness in the record (eta1 / h2)
-    const int mq = lay == 0 ? 2 : 0;   // own momenta in the record
-    const int gv = lay == 0 ? 3 : 0;   // own variables' gradients start at paper component gv
-    const int fv = lay == 0 ? 0 : 3;   // the other layer's height drives this layer's force
-    const int ff = lay == 0 ? 1 : 0;   // modelled field index (0: eta1, 1: h2)
-    // nonlinear weight of the force model
-    const R rL = r0[ff * T + L], rR = Rc >= 0 ? r0[ff * T + Rc] : rL;
-    const R wf0 = fmin(R(1), fmin(rL, rR));
-    const R wf = (double)wf0 < W_ONE ? wf0 : R(1);
-    // wet/dry: at an edge of this layer's front band (r0 of its own field 0 on either side) the
-    // evolution is of first order: the sides' states alone, no slopes, no acceleration
-    const bool order1 = WD && (r0[(1 - ff) * T + L] == R(0) || (Rc >= 0 && r0[(1 - ff) * T + Rc] == R(0)));
-    SideL<R> side[2];
-    double h64[2];
-#pragma unroll
-    for (int s = 0; s < 2; s++) {
-        if (s == 1 && Rc < 0) break;
-        const int64_t cell = s == 0 ? L : Rc;
-        const int64_t at = s == 0 ? rec_at(T, cell, kL, g) : rec_at(T, cell, kR, 1 - g);
-        const GpHead<R> *hp = rec.head + at;
-        const R *rm = hp->q, *rg = rec.tail[at].g;
-        double hh = hp->h[hq];
-        const R ex = rg[2 * gv], ey = rg[2 * gv + 1];  // slope of h2, or of eta1
-        R hx = ex, hy = ey;
-        if (lay == 0) {  // eta1 -> h1 with the single-valued bottom at the Gauss point
-            hh -= Bg;
-            hx -= gBx;
-            hy -= gBy;
-        }
-        h64[s] = hh;
-        const R mx = rm[mq], my = rm[mq + 1];
-        const R mxx = rg[2 + 2 * gv], mxy = rg[3 + 2 * gv];
-        const R myx = rg[4 + 2 * gv], myy = rg[5 + 2 * gv];
-        const R fx = rg[2 * fv], fy = rg[2 * fv + 1];
-        // the plane gradient enters only where the weight is below 1 (it is not computed elsewhere)
-        R dfx = fx, dfy = fy;
-        if (wf < R(1)) {
-            const R px1 = (R)gP1[(2 * ff) * T + cell], py1 = (R)gP1[(2 * ff + 1) * T + cell];
-            dfx = wf * fx + (1 - wf) * px1;
-            dfy = wf * fy + (1 - wf) * py1;
-        }
-        R ax, ay;
-        if (lay == 0) {  // lower layer: upper-layer thickness (chi weighted); the bottom part -G gB
-            ax = -chi * G * dfx;  // of its acceleration enters through bottom_moments
-            ay = -chi * G * dfy;
-        } else {         // upper layer: slope of the interface level
-            ax = -G * dfx;
-            ay = -G * dfy;
-        }
-        SideL<R> &q = side[s];
-        // wet/dry: a side at or below h_dry is a vacuum (every term of it an exact zero)
-        const bool vac = WD && !(hh > p.h_dry);
-        if (vac) h64[s] = 0.0;
-        const R h = vac ? R(0) : (R)hh, ih = vac ? R(0) : div_(R(1), h);
-        q.h = h;
-        q.ih = ih;
-        q.U = (mx * nx + my * ny) * ih;
-        q.V = (mx * tx + my * ty) * ih;
-        q.hn = hx * nx + hy * ny;
-        q.ht = hx * tx + hy * ty;
-        q.en = ex * nx + ey * ny;
-        q.et = ex * tx + ey * ty;
-        const R dmn_x = mxx * nx + myx * ny, dmn_y = mxy * nx + myy * ny;  // grad (m . n)
-        const R dmt_x = mxx * tx + myx * ty, dmt_y = mxy * tx + myy * ty;  // grad (m . t)
-        q.mnn = dmn_x * nx + dmn_y * ny;
-        q.mnt = dmn_x * tx + dmn_y * ty;
-        q.mtn = dmt_x * nx + dmt_y * ny;
-        q.mtt = dmt_x * tx + dmt_y * ty;
-        q.pn = ax * nx + ay * ny;
-        q.pt = ax * tx + ay * ty;
-        if (order1) {
-            q.hn = q.ht = q.en = q.et = R(0);
-            q.mnn = q.mnt = q.mtn = q.mtt = R(0);
-            q.pn = q.pt = R(0);
-        }
-    }
-    if (Rc == -1) {  // wall: mirror image of the left side
-        side[1] = side[0];
-        side[1].U = -side[0].U;
-        side[1].hn = -side[0].hn;
-        side[1].en = -side[0].en;
-        side[1].mnt = -side[0].mnt;
-        side[1].mtn = -side[0].mtn;
-        side[1].pn = -side[0].pn;
-        h64[1] = h64[0];
-    } else if (Rc < 0) {  // free boundary: every component extended evenly across the edge
-        side[1] = side[0];
-        side[1].hn = -side[0].hn;
-        side[1].en = -side[0].en;
-        side[1].mnn = -side[0].mnn;
-        side[1].mtn = -side[0].mtn;
-        side[1].pn = -side[0].pn;
-        h64[1] = h64[0];
-    }
-    const double hbase = 0.5 * (h64[0] + h64[1]);
-    // single-valued bottom slope in the local frame (zero normal part at walls by construction)
-    const R gBn = (lay == 0 && !order1) ? gBx * nx + gBy * ny : R(0);
-    const R gBt = (lay == 0 && !order1) ? gBx * tx + gBy * ty : R(0);
-    R F0[3], Ft[3], Wb[3], Wbt[3];
-    const bool dry = gks_point<R, AM, WD>(side[0], side[1], hbase, gBn, gBt, G, (R)p.eps, (R)p.eps_num, dt, F0, Ft,
-                                          Wb, Wbt, order1, p.h_dry);
-    if (Rc == -1) {  // no mass crosses a wall
-        F0[0] = 0;
-        Ft[0] = 0;
-    }
-    // FP64 hydrostatic pieces: interface thickness and 1/2 G hb^2, averaged over the two points
-    // (both zero at a dry interface)
-    const double hb = dry ? 0.0 : hbase + (double)Wb[0];
-    double P = 0.5 * p.G * hb * hb, H = hb, Hc = hbase;
-    P = 0.5 * (P + __shfl_xor(P, 1));
-    H = 0.5 * (H + __shfl_xor(H, 1));
-    // the layer coupling's Gauss-point thickness (Sec. 3.2, Eq. SWE-source-discretization), read as
-    // the mean of the two sides' reconstructed values, and its rate, the mean of the sides' -div(h U)
-    Hc = 0.5 * (Hc + __shfl_xor(Hc, 1));
-    R Hct = R(-0.5) * ((side[0].mnn + side[0].mtt) + (side[1].mnn + side[1].mtt));
-    Hct = R(0.5) * (Hct + __shfl_xor(Hct, 1));
-    // the rest back to the global frame, then averaged over the two Gauss points
-    R out[11];
-    out[0] = F0[0];
-    out[1] = F0[1] * nx + F0[2] * tx;
-    out[2] = F0[1] * ny + F0[2] * ty;
-    out[3] = Ft[0];
-    out[4] = Ft[1] * nx + Ft[2] * tx;
-    out[5] = Ft[1] * ny + Ft[2] * ty;
-    R side_out[5];  // GM = 1: the right side's momenta and rates (the left side's go in out[6..10])
-    if constexpr (GM == 1) {
-        H = h64[0];
-        double Hr = h64[1];
-#pragma unroll
-        for (int s = 0; s < 2; s++) {
-            R r[3];
-            side_rate(side[s], G, r);
-            R *o5 = s == 0 ? out + 6 : side_out;
-            const R mn = side[s].h * side[s].U, mt = side[s].h * side[s].V;
-            o5[0] = mn * nx + mt * tx;
-            o5[1] = mn * ny + mt * ty;
-            o5[2] = r[0];
-            o5[3] = r[1] * nx + r[2] * tx;
-            o5[4] = r[1] * ny + r[2] * ty;
-        }
-        H = 0.5 * (H + __shfl_xor(H, 1));
-        Hr = 0.5 * (Hr + __shfl_xor(Hr, 1));
-#pragma unroll
-        for (int i = 0; i < 5; i++) side_out[i] = R(0.5) * (side_out[i] + __shfl_xor(side_out[i], 1));
-        if (g == 0) eoh[(int64_t)(lay == 0 ? 7 : 6) * E + e] = Hr;
+    if constexpr (LAYER_WAVES<R>) {
+        if (__builtin_amdgcn_readfirstlane((int)(idx >> 6) & 1) == 0)
+            flux_at<R, AM, STAGE, GM, WD, 0>(m, p, rec, r0, gP1, eoh, eom, idx);
+        else
+            flux_at<R, AM, STAGE, GM, WD, 1>(m, p, rec, r0, gP1, eoh, eom, idx);
     } else {
-        out[6] = Wb[1] * nx + Wb[2] * tx;
-        out[7] = Wb[1] * ny + Wb[2] * ty;
-        out[8] = Wbt[0];
-        out[9] = Wbt[1] * nx + Wbt[2] * tx;
-        out[10] = Wbt[1] * ny + Wbt[2] * ty;
-    }
-#pragma unroll
-    for (int i = 0; i < 11; i++) out[i] = R(0.5) * (out[i] + __shfl_xor(out[i], 1));
-    const int o = lay == 0 ? 3 : 0;  // paper component offset of this layer
-    if (g == 0) {
-        if constexpr (STAGE == 0) eoh[(int64_t)(lay == 0 ? 1 : 0) * E + e] = P;
-        eoh[(int64_t)(lay == 0 ? 3 : 2) * E + e] = H;
-        eoh[(int64_t)(lay == 0 ? 5 : 4) * E + e] = Hc;
-#pragma unroll
-        for (int i = 0; i < 3; i++)
-            if (STAGE == 0 || i == 0) eom[(int64_t)(o + i) * E + e] = out[i];      // F0
-#pragma unroll
-        for (int i = 0; i < 3; i++) eom[(int64_t)(6 + o + i) * E + e] = out[3 + i];  // Ft
-    } else {
-        const int mo = lay == 0 ? 2 : 0;
-        if constexpr (STAGE == 0) {
-            eom[(int64_t)(12 + mo) * E + e] = out[6];  // Wb momenta
-            eom[(int64_t)(13 + mo) * E + e] = out[7];
-        }
-#pragma unroll
-        for (int i = 0; i < 3; i++) eom[(int64_t)(16 + o + i) * E + e] = out[8 + i];  // Wbt
-        eom[(int64_t)(lay == 0 ? 23 : 22) * E + e] = Hct;
-        if constexpr (GM == 1) {
-            if constexpr (STAGE == 0) {
-                eom[(int64_t)(24 + mo) * E + e] = side_out[0];
-                eom[(int64_t)(25 + mo) * E + e] = side_out[1];
-            }
-#pragma unroll
-            for (int i = 0; i < 3; i++) eom[(int64_t)(28 + o + i) * E + e] = side_out[2 + i];
-        }
+        constexpr int LAY = -1;
+        const int64_t e = idx >> 2;
+        const int g = idx & 1, lay = (idx >> 1) & 1;  // lay 0: lower layer (h1), 1: upper (h2)
+#include "gks_flux_body.h"
     }
 }
 
