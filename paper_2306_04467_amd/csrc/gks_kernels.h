@@ -964,6 +964,38 @@ __global__ void __launch_bounds__(64, (sizeof(R) == 8 ? 3 : 4)) k_recon(MeshDev 
     }
 }
 
+// a b + k with the constant k in scalar registers (the compiler would copy it to vector registers with
+// two moves an operation)
+__device__ inline double fma_k(double a, double b, double k)
+{
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(k));
+    return r;
+}
+
+// 1/2 erfc(-x) of k_plane.  FP64: from erf(x), which below 1, where almost all flows are, is x + x P(x^2),
+// P interpolated at the Chebyshev nodes (4e-17 of P); beyond, the library's.  FP32 has the library's
+// throughout: another last bit, once in 1e9 values, would show in the mixed path's results (Fit).
+template <typename R>
+__device__ inline double kinetic_fraction(double x)
+{
+    if constexpr (sizeof(R) == 4) return 0.5 * erfc(-x);
+    if (!(fabs(x) <= 1.0)) return 0.5 + 0.5 * erf(x);
+    const double s = x * x;
+    double p = fma_k(s, -7.795898827002142e-10, 1.3720064546777686e-08);
+    p = fma_k(p, s, -1.6208483801871705e-07);
+    p = fma_k(p, s, 1.6447424703317362e-06);
+    p = fma_k(p, s, -1.492473690741966e-05);
+    p = fma_k(p, s, 0.00012055294904839707);
+    p = fma_k(p, s, -0.0008548325975389692);
+    p = fma_k(p, s, 0.0052239776071164225);
+    p = fma_k(p, s, -0.02686617064323777);
+    p = fma_k(p, s, 0.11283791670945006);
+    p = fma_k(p, s, -0.37612638903183543);
+    p = fma_k(p, s, 0.12837916709551256);
+    return 0.5 + 0.5 * fma(x, p, x);
+}
+
 // --------------------------------------------------------------------------------------------
 // interface force modelling (Sec. 2.3): gradient of the plane through the edge-centre heights of eta1
 // (lower-layer velocity) and of h2 (upper-layer velocity), each from the two Gauss points' convex
@@ -979,6 +1011,8 @@ __global__ void __launch_bounds__(64, (sizeof(R) == 8 ? 3 : 4)) k_recon(MeshDev 
 // which costs less than the heights' way through memory and two more launches: between events, three
 // kernels (weights to a mark per cell, heights per edge, planes per cell) took 18.7 us a stage at 800
 // cells FP64 where this one takes 9.5, 20.3 / 11.6 at 80k, 34.2 / 27.0 at 520k.
+// Reading all three edges before the first is used and the short error function: 800 cells 6.9 -> 5.1 us a
+// launch (in a trace), 10k 7.9 -> 5.3, 160k wet/dry 28.8 -> 24.5; 20k FP32, the reading alone, 9.0 -> 8.0.
 template <typename R>
 __global__ void __launch_bounds__(256) k_plane(MeshDev m, Phys p, const GpHead<R> *__restrict__ head,
                                                const R *__restrict__ r0, double *__restrict__ gP1)
@@ -996,38 +1030,73 @@ __global__ void __launch_bounds__(256) k_plane(MeshDev m, Phys p, const GpHead<R
     // field 0: eta1 with the lower layer's momentum; 1: h2 with the upper layer's
     const int hq = f == 0 ? 1 : 0, mq = f == 0 ? 2 : 0;
     const R *en = tab<R>(m.en);
-    double sx = 0, sy = 0;
+    // all three edges' reads are under way before any is used: a branch at the first (a wall, the error
+    // function) would hold back the others'
+    int64_t e[3];
+    int32_t L[3], Rc[3], sl[3];
 #pragma unroll
     for (int k = 0; k < 3; k++) {
         const int32_t code = m.cedge[k * T + c];
-        const int64_t e = GKS_IX(code >= 0 ? code : ~code, E);
-        const int32_t L = GKS_IX(m.eL[e], T), Rc = m.eR[e] >= 0 ? GKS_IX(m.eR[e], T) : m.eR[e], sl = m.eslot[e];
-        const double nx = en[e], ny = en[E + e], Bg = m.eBgp[g * E + e];
-        const GpHead<R> ql = head[rec_at(T, L, GKS_IX(sl & 3, 3), g)];
-        GpHead<R> qr = ql;
-        if (Rc >= 0) qr = head[rec_at(T, Rc, GKS_IX(sl >> 2, 3), 1 - g)];
+        e[k] = GKS_IX(code >= 0 ? code : ~code, E);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        L[k] = GKS_IX(m.eL[e[k]], T);
+        Rc[k] = m.eR[e[k]] >= 0 ? GKS_IX(m.eR[e[k]], T) : m.eR[e[k]];
+        sl[k] = m.eslot[e[k]];
+    }
+    double geo[3][5], z[3][2];  // normal, bottom, Green-Gauss weights; the sides' levels
+    R q[3][4];                  // their momenta
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        const bool in = Rc[k] >= 0;  // a boundary edge reads its left cell twice
+        const GpHead<R> *hl = head + rec_at(T, L[k], GKS_IX(sl[k] & 3, 3), g);
+        const GpHead<R> *hr = in ? head + rec_at(T, Rc[k], GKS_IX(sl[k] >> 2, 3), 1 - g) : hl;
+        z[k][0] = hl->h[hq];
+        z[k][1] = hr->h[hq];
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            q[k][i] = hl->q[mq + i];
+            q[k][2 + i] = hr->q[mq + i];
+        }
+        geo[k][0] = en[e[k]];
+        geo[k][1] = en[E + e[k]];
+        geo[k][2] = m.eBgp[g * E + e[k]];
+        geo[k][3] = m.gg[(2 * k) * T + c];
+        geo[k][4] = m.gg[(2 * k + 1) * T + c];
+    }
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        settle(geo[k]);
+        settle(z[k]);
+        settle(q[k]);
+    }
+    double sx = 0, sy = 0;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        const double nx = geo[k][0], ny = geo[k][1], Bg = geo[k][2];
         // a dry side (thickness at or below h_dry, or not positive) has no velocity
-        const double zl = ql.h[hq];
+        const double zl = z[k][0];
         const double hl = f == 0 ? zl - Bg : zl;
-        const double unl = (hl > p.h_dry && hl > 0) ? ((double)ql.q[mq] * nx + (double)ql.q[mq + 1] * ny) / hl : 0.0;
+        const double unl = (hl > p.h_dry && hl > 0) ? ((double)q[k][0] * nx + (double)q[k][1] * ny) / hl : 0.0;
         double zr, hr, unr;
-        if (Rc >= 0) {
-            zr = qr.h[hq];
+        if (Rc[k] >= 0) {
+            zr = z[k][1];
             hr = f == 0 ? zr - Bg : zr;
-            unr = (hr > p.h_dry && hr > 0) ? ((double)qr.q[mq] * nx + (double)qr.q[mq + 1] * ny) / hr : 0.0;
+            unr = (hr > p.h_dry && hr > 0) ? ((double)q[k][2] * nx + (double)q[k][3] * ny) / hr : 0.0;
         } else {  // mirror state across a wall; the same state across a free boundary
             zr = zl;
             hr = hl;
-            unr = Rc == -1 ? -unl : unl;
+            unr = Rc[k] == -1 ? -unl : unl;
         }
         // reading: xi is the kinetic fraction of particles moving from left to right (one half
         // when both sides are dry)
         const double lb = 2.0 / (p.G * (hl + hr));
-        const double xi = (hl + hr > 0) ? 0.5 * erfc(-sqrt(lb) * 0.5 * (unl + unr)) : 0.5;
+        const double xi = (hl + hr > 0) ? kinetic_fraction<R>(sqrt(lb) * 0.5 * (unl + unr)) : 0.5;
         const double hh = xi * zl + (1 - xi) * zr;
         const double h = 0.5 * hh + 0.5 * __shfl_xor(hh, 1);
-        sx += m.gg[(2 * k) * T + c] * h;
-        sy += m.gg[(2 * k + 1) * T + c] * h;
+        sx += geo[k][3] * h;
+        sy += geo[k][4] * h;
     }
     gP1[(2 * f + g) * T + c] = g == 0 ? sx : sy;
 }
