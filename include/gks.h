@@ -264,7 +264,7 @@ typedef enum {
     GKS_KERNEL_PLANE = 3,   /* edge-centre heights and plane gradient of the force model (Sec. 2.3) */
     GKS_KERNEL_FLUX = 4,    /* gas-kinetic evolution at the Gauss points (Sec. 2.2) */
     GKS_KERNEL_UPDATE = 5,  /* gather, sources, S2O4 stage update (Sec. 3.1-3.3) */
-    GKS_KERNEL_DT = 6,      /* CFL time step (Sec. 4) */
+    GKS_KERNEL_DT = 6,      /* wave speeds of a state from the host; a step takes them from its updates */
     GKS_KERNEL_INDICATOR = 7, /* learned smoothness indicator (skip mask of the reconstruction) */
     GKS_KERNEL_COUNT = 8
 } gks_kernel;

@@ -74,7 +74,6 @@ hipError_t upload_f32(const std::vector<double> &h, const void **d, std::vector<
 
 inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
-constexpr int64_t DT_CHUNK = 4096;  // cells per block of the batched time step
 
 // bytes of the head and of the tail of one Gauss-point record
 size_t head_bytes(int prec) { return prec == GKS_FP64 ? sizeof(gks::GpHead<double>) : sizeof(gks::GpHead<float>); }
@@ -114,13 +113,14 @@ struct gks_state {
     void *Gc = nullptr, *rec = nullptr, *r0 = nullptr, *eom = nullptr;  // rec: GpRec[6T]
     double *scal = nullptr, *part = nullptr, *chi = nullptr, *tend = nullptr;
     uint8_t *smooth = nullptr;  // skip mask of the reconstruction (learned indicator)
+    double *speed = nullptr;              // largest wave speeds, up to date between steps (Phys)
+    unsigned long long *smax = nullptr;
     unsigned long long *bad = nullptr;  // first cell updated to a non-finite / non-positive state
     bool src4 = false;          // higher-order layer coupling
     bool gm1 = false;           // discontinuous interface values in the gradient update
     void *src = nullptr;        // its interior correction [8][T] (real), written by the reconstruction
     // threads per block of the edge and cell kernels (per kernel class), chosen by gks_autotune
     int bs[GKS_KERNEL_COUNT] = {256, 192, 256, 256, 256, 256, 256, 256};
-    int nparts = 0;
     // learned indicator: parameters, bf16 copies of the weight matrices, threshold
     bool ind_on = false;
     float ind_thr = 0;
@@ -260,7 +260,7 @@ void launch_update(gks_state *s, int stage, hipStream_t st, const gks::LayerW<R>
 }
 
 template <typename R>
-void launch_stage(gks_state *s, int stage, hipStream_t st)
+void launch_stage(gks_state *s, int stage, int step, hipStream_t st)
 {
     const gks::MeshDev &m = s->md;
     const int in = stage == 0 ? 0 : 1, out = 1 - in;  // the input's ghosts are up to date
@@ -274,7 +274,7 @@ void launch_stage(gks_state *s, int stage, hipStream_t st)
     });
     timed(s, st, GKS_KERNEL_PLANE, [&] {
         const int b = s->bs[GKS_KERNEL_PLANE];
-        hipLaunchKernelGGL(gks::k_plane<R>, dim3(blocks(4 * m.T, b)), dim3(b), 0, st, m, s->p,
+        hipLaunchKernelGGL(gks::k_plane<R>, dim3(blocks(4 * m.T, b) + (step == gks::STEP_NONE ? 0 : gks::step_blocks(m.S))), dim3(b), 0, st, m, s->p, step,
                            (const gks::GpHead<R> *)s->rec, (const R *)s->r0, s->gP1);
     });
     timed(s, st, GKS_KERNEL_FLUX, [&] {
@@ -298,37 +298,39 @@ void launch_stage(gks_state *s, int stage, hipStream_t st)
     });
 }
 
+// the largest wave speeds of a state that did not come from a step: the maxima start at zero
 template <typename R>
-void launch_dt(gks_state *s, hipStream_t st)
+void launch_speed(gks_state *s, hipStream_t st)
 {
     const gks::MeshDev &m = s->md;
     timed(s, st, GKS_KERNEL_DT, [&] {
-        if (m.S == 1) {
-            hipLaunchKernelGGL(gks::k_dt_partial<R>, dim3(s->nparts), dim3(gks::DT_BLOCK), 0, st, m, s->p,
-                               (const gks::LayerW<R> *)s->W[0], s->part);
-            hipLaunchKernelGGL(gks::k_dt_final, dim3(1), dim3(gks::DT_BLOCK), 0, st, m, s->p, s->part, s->nparts);
-        } else {
-            hipLaunchKernelGGL(gks::k_dt_chunk<R>, dim3(m.NCH), dim3(gks::DT_BLOCK), 0, st, m, s->p,
-                               (const gks::LayerW<R> *)s->W[0], s->part);
-            hipLaunchKernelGGL(gks::k_dt_scenario, dim3(m.S), dim3(64), 0, st, m, s->p, s->part);
-        }
+        hipLaunchKernelGGL(gks::k_speed<R>, dim3(blocks(2 * m.T, 256)), dim3(256), 0, st, m, s->p,
+                           (const gks::LayerW<R> *)s->W[0]);
     });
 }
 
-void stage_any(gks_state *s, int stage, hipStream_t st)
+void stage_any(gks_state *s, int stage, int step, hipStream_t st)
 {
     if (s->prec == GKS_FP64)
-        launch_stage<double>(s, stage, st);
+        launch_stage<double>(s, stage, step, st);
     else
-        launch_stage<float>(s, stage, st);
+        launch_stage<float>(s, stage, step, st);
 }
 
-void dt_any(gks_state *s, hipStream_t st)
+// both stages with the CFL step sizes
+void step_any(gks_state *s, hipStream_t st)
 {
+    stage_any(s, 0, gks::STEP_CFL, st);
+    stage_any(s, 1, gks::STEP_NONE, st);
+}
+
+void speeds_any(gks_state *s)
+{
+    hipLaunchKernelGGL(gks::k_clear, dim3(blocks(s->md.S, 256)), dim3(256), 0, s->stream, s->p.smax, (int64_t)s->md.S);
     if (s->prec == GKS_FP64)
-        launch_dt<double>(s, st);
+        launch_speed<double>(s, s->stream);
     else
-        launch_dt<float>(s, st);
+        launch_speed<float>(s, s->stream);
 }
 
 // The least-squares operators as the reconstruction reads them: block-major, each block of
@@ -413,22 +415,8 @@ gks_status upload_mesh(gks_mesh *m)
     if (h.S > 1) {
         up(h.cscen, &d.cscen);
         up(h.escen, &d.escen);
-        // time-step chunks: at most DT_CHUNK cells, never across a scenario boundary
-        std::vector<int64_t> cb{0};
-        std::vector<int32_t> sc0{0};
-        for (int32_t sn = 0; sn < h.S; sn++) {
-            for (int64_t c = h.scell[sn] + DT_CHUNK; c < h.scell[sn + 1]; c += DT_CHUNK) cb.push_back(c);
-            cb.push_back(h.scell[sn + 1]);
-            sc0.push_back((int32_t)cb.size() - 1);
-        }
-        d.NCH = (int32_t)cb.size() - 1;
-        up(cb, &d.cb);
-        up(sc0, &d.sc0);
     } else {
         d.cscen = d.escen = nullptr;
-        d.cb = nullptr;
-        d.sc0 = nullptr;
-        d.NCH = 0;
     }
     if (e != hipSuccess) return fail(GKS_ENOMEM, std::string("mesh upload: ") + hipGetErrorString(e));
     m->d32 = d;
@@ -643,12 +631,13 @@ void move_checkpoint(const gks_state *s, bool to_state, void *raw)
     if (s->prec == GKS_FP64) go(double()); else go(float());
 }
 
-// ghost cells of a state that was written from the host; every update after that writes them itself
-gks_status fill_ghosts(gks_state *s)
+// ghost cells and wave speeds of a state that was written from the host; every update after that
+// leaves them itself
+gks_status complete(gks_state *s)
 {
     const gks::MeshDev &m = s->md;
-    if (m.NG == 0) return GKS_OK;
-    timed(s, s->stream, GKS_KERNEL_GHOST, [&] {
+    speeds_any(s);
+    if (m.NG > 0) timed(s, s->stream, GKS_KERNEL_GHOST, [&] {
         const int b = s->bs[GKS_KERNEL_GHOST];
         const dim3 g(blocks(m.NG, b)), t(b);
         if (s->prec == GKS_FP64)
@@ -804,7 +793,6 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
         s->gm1 = prm[0].grad_mode == 1;
         s->md = prec == GKS_FP64 ? mesh->d64 : mesh->d32;
         s->stream = (hipStream_t)stream;
-        s->nparts = (int)std::min<int64_t>(1024, std::max<int64_t>(1, (T + gks::DT_BLOCK - 1) / gks::DT_BLOCK));
         const size_t rs = prec == GKS_FP64 ? sizeof(double) : sizeof(float);
         const size_t uT = (size_t)T, uTG = (size_t)TG, uE = (size_t)E, uS = (size_t)S;
         struct Buf {
@@ -815,8 +803,9 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
                     {&s->r0, 2 * uT * rs},
                     {(void **)&s->gP1, 4 * uT * 8}, {(void **)&s->eoh, (s->gm1 ? 8 : 6) * uE * 8},
                     {&s->eom, (s->gm1 ? 34 : 24) * uE * rs},
-                    {(void **)&s->scal, 2 * uS * 8}, {(void **)&s->part, 2 * (size_t)std::max<int64_t>(std::max(s->nparts, 1024), mesh->d64.NCH) * 8},
-                    {(void **)&s->chi, uS * 8}, {(void **)&s->tend, uS * 8}, {(void **)&s->bad, 8},
+                    {(void **)&s->scal, 2 * uS * 8}, {(void **)&s->part, 2048 * 8},
+                    {(void **)&s->chi, uS * 8}, {(void **)&s->tend, uS * 8}, {(void **)&s->bad, 8}, {(void **)&s->smax, uS * 8},
+                    {(void **)&s->speed, (uT + 31) / 32 * 8},
                     {&s->src, s->src4 ? 8 * uT * rs : 8}};
         for (auto &b : bufs) {
             hipError_t e = hipMalloc(b.p, std::max<size_t>(b.bytes, 8));
@@ -842,6 +831,8 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
         s->p.chi = s->chi;
         s->p.t_end = s->tend;
         s->p.scal = s->scal;
+        s->p.speed = s->speed;
+        s->p.smax = s->smax;
         s->p.bad = s->bad;
         // a failed copy releases the partly built state
         const gks_status r = [&]() -> gks_status {
@@ -854,7 +845,7 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
             HIP_OK(hipMemcpy(s->bad, &none, 8, hipMemcpyHostToDevice));
             HIP_OK(hipMemset(s->W[1], 0, w_bytes(prec, TG)));
             HIP_OK(hipMemset(s->gW[1], 0, 12 * TG * rs));
-            return fill_ghosts(s);
+            return complete(s);
         }();
         if (r != GKS_OK) {
             gks_state_destroy(s);
@@ -924,18 +915,20 @@ gks_status gks_stage(gks_state *s, int32_t stage, const double *dt)
         if (!s || (stage != 0 && stage != 1)) return fail(GKS_EINVAL, "bad stage arguments");
         if (stage == 1 && !s->half) return fail(GKS_EINVAL, "stage 1 must follow stage 0");
         if (stage == 0 && s->half) return fail(GKS_EINVAL, "stage 0 must follow stage 1");
+        int step = gks::STEP_NONE;
         if (stage == 0) {
             if (dt) {
                 if (s->md.S != 1) return fail(GKS_EINVAL, "an explicit dt needs a single-scenario state");
                 if (!(*dt > 0) || !std::isfinite(*dt)) return fail(GKS_EINVAL, "dt must be positive");
                 hipLaunchKernelGGL(gks::k_set_dt, dim3(1), dim3(1), 0, s->stream, s->p, *dt);
+                step = gks::STEP_GIVEN;
             } else {
-                dt_any(s, s->stream);
+                step = gks::STEP_CFL;
             }
         } else if (dt) {
             return fail(GKS_EINVAL, "stage 1 reuses the step size of stage 0");
         }
-        stage_any(s, stage, s->stream);
+        stage_any(s, stage, step, s->stream);
         HIP_OK(hipGetLastError());
         s->half = stage == 0;
         return GKS_OK;
@@ -948,9 +941,7 @@ gks_status gks_step(gks_state *s, int32_t n_steps, double *dt_last)
         if (!s || n_steps < 0) return fail(GKS_EINVAL, "bad step arguments");
         if (s->half) return fail(GKS_EINVAL, "a step cannot start between stage 0 and stage 1");
         for (int i = 0; i < n_steps; i++) {
-            dt_any(s, s->stream);
-            stage_any(s, 0, s->stream);
-            stage_any(s, 1, s->stream);
+            step_any(s, s->stream);
             HIP_OK(hipGetLastError());
         }
         if (dt_last) {
@@ -978,9 +969,7 @@ gks_status gks_batch_step(gks_state *s, int32_t n_steps)
             HIP_OK(hipEventCreateWithFlags(&s->gev[1], hipEventDisableTiming));
             s->capturing = true;
             HIP_OK(hipStreamBeginCapture(s->gstream, hipStreamCaptureModeThreadLocal));
-            dt_any(s, s->gstream);
-            stage_any(s, 0, s->gstream);
-            stage_any(s, 1, s->gstream);
+            step_any(s, s->gstream);
             hipError_t e = hipStreamEndCapture(s->gstream, &s->graph);
             s->capturing = false;
             HIP_OK(e);
@@ -1230,7 +1219,7 @@ gks_status gks_state_load(gks_state *s, const void *blob, int64_t bytes)
         HIP_OK(hipMemcpy(s->W[1], p, raw_bytes, hipMemcpyHostToDevice));
         move_checkpoint(s, true, s->W[1]);
         HIP_OK(hipGetLastError());
-        const gks_status filled = fill_ghosts(s);  // also where the checkpoint's ghosts are older than its cells
+        const gks_status filled = complete(s);  // also where the checkpoint's ghosts are older than its cells
         if (filled != GKS_OK) return filled;
         HIP_OK(hipStreamSynchronize(s->stream));
         p += raw_bytes;
@@ -1812,13 +1801,12 @@ extern "C" gks_status gks_autotune(gks_state *s, int32_t reps, int32_t *chosen)
                 for (int b : cand) {
                     s->bs[k] = b;
                     copy(true);
+                    speeds_any(s);
                     s->prof.clear();
                     s->ev_used = 0;
                     s->prof_on = true;
                     for (int i = 0; i < reps; i++) {
-                        dt_any(s, s->stream);
-                        stage_any(s, 0, s->stream);
-                        stage_any(s, 1, s->stream);
+                        step_any(s, s->stream);
                     }
                     if (hipStreamSynchronize(s->stream) != hipSuccess) {
                         r = fail(GKS_EDEVICE, "autotune run failed");
@@ -1840,6 +1828,7 @@ extern "C" gks_status gks_autotune(gks_state *s, int32_t reps, int32_t *chosen)
                 if (r != GKS_OK) break;
             }
             copy(true);
+            speeds_any(s);
             (void)hipStreamSynchronize(s->stream);
         }
         s->prof.clear();

@@ -41,11 +41,6 @@ struct MeshDev {
     const int32_t *cedge, *sten, *eL, *eR, *eslot, *gsrc;
     const int32_t *gfirst, *gof;    // ghosts gof[gfirst[c] .. gfirst[c + 1]) mirror cell c
     const int32_t *cscen, *escen;   // scenario of each cell / edge, nullptr when S == 1
-    // batches: the cells cut into chunks that never straddle two scenarios, chunk c covering
-    // [cb[c], cb[c + 1]); scenario s owns chunks [sc0[s], sc0[s + 1])
-    const int64_t *cb;
-    const int32_t *sc0;
-    int32_t NCH;
     const int64_t *scell;           // [S + 1] first cell of each scenario
 };
 
@@ -57,6 +52,11 @@ struct Phys {
     const double *chi;    // [S] density ratio
     const double *t_end;  // [S]
     double *scal;         // [2S] per scenario: dt of the current step, time at its end
+    // the state's largest wave speeds, left by the second stage's update for the next step: per wave of 32
+    // cells of one scenario, and per scenario, as the bits of a non-negative double (whose order is that of
+    // the value), the waves that hold a border or the mesh's end (cleared by the step that uses them)
+    double *speed;             // [ceil(T / 32)]
+    unsigned long long *smax;  // [S]
     unsigned long long *bad;  // smallest cell whose updated state is non-finite or has a layer
                               // thickness <= 0 (all ones: none), kept until the state is reloaded
 };
@@ -122,9 +122,9 @@ __device__ inline int64_t checked_index(int64_t i, int64_t n)
 // gathers then hit the same L2 instead of being fetched from HBM by several XCDs.
 constexpr int N_XCD = 8;
 
-__device__ inline int64_t xcd_block()
+__device__ inline int64_t xcd_block(unsigned extra = 0)  // blocks of another kind before the kernel's own
 {
-    const int64_t b = blockIdx.x, nb = gridDim.x;
+    const int64_t b = blockIdx.x - extra, nb = gridDim.x - extra;
     const int64_t q = nb / N_XCD, r = nb % N_XCD, x = b % N_XCD, j = b / N_XCD;
     return x * q + (x < r ? x : r) + j;
 }
@@ -997,6 +997,99 @@ __device__ inline double kinetic_fraction(double x)
 }
 
 // --------------------------------------------------------------------------------------------
+// time step
+
+// a layer's |U| + sqrt(G h); the velocity is desingularised in a thin layer (wet/dry; m / h otherwise)
+// and a dry cell may hold -0
+template <typename R>
+__device__ inline double wave_speed(const Phys &p, double h, const R *mom)
+{
+    const double u = wd_velocity(h, mom[0], p.h_dry), v = wd_velocity(h, mom[1], p.h_dry);
+    return sqrt(u * u + v * v) + sqrt(p.G * fmax(h, 0.0));
+}
+
+// One wave's part of the maxima; a NaN (a state gone bad) does not count.  A whole wave inside one
+// scenario stores its maximum; with one atomic a wave instead, the second update of 180k cells FP32 took
+// 45 us for 22.
+// A wave with a border or with lanes outside the mesh sends atomics, lane by lane.
+__device__ inline void max_speed(const Phys &p, int64_t wave, int sc, double v)
+{
+    v = fmax(v, 0.0);
+    const bool whole = __ballot(sc == __builtin_amdgcn_readfirstlane(sc)) == ~0ull;
+    if (whole) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
+    } else {
+        const unsigned long long bits = __builtin_bit_cast(unsigned long long, v);
+        if (bits > __hip_atomic_load(p.smax + sc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(p.smax + sc, bits);
+        v = 0;
+    }
+    if (__lane_id() == 0) p.speed[wave] = v;
+}
+
+__global__ void __launch_bounds__(256) k_clear(unsigned long long *__restrict__ x, int64_t n)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) x[i] = 0;
+}
+
+// the maxima of a state that did not come from a step (smax holds zeros)
+template <typename R>
+__global__ void __launch_bounds__(256) k_speed(MeshDev m, Phys p, const LayerW<R> *__restrict__ W)
+{
+    const int64_t idx = xcd_block() * blockDim.x + threadIdx.x, c = idx >> 1;
+    const int l = idx & 1;
+    if (c >= m.T) return;
+    const LayerW<R> w = W[2 * c + l];
+    max_speed(p, idx >> 6, m.cscen ? (int)GKS_IX(m.cscen[c], m.S) : 0, wave_speed(p, l ? w.h - m.Bbar[c] : w.h, w.m));
+}
+
+__device__ inline void set_step(const MeshDev &m, const Phys &p, int s, double smax)
+{
+    double dt = p.cfl * m.sdxmin[s] / smax;
+    const double t = p.scal[2 * s + 1];
+    double tn = t + dt;
+    if (tn > p.t_end[s]) {  // the last step ends exactly at t_end; none ever goes back
+        dt = fmax(0.0, p.t_end[s] - t);
+        tn = fmax(t, p.t_end[s]);
+    }
+    p.scal[2 * s] = dt;
+    p.scal[2 * s + 1] = tn;
+}
+
+// what a launch of k_plane does for the step besides the planes
+enum { STEP_NONE = 0, STEP_CFL = 1, STEP_GIVEN = 2 };
+
+__host__ __device__ inline unsigned step_blocks(int S) { return (unsigned)(S + N_XCD - 1) / N_XCD * N_XCD; }
+
+// one block: the step size of scenario s (STEP_CFL); its part of smax is cleared for the next update
+__device__ inline void begin_step(const MeshDev &m, const Phys &p, int step, int s)
+{
+    __shared__ double sh[4];
+    if (step == STEP_CFL) {
+        // the waves whose first cell is the scenario's
+        const int64_t w0 = (m.scell[s] + 31) / 32, w1 = (m.scell[s + 1] + 31) / 32;
+        double v = __builtin_bit_cast(double, p.smax[s]);
+        for (int64_t w = w0 + threadIdx.x; w < w1; w += 8 * blockDim.x) {
+            double x[8];
+#pragma unroll
+            for (int i = 0; i < 8; i++) x[i] = w + i * blockDim.x < w1 ? p.speed[w + i * blockDim.x] : 0.0;
+#pragma unroll
+            for (int i = 0; i < 8; i++) v = fmax(v, x[i]);
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int i = 1; i < (int)(blockDim.x >> 6); i++) v = fmax(v, sh[i]);
+            set_step(m, p, s, v);
+        }
+    }
+    if (threadIdx.x == 0) p.smax[s] = 0;
+}
+
+// --------------------------------------------------------------------------------------------
 // interface force modelling (Sec. 2.3): gradient of the plane through the edge-centre heights of eta1
 // (lower-layer velocity) and of h2 (upper-layer velocity), each from the two Gauss points' convex
 // combinations (FP64: cheap, and the plane through them must be flat at rest)
@@ -1013,11 +1106,22 @@ __device__ inline double kinetic_fraction(double x)
 // cells FP64 where this one takes 9.5, 20.3 / 11.6 at 80k, 34.2 / 27.0 at 520k.
 // Reading all three edges before the first is used and the short error function: 800 cells 6.9 -> 5.1 us a
 // launch (in a trace), 10k 7.9 -> 5.3, 160k wet/dry 28.8 -> 24.5; 20k FP32, the reading alone, 9.0 -> 8.0.
+//
+// In a step's first stage one more block per scenario sets the step size from the largest wave speeds
+// (nothing reads it before the fluxes).  As two kernels of their own over the state, the step sizes cost
+// 5.2 us a step at 800 cells FP64, 13.3 us at 520k, 17.7 us at a million, 19.3 us on an ensemble of 12
+// scenarios; here 2 to 9 us, most of it beside the planes (a million cells: 34.8 -> 38.8 us a launch).
 template <typename R>
-__global__ void __launch_bounds__(256) k_plane(MeshDev m, Phys p, const GpHead<R> *__restrict__ head,
+__global__ void __launch_bounds__(256) k_plane(MeshDev m, Phys p, int step, const GpHead<R> *__restrict__ head,
                                                const R *__restrict__ r0, double *__restrict__ gP1)
 {
-    const int64_t idx = xcd_block() * blockDim.x + threadIdx.x, c = idx >> 2;
+    // those blocks come first, for they take longest, and in eights, so that the others keep their XCDs
+    const unsigned extra = step == STEP_NONE ? 0 : step_blocks(m.S);
+    if (blockIdx.x < extra) {
+        if ((int)blockIdx.x < m.S) begin_step(m, p, step, blockIdx.x);
+        return;
+    }
+    const int64_t idx = xcd_block(extra) * blockDim.x + threadIdx.x, c = idx >> 2;
     if (c >= m.T) return;  // the lanes of a cell leave together, here and below
     const int j = idx & 3, g = j & 1, f = j >> 1;
     const int64_t T = m.T, E = m.E;
@@ -1825,103 +1929,11 @@ __global__ void __launch_bounds__(256) k_update(MeshDev m, Phys p, const double 
     }
     Wout[idx] = w;
     Gout[idx] = g;
+    if constexpr (STAGE == 1) max_speed(p, idx >> 6, sc, wave_speed(p, lower ? w.h - m.Bbar[c] : w.h, w.m));
     if (m.NG > 0) {
         const int32_t j1 = m.gfirst[c + 1];
         for (int32_t j = m.gfirst[c]; j < j1; j++) mirror(m, GKS_IX(m.gof[GKS_IX(j, m.NG)], m.NG), l, w, g, Wout, Gout);
     }
-}
-
-// --------------------------------------------------------------------------------------------
-// time step: per-block maxima of the wave speed, then one block finishes (no atomics); batches of
-// scenarios use one block per scenario
-
-constexpr int DT_BLOCK = 256;
-
-__device__ inline double block_max(double v, double *sh)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) sh[w] = v;
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        v = (lane < (int)(blockDim.x >> 6)) ? sh[lane] : 0.0;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-    }
-    return v;
-}
-
-template <typename R>
-__device__ inline double wave_speed(const MeshDev &m, const Phys &p, const LayerW<R> *W, int64_t c)
-{
-    const LayerW<R> wu = W[2 * c], wl = W[2 * c + 1];
-    const double h2 = wu.h, h1 = wl.h - m.Bbar[c];
-    // velocities desingularised in thin layers (wet/dry; m / h otherwise), a dry cell may hold -0
-    const double u2 = wd_velocity(h2, wu.m[0], p.h_dry), v2 = wd_velocity(h2, wu.m[1], p.h_dry);
-    const double u1 = wd_velocity(h1, wl.m[0], p.h_dry), v1 = wd_velocity(h1, wl.m[1], p.h_dry);
-    const double s1 = sqrt(u1 * u1 + v1 * v1) + sqrt(p.G * fmax(h1, 0.0));
-    const double s2 = sqrt(u2 * u2 + v2 * v2) + sqrt(p.G * fmax(h2, 0.0));
-    return fmax(s1, s2);
-}
-
-template <typename R>
-__global__ void __launch_bounds__(DT_BLOCK) k_dt_partial(MeshDev m, Phys p, const LayerW<R> *__restrict__ W, double *__restrict__ part)
-{
-    __shared__ double sh[DT_BLOCK / 64];
-    double smax = 0;
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < m.T; c += (int64_t)gridDim.x * blockDim.x)
-        smax = fmax(smax, wave_speed(m, p, W, c));
-    smax = block_max(smax, sh);
-    if (threadIdx.x == 0) part[blockIdx.x] = smax;
-}
-
-__device__ inline void set_step(const MeshDev &m, const Phys &p, int s, double smax)
-{
-    double dt = p.cfl * m.sdxmin[s] / smax;
-    const double t = p.scal[2 * s + 1];
-    double tn = t + dt;
-    if (tn > p.t_end[s]) {  // the last step ends exactly at t_end; none ever goes back
-        dt = fmax(0.0, p.t_end[s] - t);
-        tn = fmax(t, p.t_end[s]);
-    }
-    p.scal[2 * s] = dt;
-    p.scal[2 * s + 1] = tn;
-}
-
-__global__ void __launch_bounds__(DT_BLOCK) k_dt_final(MeshDev m, Phys p, const double *__restrict__ part, int nparts)
-{
-    __shared__ double sh[DT_BLOCK / 64];
-    double v = 0;
-    for (int i = threadIdx.x; i < nparts; i += blockDim.x) v = fmax(v, part[i]);
-    v = block_max(v, sh);
-    if (threadIdx.x == 0) set_step(m, p, 0, v);
-}
-
-// batches: one block per chunk of cells (the chunk's largest wave speed), then one block per
-// scenario over its chunks
-template <typename R>
-__global__ void __launch_bounds__(DT_BLOCK) k_dt_chunk(MeshDev m, Phys p, const LayerW<R> *__restrict__ W, double *__restrict__ part)
-{
-    __shared__ double sh[DT_BLOCK / 64];
-    const int ch = blockIdx.x;
-    double smax = 0;
-    const int64_t c0 = GKS_IX(m.cb[ch], m.T + 1), c1 = GKS_IX(m.cb[ch + 1], m.T + 1);
-    for (int64_t c = c0 + threadIdx.x; c < c1; c += blockDim.x)
-        smax = fmax(smax, wave_speed(m, p, W, c));
-    smax = block_max(smax, sh);
-    if (threadIdx.x == 0) part[ch] = smax;
-}
-
-__global__ void __launch_bounds__(64) k_dt_scenario(MeshDev m, Phys p, const double *__restrict__ part)
-{
-    const int s = blockIdx.x;
-    double v = 0;
-    const int i0 = (int)GKS_IX(m.sc0[s], m.NCH + 1), i1 = (int)GKS_IX(m.sc0[s + 1], m.NCH + 1);
-    for (int i = i0 + threadIdx.x; i < i1; i += 64) v = fmax(v, part[i]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-    if (threadIdx.x == 0) set_step(m, p, s, v);
 }
 
 // an explicit step of a single scenario, clipped like the CFL step so that t never passes t_end
