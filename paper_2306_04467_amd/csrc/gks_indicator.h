@@ -202,34 +202,75 @@ __device__ inline f32x4 tile_product(const float *A, int ai, int ak, const float
 // adds the blocks in order (no atomics, the same bits every time).  All products run on the matrix
 // cores in FP32, column block w of every matrix on wave w.
 // What bounds it: a batch of 2048 is 86 MFLOP on 64 blocks, about 2 us of matrix work a block, so
-// launch and LDS latency.  One thread per parameter summing the batch serially (111 waves on the whole chip)
+// launch and memory latency: with the weights, the indices, the rows and the labels read one after the
+// other 19.5 us a batch of 2048, 11.3 with all of it under way at once.  One thread per parameter summing the batch serially (111 waves on the whole chip)
 // and a forward pass on 16 blocks took 526 + 79 us for 2048 samples.
 __global__ void __launch_bounds__(256) k_mlp_batch(const float *__restrict__ P, const float *__restrict__ X,
                                                    const float *__restrict__ Y, const int32_t *__restrict__ idx, int B,
                                                    float *__restrict__ part, float *__restrict__ lpart)
 {
-    __shared__ float w1[MLP_IN * TH], w2[MLP_H * TH], b1[MLP_H], b2[MLP_H], w3[MLP_H];
-    __shared__ float xs[TRAIN_TILE * TX], h1[TRAIN_TILE * TH], h2[TRAIN_TILE * TH], d1[TRAIN_TILE * TH],
+    __shared__ alignas(16) float w1[MLP_IN * TH], w2[MLP_H * TH], xs[TRAIN_TILE * TX];
+    __shared__ float b1[MLP_H], b2[MLP_H], w3[MLP_H];
+    __shared__ float h1[TRAIN_TILE * TH], h2[TRAIN_TILE * TH], d1[TRAIN_TILE * TH],
         d2[TRAIN_TILE * TH], dz[TRAIN_TILE], ls[TRAIN_TILE];
     const int t = threadIdx.x, w = t >> 6, lane = t & 63, j0 = 16 * w;
     const int col = lane & 15, row4 = 4 * (lane >> 4);
-    for (int i = t; i < MLP_IN * MLP_H; i += 256) w1[(i / MLP_H) * TH + i % MLP_H] = P[i];
-    for (int i = t; i < MLP_H * MLP_H; i += 256) w2[(i / MLP_H) * TH + i % MLP_H] = P[OFF_W2 + i];
-    if (t < MLP_H) {
-        b1[t] = P[OFF_B1 + t];
-        b2[t] = P[OFF_B2 + t];
-        w3[t] = P[OFF_W3 + t];
-    }
+    // everything the block reads is under way before any of it is stored: the tile's rows and labels (whose
+    // indices come first) and the weights, in 16-byte words
+    constexpr int XV = TRAIN_TILE * 12, V1 = MLP_IN * MLP_H / 4, V2 = MLP_H * MLP_H / 4;  // words (12 a row, the last 0)
+    static_assert(MLP_IN % 4 == 0 && MLP_H % 4 == 0 && OFF_W2 % 4 == 0 && TX % 4 == 0 && TH % 4 == 0, "16-byte words");
+    f32x4 xv[(XV + 255) / 256];
+    float yv = 0.f;
+    auto load_tile = [&](int tile) {
+        const int s0 = tile * TRAIN_TILE, ns = B - s0 < TRAIN_TILE ? B - s0 : TRAIN_TILE;
+        int row[(XV + 255) / 256];
+#pragma unroll
+        for (int j = 0; j < (XV + 255) / 256; j++) {
+            const int r = (t + 256 * j) / 12, k = (t + 256 * j) % 12;
+            row[j] = r < ns && k < MLP_IN / 4 ? idx[s0 + r] : -1;
+        }
+        const int ry = (t >> 3) < ns ? idx[s0 + (t >> 3)] : -1;
+#pragma unroll
+        for (int j = 0; j < (XV + 255) / 256; j++)
+            xv[j] = row[j] >= 0 ? reinterpret_cast<const f32x4 *>(X + (int64_t)row[j] * MLP_IN)[(t + 256 * j) % 12] : f32x4{0};
+        yv = ry >= 0 ? Y[ry] : 0.f;
+    };
+    f32x4 v1[(V1 + 255) / 256], v2[V2 / 256];
+#pragma unroll
+    for (int j = 0; j < (V1 + 255) / 256; j++)
+        if (t + 256 * j < V1) v1[j] = reinterpret_cast<const f32x4 *>(P)[t + 256 * j];
+#pragma unroll
+    for (int j = 0; j < V2 / 256; j++) v2[j] = reinterpret_cast<const f32x4 *>(P + OFF_W2)[t + 256 * j];
     const float b3 = P[OFF_B3];
+    const float p1 = P[OFF_B1 + (t & 63)], p2 = P[OFF_B2 + (t & 63)], p3 = P[OFF_W3 + (t & 63)];
+    load_tile(blockIdx.x);
+#pragma unroll
+    for (int j = 0; j < (V1 + 255) / 256; j++) {
+        const int i = t + 256 * j;
+        if (i < V1) *reinterpret_cast<f32x4 *>(w1 + (i / (MLP_H / 4)) * TH + 4 * (i % (MLP_H / 4))) = v1[j];
+    }
+#pragma unroll
+    for (int j = 0; j < V2 / 256; j++) {
+        const int i = t + 256 * j;
+        *reinterpret_cast<f32x4 *>(w2 + (i / (MLP_H / 4)) * TH + 4 * (i % (MLP_H / 4))) = v2[j];
+    }
+    if (t < MLP_H) {
+        b1[t] = p1;
+        b2[t] = p2;
+        w3[t] = p3;
+    }
     f32x4 g1[3] = {}, g2[4] = {};  // column block w of dW1 (44 rows padded to 48) and dW2
     float gb = 0.f;                // threads 0..63 db1, 64..127 db2, 128..191 dw3, 192 db3, 193 the loss
     for (int tile = blockIdx.x; tile * TRAIN_TILE < B; tile += gridDim.x) {
         const int s0 = tile * TRAIN_TILE, ns = B - s0 < TRAIN_TILE ? B - s0 : TRAIN_TILE;
         __syncthreads();
-        for (int i = t; i < TRAIN_TILE * 48; i += 256) {
-            const int r = i / 48, k = i % 48;
-            xs[r * TX + k] = (r < ns && k < MLP_IN) ? X[(int64_t)idx[s0 + r] * MLP_IN + k] : 0.f;
+#pragma unroll
+        for (int j = 0; j < (XV + 255) / 256; j++) {
+            const int i = t + 256 * j;
+            if (i < XV) *reinterpret_cast<f32x4 *>(xs + (i / 12) * TX + 4 * (i % 12)) = xv[j];
         }
+        const float y = yv;
+        if ((tile + gridDim.x) * TRAIN_TILE < B) load_tile(tile + gridDim.x);
         __syncthreads();
 #pragma unroll
         for (int rb = 0; rb < 2; rb++) {
@@ -254,7 +295,6 @@ __global__ void __launch_bounds__(256) k_mlp_batch(const float *__restrict__ P, 
             z += __shfl_xor(z, 2);
             z += __shfl_xor(z, 4);
             z += b3;
-            const float y = s < ns ? Y[idx[s0 + s]] : 0.f;
             // softplus(z) - y z, evaluated without overflow
             const float L = fmaxf(z, 0.f) + log1pf(expf(-fabsf(z))) - y * z;
             const float e = s < ns ? (1.f / (1.f + expf(-z)) - y) / (float)B : 0.f;
@@ -316,6 +356,7 @@ struct AdamArgs {
 
 // the blocks' partial sums in a fixed order: the mean loss, and the gradient (grad not null) or the
 // Adam step with it.  One thread per parameter, thread MLP_NP the loss.
+// Bound by latency: 64 blocks' sums with 8 reads under way 5.1 us, with 32 3.9.
 __global__ void __launch_bounds__(64) k_mlp_reduce(const float *__restrict__ part, const float *__restrict__ lpart, int nb,
                                                    int B, float *__restrict__ loss, float *__restrict__ grad, AdamArgs o)
 {
@@ -325,6 +366,13 @@ __global__ void __launch_bounds__(64) k_mlp_reduce(const float *__restrict__ par
     const int64_t st = p < MLP_NP ? MLP_NP : 1;
     float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     int b = 0;
+    for (; b + 32 <= nb; b += 32) {  // 32 reads ahead of their sums
+        float x[32];
+#pragma unroll
+        for (int k = 0; k < 32; k++) x[k] = q[(b + k) * st];
+#pragma unroll
+        for (int k = 0; k < 32; k++) s[k & 7] += x[k];
+    }
     for (; b + 8 <= nb; b += 8)
 #pragma unroll
         for (int k = 0; k < 8; k++) s[k] += q[(b + k) * st];
