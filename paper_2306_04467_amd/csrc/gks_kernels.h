@@ -966,21 +966,27 @@ __global__ void __launch_bounds__(64, (sizeof(R) == 8 ? 3 : 4)) k_recon(MeshDev 
 
 // a b + k with the constant k in scalar registers (the compiler would copy it to vector registers with
 // two moves an operation)
-__device__ inline double fma_k(double a, double b, double k)
+__host__ __device__ inline double fma_k(double a, double b, double k)
 {
+#ifdef __HIP_DEVICE_COMPILE__
     double r;
     asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(k));
     return r;
+#else
+    return fma(a, b, k);
+#endif
 }
 
-// 1/2 erfc(-x) of k_plane.  FP64: from erf(x), which below 1, where almost all flows are, is x + x P(x^2),
-// P interpolated at the Chebyshev nodes (4e-17 of P); beyond, the library's.  FP32 has the library's
-// throughout: another last bit, once in 1e9 values, would show in the mixed path's results (Fit).
+// 1/2 erfc(-x) of k_plane.  FP64: for -1/2 <= x <= 1, where almost all flows are, 1/2 + erf(x) / 2 with
+// erf(x) = x + x P(x^2), P interpolated at the Chebyshev nodes (4e-17 of P).  Beyond, the library's erfc:
+// below -1/2 the sum would lose the small fraction's digits (8e-16 of it at -1, 4e-9 at -4, all at -6).
+// FP32 has the library's throughout: another last bit, once in 1e9 values, would show in the mixed
+// path's results (Fit).
 template <typename R>
-__device__ inline double kinetic_fraction(double x)
+__host__ __device__ inline double kinetic_fraction(double x)
 {
     if constexpr (sizeof(R) == 4) return 0.5 * erfc(-x);
-    if (!(fabs(x) <= 1.0)) return 0.5 + 0.5 * erf(x);
+    if (!(x >= -0.5 && x <= 1.0)) return 0.5 * erfc(-x);
     const double s = x * x;
     double p = fma_k(s, -7.795898827002142e-10, 1.3720064546777686e-08);
     p = fma_k(p, s, -1.6208483801871705e-07);
