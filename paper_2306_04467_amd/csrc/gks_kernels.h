@@ -75,12 +75,22 @@ constexpr double W_ONE = 1.0 - 1e-12;
 // desingularised (Kurganov and Petrova 2007).
 constexpr double WD_THIN = 1000.0, WD_FRONT = 0.3;
 
+// a b + c d with one order of rounding in every kernel it is inlined into: what a step leaves for the next
+// (ghosts, wave speeds) is also formed from a loaded checkpoint, by other kernels, and has to have the
+// same bits there; left to the compiler, either product may be the one that is fused
+__host__ __device__ inline double fma2(double a, double b, double c, double d)
+{
+#pragma clang fp contract(off)
+    const double q = c * d;
+    return fma(a, b, q);
+}
+
 __host__ __device__ inline double wd_velocity(double h, double m, double h_dry)
 {
     const double hs = WD_THIN * h_dry;
     if (!(h_dry > 0) || h >= hs) return m / h;
     const double h2 = h * h, d2 = hs * hs;
-    return 1.4142135623730950488 * h * m / sqrt(h2 * h2 + d2 * d2);
+    return 1.4142135623730950488 * h * m / sqrt(fma2(d2, d2, h2, h2));
 }
 
 
@@ -192,13 +202,13 @@ __device__ inline void mirror(const MeshDev &m, int64_t g, int l, const LayerW<R
     const double a = m.gR[g], b = m.gR[NG + g], c = m.gR[2 * NG + g], e = m.gR[3 * NG + g];
     const double va = m.gR[4 * NG + g], vb = m.gR[5 * NG + g], vc = m.gR[6 * NG + g], ve = m.gR[7 * NG + g];
     const double mx = w.m[0], my = w.m[1], hx = q.g[0], hy = q.g[1];
-    W[2 * d + l] = {w.h, {(R)(va * mx + vb * my), (R)(vc * mx + ve * my)}};
+    W[2 * d + l] = {w.h, {(R)fma2(va, mx, vb, my), (R)fma2(vc, mx, ve, my)}};
     // momentum gradient G[i][j] = d m_i / d x_j  ->  V G R^T
     const double g00 = q.g[2], g01 = q.g[3], g10 = q.g[4], g11 = q.g[5];
-    const double r00 = va * g00 + vb * g10, r01 = va * g01 + vb * g11;
-    const double r10 = vc * g00 + ve * g10, r11 = vc * g01 + ve * g11;
-    G[2 * d + l] = {{(R)(a * hx + b * hy), (R)(c * hx + e * hy), (R)(r00 * a + r01 * b), (R)(r00 * c + r01 * e),
-                     (R)(r10 * a + r11 * b), (R)(r10 * c + r11 * e)}};
+    const double r00 = fma2(va, g00, vb, g10), r01 = fma2(va, g01, vb, g11);
+    const double r10 = fma2(vc, g00, ve, g10), r11 = fma2(vc, g01, ve, g11);
+    G[2 * d + l] = {{(R)fma2(a, hx, b, hy), (R)fma2(c, hx, e, hy), (R)fma2(r00, a, r01, b), (R)fma2(r00, c, r01, e),
+                     (R)fma2(r10, a, r11, b), (R)fma2(r10, c, r11, e)}};
 }
 
 // all ghosts of a state that did not come from k_update, which writes them along with its cells
@@ -1011,7 +1021,7 @@ template <typename R>
 __device__ inline double wave_speed(const Phys &p, double h, const R *mom)
 {
     const double u = wd_velocity(h, mom[0], p.h_dry), v = wd_velocity(h, mom[1], p.h_dry);
-    return sqrt(u * u + v * v) + sqrt(p.G * fmax(h, 0.0));
+    return sqrt(fma2(u, u, v, v)) + sqrt(p.G * fmax(h, 0.0));
 }
 
 // One wave's part of the maxima; a NaN (a state gone bad) does not count.  A whole wave inside one
