@@ -846,7 +846,10 @@ __global__ void __launch_bounds__(64, (sizeof(R) == 8 ? 3 : 4)) k_recon(MeshDev 
     }
     if (valid) (r0 + c0)[(lower ? 0 : T) + cl] = ratio;
     // the records, one local edge (two points) at a time through LDS; the points' monomials are formed
-    // again and not kept from above (60 registers in FP64)
+    // again and not kept from above (60 registers in FP64).  They lie over other lanes' differences, which
+    // have to be read before: the block is one wave, so the barrier is an order for the compiler and no
+    // instruction
+    __syncthreads();
     settle(vx);
     settle(vy);
     char *lh = reinterpret_cast<char *>(lds) + lane * HS, *lt = reinterpret_cast<char *>(lds) + RECON_CELLS * HS + lane * TS;
