@@ -324,13 +324,13 @@ void step_any(gks_state *s, hipStream_t st)
     stage_any(s, 1, gks::STEP_NONE, st);
 }
 
-void speeds_any(gks_state *s)
+void speeds_any(gks_state *s, hipStream_t st)
 {
-    hipLaunchKernelGGL(gks::k_clear, dim3(blocks(s->md.S, 256)), dim3(256), 0, s->stream, s->p.smax, (int64_t)s->md.S);
+    hipLaunchKernelGGL(gks::k_clear, dim3(blocks(s->md.S, 256)), dim3(256), 0, st, s->p.smax, (int64_t)s->md.S);
     if (s->prec == GKS_FP64)
-        launch_speed<double>(s, s->stream);
+        launch_speed<double>(s, st);
     else
-        launch_speed<float>(s, s->stream);
+        launch_speed<float>(s, st);
 }
 
 // The least-squares operators as the reconstruction reads them: block-major, each block of
@@ -631,24 +631,24 @@ void move_checkpoint(const gks_state *s, bool to_state, void *raw)
     if (s->prec == GKS_FP64) go(double()); else go(float());
 }
 
-// ghost cells and wave speeds of a state that was written from the host; every update after that
-// leaves them itself
-gks_status complete(gks_state *s)
+// ghost cells and wave speeds of a state that was written from the host, on stream st, which is waited
+// for; every update after that leaves them itself
+gks_status complete(gks_state *s, hipStream_t st)
 {
     const gks::MeshDev &m = s->md;
-    speeds_any(s);
-    if (m.NG > 0) timed(s, s->stream, GKS_KERNEL_GHOST, [&] {
+    speeds_any(s, st);
+    if (m.NG > 0) timed(s, st, GKS_KERNEL_GHOST, [&] {
         const int b = s->bs[GKS_KERNEL_GHOST];
         const dim3 g(blocks(m.NG, b)), t(b);
         if (s->prec == GKS_FP64)
-            hipLaunchKernelGGL(gks::k_ghost_fill<double>, g, t, 0, s->stream, m, (gks::LayerW<double> *)s->W[0],
+            hipLaunchKernelGGL(gks::k_ghost_fill<double>, g, t, 0, st, m, (gks::LayerW<double> *)s->W[0],
                                (gks::LayerG<double> *)s->gW[0]);
         else
-            hipLaunchKernelGGL(gks::k_ghost_fill<float>, g, t, 0, s->stream, m, (gks::LayerW<float> *)s->W[0],
+            hipLaunchKernelGGL(gks::k_ghost_fill<float>, g, t, 0, st, m, (gks::LayerW<float> *)s->W[0],
                                (gks::LayerG<float> *)s->gW[0]);
     });
     HIP_OK(hipGetLastError());
-    HIP_OK(hipStreamSynchronize(s->stream));
+    HIP_OK(hipStreamSynchronize(st));
     return GKS_OK;
 }
 
@@ -845,7 +845,9 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
             HIP_OK(hipMemcpy(s->bad, &none, 8, hipMemcpyHostToDevice));
             HIP_OK(hipMemset(s->W[1], 0, w_bytes(prec, TG)));
             HIP_OK(hipMemset(s->gW[1], 0, 12 * TG * rs));
-            return complete(s);
+            // on the null stream, as the copies: the state's own may be one that is being captured, or
+            // hold work that a new state need not wait for
+            return complete(s, nullptr);
         }();
         if (r != GKS_OK) {
             gks_state_destroy(s);
@@ -1219,7 +1221,7 @@ gks_status gks_state_load(gks_state *s, const void *blob, int64_t bytes)
         HIP_OK(hipMemcpy(s->W[1], p, raw_bytes, hipMemcpyHostToDevice));
         move_checkpoint(s, true, s->W[1]);
         HIP_OK(hipGetLastError());
-        const gks_status filled = complete(s);  // also where the checkpoint's ghosts are older than its cells
+        const gks_status filled = complete(s, s->stream);  // also where the checkpoint's ghosts are older than its cells
         if (filled != GKS_OK) return filled;
         HIP_OK(hipStreamSynchronize(s->stream));
         p += raw_bytes;
@@ -1801,7 +1803,7 @@ extern "C" gks_status gks_autotune(gks_state *s, int32_t reps, int32_t *chosen)
                 for (int b : cand) {
                     s->bs[k] = b;
                     copy(true);
-                    speeds_any(s);
+                    speeds_any(s, s->stream);
                     s->prof.clear();
                     s->ev_used = 0;
                     s->prof_on = true;
@@ -1828,7 +1830,7 @@ extern "C" gks_status gks_autotune(gks_state *s, int32_t reps, int32_t *chosen)
                 if (r != GKS_OK) break;
             }
             copy(true);
-            speeds_any(s);
+            speeds_any(s, s->stream);
             (void)hipStreamSynchronize(s->stream);
         }
         s->prof.clear();

@@ -1,0 +1,42 @@
+"""The library's host code on a stub of the HIP calls: what its calls do to streams, devices and memory
+that a single-GPU run does not show.  The stub's kernels do nothing, so no value is looked at."""
+import ctypes
+
+import pytest
+
+import workloads
+from tests import _stub
+
+pytestmark = pytest.mark.skipif(not _stub.HAVE, reason="hipcc or g++ not available")
+
+
+@pytest.fixture(scope="module")
+def lib():
+    return _stub.load()
+
+
+@pytest.fixture
+def stream(lib):
+    _, stub = lib
+    s = stub.stub_stream()
+    yield ctypes.c_void_p(s)
+    stub.stub_stream_free(s)
+
+
+def _state(gks, stream, n=4, **kw):
+    sc = workloads.lake_at_rest(n, perturb=1e-2, seed=1)
+    return gks.State.from_scenario(gks.Mesh.from_scenario(sc), sc, stream=stream, **kw)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_a_new_state_leaves_its_stream_alone(lib, stream, precision):
+    """Initial data are copied without the state's stream, which may be one that is being captured or
+    holds other work: completing them puts nothing on it and does not wait for it."""
+    gks, stub = lib
+    stub.stub_capture(stream, 1)
+    stub.stub_reset()
+    st = _state(gks, stream, precision=precision)
+    assert _stub.count(stub, "captured") == 0
+    assert _stub.count(stub, "launches") > 0  # ghosts and wave speeds, elsewhere
+    stub.stub_capture(stream, 0)
+    st.close()
