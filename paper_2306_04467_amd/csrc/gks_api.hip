@@ -482,6 +482,16 @@ void *pinned_page(const gks_state *s)
     return s->pin;
 }
 
+// A stream that is being captured refuses to be waited for: a query says so before it queues anything,
+// which would go into the caller's graph and write to this call's host memory when that is replayed.
+gks_status refuse_capture(const gks_state *s)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
+        HIP_OK(hipStreamSynchronize(s->stream));
+    return GKS_OK;
+}
+
 struct Piece {
     const void *src;  // on the device
     size_t bytes;
@@ -493,6 +503,8 @@ struct Piece {
 // 50 us each).  Call with io_mu held.
 gks_status fetch(const gks_state *s, std::initializer_list<Piece> pieces)
 {
+    const gks_status capture = refuse_capture(s);
+    if (capture != GKS_OK) return capture;
     size_t total = 0;
     for (const Piece &p : pieces) total += p.bytes;
     char *pin = total <= PIN_BYTES ? static_cast<char *>(pinned_page(s)) : nullptr;
@@ -995,10 +1007,8 @@ gks_status gks_state_read(const gks_state *s, double *W, double *gradW, double *
         std::lock_guard<std::mutex> lock(s->io_mu);
         const size_t T = (size_t)s->md.T;
         const int b = s->half ? 1 : 0;
-        // a stream that is being captured refuses to be waited for: say so before anything is queued
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(s->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)
-            HIP_OK(hipStreamSynchronize(s->stream));
+        const gks_status capture = refuse_capture(s);
+        if (capture != GKS_OK) return capture;
         // values [first, last) of the snapshot (W [6][T], then gradW [6][2][T]) are packed on the device
         // in the caller's layout and precision, in one piece, or where the device has no room for that in as
         // many as the state's reduction buffer takes
@@ -1074,6 +1084,8 @@ gks_status gks_state_mass(const gks_state *s, int32_t scen, double mass[2])
         const int64_t c0 = scen < 0 ? 0 : h.scell[scen], c1 = scen < 0 ? h.nt : h.scell[scen + 1];
         constexpr int nb = 256;
         std::lock_guard<std::mutex> lock(s->io_mu);
+        const gks_status capture = refuse_capture(s);
+        if (capture != GKS_OK) return capture;
         launch_mass(s, c0, c1, s->part);
         HIP_OK(hipGetLastError());
         double part[2 * nb];
@@ -1099,6 +1111,8 @@ gks_status gks_state_diagnostics(const gks_state *s, int32_t scen, double out[8]
         constexpr int nb = 256;
         const int b = s->half ? 1 : 0;
         std::lock_guard<std::mutex> lock(s->io_mu);
+        const gks_status capture = refuse_capture(s);
+        if (capture != GKS_OK) return capture;
         launch_mass(s, c0, c1, s->part);
         HIP_OK(hipGetLastError());
         if (s->prec == GKS_FP64)

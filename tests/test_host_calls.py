@@ -40,3 +40,34 @@ def test_a_new_state_leaves_its_stream_alone(lib, stream, precision):
     assert _stub.count(stub, "launches") > 0  # ghosts and wave speeds, elsewhere
     stub.stub_capture(stream, 0)
     st.close()
+
+
+@pytest.mark.parametrize("query", ["time", "mass", "diagnostics", "check", "read"])
+def test_a_query_of_a_captured_stream_queues_nothing(lib, stream, query):
+    """It is refused (such a stream cannot be waited for), and leaves nothing in the caller's graph, least
+    of all a copy into memory of the call."""
+    gks, stub = lib
+    st = _state(gks, stream)
+    getattr(st, query)()
+    stub.stub_capture(stream, 1)
+    stub.stub_reset()
+    with pytest.raises(gks.GksError):
+        getattr(st, query)()
+    assert _stub.count(stub, "captured") == 0
+    stub.stub_capture(stream, 0)
+    getattr(st, query)()
+    st.close()
+
+
+def test_a_step_size_asked_for_under_capture_adds_nothing_to_the_step(lib, stream):
+    gks, stub = lib
+    st = _state(gks, stream)
+    stub.stub_capture(stream, 1)
+    stub.stub_reset()
+    st.step(2)
+    n = _stub.count(stub, "captured")
+    with pytest.raises(gks.GksError):
+        st.step(2, want_dt=True)
+    assert _stub.count(stub, "captured") == 2 * n > 0
+    stub.stub_capture(stream, 0)
+    st.close()
