@@ -469,6 +469,25 @@ void launch_mass(const gks_state *s, int64_t c0, int64_t c1, double *part)
                            (const gks::LayerW<float> *)s->W[b], c0, c1, part);
 }
 
+// makes a device current, and the caller's again at the end of the scope: what only copies works from any
+// thread, and so must what also allocates or launches on its way
+class DeviceScope {
+    int before = 0;
+    bool changed = false;
+
+public:
+    explicit DeviceScope(int device)
+    {
+        if (hipGetDevice(&before) == hipSuccess && before != device) changed = hipSetDevice(device) == hipSuccess;
+    }
+    ~DeviceScope()
+    {
+        if (changed) (void)hipSetDevice(before);
+    }
+    DeviceScope(const DeviceScope &) = delete;
+    DeviceScope &operator=(const DeviceScope &) = delete;
+};
+
 constexpr size_t PIN_BYTES = (size_t)1 << 20;   // the pinned page of a state
 constexpr size_t SLOT_BYTES = (size_t)1 << 20;  // a copying thread's pinned slot
 
@@ -505,6 +524,7 @@ gks_status fetch(const gks_state *s, std::initializer_list<Piece> pieces)
 {
     const gks_status capture = refuse_capture(s);
     if (capture != GKS_OK) return capture;
+    const DeviceScope on(s->mesh->device);
     size_t total = 0;
     for (const Piece &p : pieces) total += p.bytes;
     char *pin = total <= PIN_BYTES ? static_cast<char *>(pinned_page(s)) : nullptr;
@@ -535,7 +555,7 @@ gks_status bad_status(unsigned long long v)
 // by four threads, each copying 1 MiB pieces through a pinned slot on a stream of its own, so that
 // one thread's transfer runs beside the others' writes to the caller's (often untouched) pages.
 // Measured for 75 MiB into fresh pages: 7.5 ms as one hipMemcpy, of which the transfer is 1.4 ms.
-// The snapshot is complete (the stream was waited for) and io_mu is held.
+// The snapshot is complete (the stream was waited for), the device current and io_mu held.
 gks_status copy_out(const gks_state *s, const double *src, void *dst, size_t bytes)
 {
     const char *from = reinterpret_cast<const char *>(src);
@@ -581,11 +601,8 @@ gks_status copy_out(const gks_state *s, const double *src, void *dst, size_t byt
         } catch (const std::exception &) {
             // fewer threads: the others take the rest
         }
-        int dev = 0;
-        const bool have = hipGetDevice(&dev) == hipSuccess;
         work(0);
         for (std::thread &t : pool) t.join();
-        if (have) (void)hipSetDevice(dev);
     }
     HIP_OK((hipError_t)err.load());
     return GKS_OK;
@@ -1004,6 +1021,7 @@ gks_status gks_state_read(const gks_state *s, double *W, double *gradW, double *
 {
     return guarded([&]() -> gks_status {
         if (!s) return fail(GKS_EINVAL, "null state");
+        const DeviceScope on(s->mesh->device);
         std::lock_guard<std::mutex> lock(s->io_mu);
         const size_t T = (size_t)s->md.T;
         const int b = s->half ? 1 : 0;
@@ -1201,6 +1219,7 @@ gks_status gks_state_save(const gks_state *s, void *blob, int64_t bytes)
         unsigned char *p = static_cast<unsigned char *>(blob);
         std::memcpy(p, &hd, sizeof(hd));
         p += sizeof(hd);
+        const DeviceScope on(s->mesh->device);
         HIP_OK(hipStreamSynchronize(s->stream));
         const size_t raw_bytes = 2 * (size_t)TG * 8 + 16 * (size_t)TG * rs;
         // between steps the second stage's input (as large as the checkpoint's arrays) holds nothing
@@ -1230,6 +1249,7 @@ gks_status gks_state_load(gks_state *s, const void *blob, int64_t bytes)
             return fail(GKS_EINVAL, "checkpoint of another mesh or precision");
         const int64_t TG = h.nt + h.ng, rs = s->prec == GKS_FP64 ? 8 : 4;
         const unsigned char *p = static_cast<const unsigned char *>(blob) + sizeof(hd);
+        const DeviceScope on(s->mesh->device);
         HIP_OK(hipStreamSynchronize(s->stream));
         const size_t raw_bytes = 2 * (size_t)TG * 8 + 16 * (size_t)TG * rs;
         HIP_OK(hipMemcpy(s->W[1], p, raw_bytes, hipMemcpyHostToDevice));

@@ -71,3 +71,25 @@ def test_a_step_size_asked_for_under_capture_adds_nothing_to_the_step(lib, strea
     assert _stub.count(stub, "captured") == 2 * n > 0
     stub.stub_capture(stream, 0)
     st.close()
+
+
+@pytest.mark.parametrize("n", [4, 250])  # 250: 125,000 cells, whose snapshot takes the copying threads
+def test_copies_out_and_in_work_from_any_threads_device(lib, stream, n):
+    """A thread of a process with several GPUs starts with device 0: what a read, a checkpoint or a query
+    allocates and launches on its way goes to the state's device, and the thread's stays what it was."""
+    gks, stub = lib
+    stub.hipSetDevice(3)
+    st = _state(gks, stream, n)
+    stub.hipSetDevice(0)
+    stub.stub_expect_device(3)
+    stub.stub_reset()
+    blob = st.save()
+    st.load(blob)
+    for query in ("read", "time", "check"):
+        getattr(st, query)()
+    assert _stub.count(stub, "wrong_device") == 0
+    now = ctypes.c_int(-1)
+    stub.hipGetDevice(ctypes.byref(now))
+    assert now.value == 0
+    stub.stub_expect_device(-1)
+    st.close()
