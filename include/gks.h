@@ -171,7 +171,8 @@ gks_status gks_batch_step(gks_state *st, int32_t n_steps);
 
 /* Copy the latest state to the host (synchronising): W^{n+1/2} between stage 0 and stage 1,
  * otherwise W^n.  W [6][n_tri], gradW [6][2][n_tri] (either may be NULL), t = time of scenario 0
- * (may be NULL). */
+ * (may be NULL).  Reads, checkpoints and queries of one state may come from several threads, one is
+ * served at a time; none may run beside a step or a load of that state. */
 gks_status gks_state_read(const gks_state *st, double *W, double *gradW, double *t);
 /* Time of the latest state and last step size of scenario s (synchronising). */
 gks_status gks_state_time(const gks_state *st, int32_t s, double *t, double *dt);

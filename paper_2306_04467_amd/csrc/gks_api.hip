@@ -108,7 +108,7 @@ struct gks_state {
     hipStream_t stream = nullptr;
     // LayerW[TG][2] and behind it in the same allocation LayerG[TG][2]
     void *W[2] = {nullptr, nullptr}, *gW[2] = {nullptr, nullptr};
-    double *Wc = nullptr, *gP1 = nullptr;
+    double *Wc = nullptr, *gP1 = nullptr;  // Wc: the carry, Gc behind it in the same allocation
     double *eoh = nullptr;
     void *Gc = nullptr, *rec = nullptr, *r0 = nullptr, *eom = nullptr;  // rec: GpRec[6T]
     double *scal = nullptr, *part = nullptr, *chi = nullptr, *tend = nullptr;
@@ -137,12 +137,10 @@ struct gks_state {
     hipGraphExec_t gexec = nullptr;
     hipEvent_t gev[2] = {nullptr, nullptr};
     bool capturing = false;
-    // read-back: the packed snapshot on the device, a pinned host page for what the queries return
-    // and for small snapshots, pinned slots and a stream for each thread that copies a large one
-    // out; made on first use, one query at a time
+    // read-back: a pinned host page for what the queries return and for small snapshots, pinned slots
+    // and a stream for each thread that copies a large one out; made on first use.  One query at a
+    // time: they share the reduction buffer, the idle state buffer and the carry
     mutable std::mutex io_mu;
-    mutable double *snap = nullptr;
-    mutable size_t snap_n = 0;
     mutable void *pin = nullptr;
     struct Lane {
         hipStream_t st = nullptr;
@@ -643,6 +641,18 @@ size_t w_bytes(int prec, int64_t TG)
     return (size_t)(2 * TG) * (prec == GKS_FP64 ? sizeof(gks::LayerW<double>) : sizeof(gks::LayerW<float>));
 }
 
+// bytes of W[i] and gW[i] together
+size_t state_bytes(const gks_state *s)
+{
+    const int64_t TG = s->md.T + s->md.NG;
+    return w_bytes(s->prec, TG) + (size_t)(12 * TG) * (s->prec == GKS_FP64 ? sizeof(double) : sizeof(float));
+}
+
+// The state buffer that holds nothing: between steps the second stage's input, between the stages the
+// second's output.  The next stage writes all of it before any of it is read, and between steps all of
+// the carry, so that what a read or a checkpoint puts there (with io_mu held) costs no memory of its own.
+void *idle_state(const gks_state *s) { return s->W[s->half ? 0 : 1]; }
+
 // the state between the device's layout and a checkpoint's arrays (in device memory)
 void move_checkpoint(const gks_state *s, bool to_state, void *raw)
 {
@@ -828,7 +838,7 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
             void **p;
             size_t bytes;
         } bufs[] = {{&s->W[0], w_bytes(prec, TG) + 12 * uTG * rs}, {&s->W[1], w_bytes(prec, TG) + 12 * uTG * rs},
-                    {(void **)&s->Wc, 6 * uT * 8}, {&s->Gc, 12 * uT * rs}, {&s->rec, 6 * uT * rec_bytes(prec)},
+                    {(void **)&s->Wc, 6 * uT * 8 + 12 * uT * rs}, {&s->rec, 6 * uT * rec_bytes(prec)},
                     {&s->r0, 2 * uT * rs},
                     {(void **)&s->gP1, 4 * uT * 8}, {(void **)&s->eoh, (s->gm1 ? 8 : 6) * uE * 8},
                     {&s->eom, (s->gm1 ? 34 : 24) * uE * rs},
@@ -845,6 +855,7 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
             s->owned.push_back(*b.p);
         }
         for (int i = 0; i < 2; i++) s->gW[i] = static_cast<char *>(s->W[i]) + w_bytes(prec, TG);
+        s->Gc = s->Wc + 6 * uT;
         std::vector<double> chi(S), tend(S), scal(2 * S, 0.0);
         for (int32_t i = 0; i < S; i++) {
             chi[i] = prm[i].chi;
@@ -903,7 +914,6 @@ void gks_state_destroy(gks_state *s)
         if (l.slot) (void)hipHostFree(l.slot);
     }
     if (s->pin) (void)hipHostFree(s->pin);
-    if (s->snap) (void)hipFree(s->snap);
     for (void *p : s->owned) (void)hipFree(p);
     delete s;
 }
@@ -1028,34 +1038,28 @@ gks_status gks_state_read(const gks_state *s, double *W, double *gradW, double *
         const gks_status capture = refuse_capture(s);
         if (capture != GKS_OK) return capture;
         // values [first, last) of the snapshot (W [6][T], then gradW [6][2][T]) are packed on the device
-        // in the caller's layout and precision, in one piece, or where the device has no room for that in as
-        // many as the state's reduction buffer takes
+        // in the caller's layout and precision: W in the idle state buffer and gradW in the carry, or
+        // between the stages, where the carry is in use, both in as many pieces of the former as it takes
+        // (FP64 one, FP32 two)
         const size_t first = W ? 0 : 6 * T, last = gradW ? 18 * T : 6 * T;
-        if (last > first && s->snap_n < 18 * T) {
-            if (hipMalloc((void **)&s->snap, 18 * T * sizeof(double)) == hipSuccess)
-                s->snap_n = 18 * T;
-            else {
-                (void)hipGetLastError();
-                s->snap = nullptr;
-            }
-        }
-        double *buf = s->snap ? s->snap : s->part;
-        const size_t cap_n = s->snap ? s->snap_n : 2048;
+        double *idle = static_cast<double *>(idle_state(s));
+        const size_t cap_n = s->half ? state_bytes(s) / sizeof(double) : 18 * T;
         double sc[2];
         unsigned long long bad = 0;
         for (size_t i0 = first; i0 < last; i0 += cap_n) {
             const size_t i1 = std::min(last, i0 + cap_n);
+            const size_t m0 = std::min(std::max(6 * T, i0), i1);  // W before it, gradW from it on
+            double *bw = idle, *bg = s->half ? idle + (m0 - i0) : s->Wc;
             const dim3 g(blocks((int64_t)(i1 - i0), 256)), n(256);
             if (s->prec == GKS_FP64)
                 hipLaunchKernelGGL(gks::k_snapshot<double>, g, n, 0, s->stream, s->md, (const gks::LayerW<double> *)s->W[b],
-                                   (const gks::LayerG<double> *)s->gW[b], (int64_t)i0, (int64_t)i1, buf);
+                                   (const gks::LayerG<double> *)s->gW[b], (int64_t)i0, (int64_t)m0, (int64_t)i1, bw, bg);
             else
                 hipLaunchKernelGGL(gks::k_snapshot<float>, g, n, 0, s->stream, s->md, (const gks::LayerW<float> *)s->W[b],
-                                   (const gks::LayerG<float> *)s->gW[b], (int64_t)i0, (int64_t)i1, buf);
+                                   (const gks::LayerG<float> *)s->gW[b], (int64_t)i0, (int64_t)m0, (int64_t)i1, bw, bg);
             HIP_OK(hipGetLastError());
-            const size_t m0 = std::min(std::max(6 * T, i0), i1);  // W before it, gradW from it on
-            const Piece pw{buf, (m0 - i0) * 8, m0 > i0 ? W + i0 : nullptr};
-            const Piece pg{buf + (m0 - i0), (i1 - m0) * 8, i1 > m0 ? gradW + (m0 - 6 * T) : nullptr};
+            const Piece pw{bw, (m0 - i0) * 8, m0 > i0 ? W + i0 : nullptr};
+            const Piece pg{bg, (i1 - m0) * 8, i1 > m0 ? gradW + (m0 - 6 * T) : nullptr};
             if (pw.bytes + pg.bytes + sizeof(sc) + sizeof(bad) <= PIN_BYTES) {
                 gks_status r = GKS_OK;
                 if (pw.bytes && pg.bytes)
@@ -1220,14 +1224,14 @@ gks_status gks_state_save(const gks_state *s, void *blob, int64_t bytes)
         std::memcpy(p, &hd, sizeof(hd));
         p += sizeof(hd);
         const DeviceScope on(s->mesh->device);
+        std::lock_guard<std::mutex> lock(s->io_mu);
         HIP_OK(hipStreamSynchronize(s->stream));
-        const size_t raw_bytes = 2 * (size_t)TG * 8 + 16 * (size_t)TG * rs;
-        // between steps the second stage's input (as large as the checkpoint's arrays) holds nothing
-        // that is read again: the arrays are put into the checkpoint's order there
-        move_checkpoint(s, false, s->W[1]);
+        const size_t raw_bytes = 2 * (size_t)TG * 8 + 16 * (size_t)TG * rs;  // all of a state buffer
+        void *raw = idle_state(s);
+        move_checkpoint(s, false, raw);
         HIP_OK(hipGetLastError());
         HIP_OK(hipStreamSynchronize(s->stream));
-        HIP_OK(hipMemcpy(p, s->W[1], raw_bytes, hipMemcpyDeviceToHost));
+        HIP_OK(hipMemcpy(p, raw, raw_bytes, hipMemcpyDeviceToHost));
         p += raw_bytes;
         HIP_OK(hipMemcpy(p, s->scal, 2 * (size_t)h.S * 8, hipMemcpyDeviceToHost));
         p += 2 * (size_t)h.S * 8;

@@ -1998,12 +1998,13 @@ __global__ void __launch_bounds__(256) k_mass_partial(MeshDev m, const LayerW<R>
 }
 
 // values [i0, i1) of the snapshot a caller reads: W [6][T] (h1 = eta1 - B), then gradW [6][2][T]
-// (grad h1 = grad eta1 - grad B), in double, into out[0 .. i1 - i0).  One read and one write per
-// value, coalesced; the host used to unpack and convert them component by component (31 ms on
-// 520,200 cells in FP64, of which the transfer over PCIe is 1.4 ms).
+// (grad h1 = grad eta1 - grad B), in double: those before m0, W's, into outW, those from m0 on, gradW's,
+// into outG.  One read and one write per value, coalesced; the host used to unpack and convert them
+// component by component (31 ms on 520,200 cells in FP64, of which the transfer over PCIe is 1.4 ms).
 template <typename R>
 __global__ void __launch_bounds__(256) k_snapshot(MeshDev m, const LayerW<R> *__restrict__ W, const LayerG<R> *__restrict__ G,
-                                                  int64_t i0, int64_t i1, double *__restrict__ out)
+                                                  int64_t i0, int64_t m0, int64_t i1, double *__restrict__ outW,
+                                                  double *__restrict__ outG)
 {
     const int64_t i = i0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= i1) return;
@@ -2018,7 +2019,8 @@ __global__ void __launch_bounds__(256) k_snapshot(MeshDev m, const LayerW<R> *__
         x = G[2 * c + l].g[q];
         if (l && q < 2) x -= m.gB[q * T + c];
     }
-    out[i - i0] = x;
+    if (i < m0) outW[i - i0] = x;
+    else outG[i - m0] = x;
 }
 
 // Rows of the checkpoint's arrays, between the device's layout and the checkpoint's component-major

@@ -2,6 +2,7 @@
 sizes where the read-back changes its way: one copy through the pinned page up to 1 MiB (7,281
 cells), one plain copy up to 8 MiB of a component block, copying threads beyond."""
 import ctypes
+import threading
 
 import numpy as np
 import pytest
@@ -58,3 +59,34 @@ def test_read_matches_the_checkpoint(gks, n, precision):
     assert lib.gks_state_read(st._h, None, g1.ctypes.data_as(dp), None) == 0
     assert lib.gks_state_read(st._h, None, None, ctypes.byref(t1)) == 0
     assert np.array_equal(W1, W) and np.array_equal(g1, g) and t1.value == t
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("n", [12, 300])
+def test_reading_leaves_the_run_as_it_is(gks, n, precision):
+    """A read or a checkpoint packs into the state buffer that is idle then, between the stages the other
+    one: the run with reads, checkpoints and their threads in between has the bits of the run without."""
+    sc = workloads.lake_at_rest(n, perturb=1e-2, seed=14)
+    mesh = gks.Mesh.from_scenario(sc)
+    a = gks.State.from_scenario(mesh, sc, precision=precision)
+    b = gks.State.from_scenario(mesh, sc, precision=precision)
+    for _ in range(2):
+        a.stage(0)
+        half = [a.read() for _ in range(2)]
+        assert np.array_equal(half[0][0], half[1][0]) and np.array_equal(half[0][1], half[1][1])
+        a.stage(1)
+        saved, read = [], []
+        threads = [threading.Thread(target=lambda: saved.append(a.save())) for _ in range(2)]
+        threads += [threading.Thread(target=lambda: read.append(a.read())) for _ in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert len(saved) == len(read) == 2 and bytes(saved[0]) == bytes(saved[1])
+        assert np.array_equal(read[0][0], read[1][0]) and np.array_equal(read[0][1], read[1][1])
+        b.step(1)
+        want = b.read()
+        assert np.array_equal(read[0][0], want[0]) and np.array_equal(read[0][1], want[1]) and read[0][2] == want[2]
+        c = gks.State.from_scenario(mesh, sc, precision=precision)
+        c.load(saved[0])
+        assert np.array_equal(c.read()[0], want[0])

@@ -93,3 +93,21 @@ def test_copies_out_and_in_work_from_any_threads_device(lib, stream, n):
     assert now.value == 0
     stub.stub_expect_device(-1)
     st.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_reading_back_takes_no_device_memory(lib, stream, precision):
+    """Neither for the call nor afterwards: a state that fills the device can be read and saved."""
+    gks, stub = lib
+    st = _state(gks, stream, precision=precision)
+    held = _stub.count(stub, "device_bytes")
+    for limit in (2 ** 62, 0):
+        stub.stub_malloc_limit(limit)
+        st.read()
+        st.save()
+        st.stage(0)
+        st.read()
+        st.stage(1)
+        assert _stub.count(stub, "device_bytes") == held
+    stub.stub_malloc_limit(2 ** 62)
+    st.close()
