@@ -9,6 +9,7 @@
 #include <atomic>
 #include <exception>
 #include <initializer_list>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -92,12 +93,25 @@ gks::GpRecs<R> recs_of(void *base, int64_t T)
 
 }  // namespace
 
+constexpr size_t MAX_IDLE_PAGES = 8;
+
+// a page of pinned host memory, and where a thread has copied into it on its own, the stream for that
+struct HostPage {
+    void *pin = nullptr;
+    hipStream_t st = nullptr;
+};
+
 struct gks_mesh {
     gks::HostMesh host;             // kept for concatenation into batches and for state conversion
     gks::MeshDev d64{}, d32{};      // device tables; bulk tables as double / as float
     bool has32 = false;
     std::vector<void *> owned;
     int device = 0;
+    // pages that no call of the mesh's states is using, MAX_IDLE_PAGES of them at most
+    mutable std::mutex page_mu;
+    mutable std::vector<HostPage> pages;
+
+    gks_mesh() { pages.reserve(MAX_IDLE_PAGES); }  // giving a page back then allocates nothing
 };
 
 struct gks_state {
@@ -137,16 +151,9 @@ struct gks_state {
     hipGraphExec_t gexec = nullptr;
     hipEvent_t gev[2] = {nullptr, nullptr};
     bool capturing = false;
-    // read-back: a pinned host page for what the queries return and for small snapshots, pinned slots
-    // and a stream for each thread that copies a large one out; made on first use.  One query at a
-    // time: they share the reduction buffer, the idle state buffer and the carry
+    // one query, read or checkpoint at a time: they share the reduction buffer, the idle state buffer and
+    // the carry
     mutable std::mutex io_mu;
-    mutable void *pin = nullptr;
-    struct Lane {
-        hipStream_t st = nullptr;
-        void *slot = nullptr;
-    };
-    mutable Lane lane[4];
     // optional kernel timing: an event pair around every launch, per kernel class
     bool prof_on = false;
     std::vector<hipEvent_t> ev_pool;
@@ -486,18 +493,60 @@ public:
     DeviceScope &operator=(const DeviceScope &) = delete;
 };
 
-constexpr size_t PIN_BYTES = (size_t)1 << 20;   // the pinned page of a state
-constexpr size_t SLOT_BYTES = (size_t)1 << 20;  // a copying thread's pinned slot
+constexpr size_t PAGE_BYTES = (size_t)1 << 20;
+constexpr size_t THREADS_FROM = 8 * PAGE_BYTES;
 
-// the state's pinned page, or null if the host cannot give it
-void *pinned_page(const gks_state *s)
+void free_page(const HostPage &p)
 {
-    if (!s->pin && hipHostMalloc(&s->pin, PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        s->pin = nullptr;
-    }
-    return s->pin;
+    if (p.st) (void)hipStreamDestroy(p.st);
+    if (p.pin) (void)hipHostFree(p.pin);
 }
+
+// A pinned page for the length of a call (pin is null where the host gives none).  The pages belong to the
+// mesh and outlive its states, so that a program that makes a state, reads it and drops it does not pin
+// memory and make streams each time, nor hold them for each of many states.  The mesh's device is current.
+class PageLease {
+    const gks_mesh *mesh;
+    HostPage page;
+
+public:
+    explicit PageLease(const gks_mesh *m) : mesh(m)
+    {
+        {
+            std::lock_guard<std::mutex> lock(m->page_mu);
+            if (!m->pages.empty()) {
+                page = m->pages.back();
+                m->pages.pop_back();
+                return;
+            }
+        }
+        if (hipHostMalloc(&page.pin, PAGE_BYTES, hipHostMallocDefault) != hipSuccess) page.pin = nullptr;
+        if (!page.pin) (void)hipGetLastError();
+    }
+    ~PageLease()
+    {
+        if (!page.pin) return;
+        {
+            std::lock_guard<std::mutex> lock(mesh->page_mu);
+            if (mesh->pages.size() < MAX_IDLE_PAGES) {
+                mesh->pages.push_back(page);
+                return;
+            }
+        }
+        free_page(page);
+    }
+    PageLease(const PageLease &) = delete;
+    PageLease &operator=(const PageLease &) = delete;
+    char *pin() const { return static_cast<char *>(page.pin); }
+    hipStream_t stream()
+    {
+        if (page.pin && !page.st && hipStreamCreateWithFlags(&page.st, hipStreamNonBlocking) != hipSuccess) {
+            page.st = nullptr;
+            (void)hipGetLastError();
+        }
+        return page.st;
+    }
+};
 
 // A stream that is being captured refuses to be waited for: a query says so before it queues anything,
 // which would go into the caller's graph and write to this call's host memory when that is replayed.
@@ -516,7 +565,7 @@ struct Piece {
 };
 
 // A query's small results to the host, after the work queued on the state's stream: the copies are
-// queued into the pinned page and waited for once (a copy to pageable memory waits by itself, 10 to
+// queued into a pinned page and waited for once (a copy to pageable memory waits by itself, 10 to
 // 50 us each).  Call with io_mu held.
 gks_status fetch(const gks_state *s, std::initializer_list<Piece> pieces)
 {
@@ -525,19 +574,23 @@ gks_status fetch(const gks_state *s, std::initializer_list<Piece> pieces)
     const DeviceScope on(s->mesh->device);
     size_t total = 0;
     for (const Piece &p : pieces) total += p.bytes;
-    char *pin = total <= PIN_BYTES ? static_cast<char *>(pinned_page(s)) : nullptr;
+    const PageLease page(s->mesh);
+    if (!page.pin() || total > PAGE_BYTES) {
+        HIP_OK(hipStreamSynchronize(s->stream));
+        for (const Piece &p : pieces) HIP_OK(hipMemcpy(p.dst, p.src, p.bytes, hipMemcpyDeviceToHost));
+        return GKS_OK;
+    }
     size_t off = 0;
     for (const Piece &p : pieces) {
-        HIP_OK(hipMemcpyAsync(pin ? pin + off : p.dst, p.src, p.bytes, hipMemcpyDeviceToHost, s->stream));
+        HIP_OK(hipMemcpyAsync(page.pin() + off, p.src, p.bytes, hipMemcpyDeviceToHost, s->stream));
         off += p.bytes;
     }
     HIP_OK(hipStreamSynchronize(s->stream));
     off = 0;
-    if (pin)
-        for (const Piece &p : pieces) {
-            std::memcpy(p.dst, pin + off, p.bytes);
-            off += p.bytes;
-        }
+    for (const Piece &p : pieces) {
+        std::memcpy(p.dst, page.pin() + off, p.bytes);
+        off += p.bytes;
+    }
     return GKS_OK;
 }
 
@@ -549,45 +602,42 @@ gks_status bad_status(unsigned long long v)
                                     std::to_string(v));
 }
 
-// `bytes` of the packed snapshot to pageable memory.  Up to the pinned page in one copy; beyond that
-// by four threads, each copying 1 MiB pieces through a pinned slot on a stream of its own, so that
-// one thread's transfer runs beside the others' writes to the caller's (often untouched) pages.
-// Measured for 75 MiB into fresh pages: 7.5 ms as one hipMemcpy, of which the transfer is 1.4 ms.
-// The snapshot is complete (the stream was waited for), the device current and io_mu held.
+// `bytes` of a packed snapshot to pageable memory: by four threads, each copying pieces through a pinned
+// page on a stream of its own, so that one thread's transfer runs beside the others' writes to the caller's
+// (often untouched) pages; below THREADS_FROM in one plain copy.  Reads of W and gradW into fresh memory,
+// plain / by threads: 24,200 cells (1.2 and 2.3 MB) 281 / 334 us, 80,000 (3.8 and 7.7 MB) 828 / 642,
+// 180,000 (8.6 and 17 MB) 1,900 / 1,080, a million 12,600 / 4,900.  The line is above where the two meet
+// because the streams of a process's first such read cost 17 ms once.  On one stream in turn the threads
+// take 1,390 us at 180,000 and 5,900 at a million, with pages of 2 MiB 1,240 and 5,060.
+// The snapshot is complete (the stream was waited for), the state's device current and io_mu held.
 gks_status copy_out(const gks_state *s, const double *src, void *dst, size_t bytes)
 {
     const char *from = reinterpret_cast<const char *>(src);
     char *to = static_cast<char *>(dst);
     const int nt = (int)std::min<size_t>(4, std::max<size_t>(1, std::thread::hardware_concurrency()));
-    bool threads = bytes > 8 * SLOT_BYTES && nt > 1;
+    bool threads = bytes > THREADS_FROM && nt > 1;
+    std::vector<std::unique_ptr<PageLease>> page;
     for (int k = 0; threads && k < nt; k++) {
-        gks_state::Lane &l = s->lane[k];
-        if (!l.st && hipStreamCreateWithFlags(&l.st, hipStreamNonBlocking) != hipSuccess) {
-            l.st = nullptr;
-            threads = false;
-        }
-        if (threads && !l.slot && hipHostMalloc(&l.slot, SLOT_BYTES, hipHostMallocDefault) != hipSuccess) {
-            l.slot = nullptr;
-            threads = false;
-        }
+        page.emplace_back(new PageLease(s->mesh));
+        threads = page.back()->stream() != nullptr;
     }
     if (!threads) {
-        (void)hipGetLastError();
         HIP_OK(hipMemcpy(to, from, bytes, hipMemcpyDeviceToHost));
         return GKS_OK;
     }
     std::atomic<size_t> next{0};
     std::atomic<int> err{(int)hipSuccess};
     auto work = [&](int k) {
-        const gks_state::Lane &l = s->lane[k];
+        char *pin = page[(size_t)k]->pin();
+        hipStream_t st = page[(size_t)k]->stream();
         hipError_t e = hipSetDevice(s->mesh->device);
         while (e == hipSuccess && err.load() == (int)hipSuccess) {
-            const size_t off = next.fetch_add(SLOT_BYTES);
+            const size_t off = next.fetch_add(PAGE_BYTES);
             if (off >= bytes) return;
-            const size_t n = std::min(SLOT_BYTES, bytes - off);
-            e = hipMemcpyAsync(l.slot, from + off, n, hipMemcpyDeviceToHost, l.st);
-            if (e == hipSuccess) e = hipStreamSynchronize(l.st);
-            if (e == hipSuccess) std::memcpy(to + off, l.slot, n);
+            const size_t n = std::min(PAGE_BYTES, bytes - off);
+            e = hipMemcpyAsync(pin, from + off, n, hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipStreamSynchronize(st);
+            if (e == hipSuccess) std::memcpy(to + off, pin, n);
         }
         if (e != hipSuccess) err.store((int)e);
     };
@@ -759,6 +809,7 @@ gks_status gks_mesh_batch(const gks_mesh *const *meshes, int32_t n, gks_mesh **o
 void gks_mesh_destroy(gks_mesh *m)
 {
     if (!m) return;
+    for (const HostPage &p : m->pages) free_page(p);
     for (void *p : m->owned) (void)hipFree(p);
     delete m;
 }
@@ -909,11 +960,6 @@ void gks_state_destroy(gks_state *s)
         if (e) (void)hipEventDestroy(e);
     if (s->gstream) (void)hipStreamDestroy(s->gstream);
     for (hipEvent_t e : s->ev_pool) (void)hipEventDestroy(e);
-    for (gks_state::Lane &l : s->lane) {
-        if (l.st) (void)hipStreamDestroy(l.st);
-        if (l.slot) (void)hipHostFree(l.slot);
-    }
-    if (s->pin) (void)hipHostFree(s->pin);
     for (void *p : s->owned) (void)hipFree(p);
     delete s;
 }
@@ -1060,7 +1106,7 @@ gks_status gks_state_read(const gks_state *s, double *W, double *gradW, double *
             HIP_OK(hipGetLastError());
             const Piece pw{bw, (m0 - i0) * 8, m0 > i0 ? W + i0 : nullptr};
             const Piece pg{bg, (i1 - m0) * 8, i1 > m0 ? gradW + (m0 - 6 * T) : nullptr};
-            if (pw.bytes + pg.bytes + sizeof(sc) + sizeof(bad) <= PIN_BYTES) {
+            if (pw.bytes + pg.bytes + sizeof(sc) + sizeof(bad) <= PAGE_BYTES) {
                 gks_status r = GKS_OK;
                 if (pw.bytes && pg.bytes)
                     r = fetch(s, {pw, pg, {s->scal, sizeof(sc), sc}, {s->bad, sizeof(bad), &bad}});

@@ -1,6 +1,7 @@
 """The library's host code on a stub of the HIP calls: what its calls do to streams, devices and memory
 that a single-GPU run does not show.  The stub's kernels do nothing, so no value is looked at."""
 import ctypes
+import threading
 
 import pytest
 
@@ -111,3 +112,31 @@ def test_reading_back_takes_no_device_memory(lib, stream, precision):
         assert _stub.count(stub, "device_bytes") == held
     stub.stub_malloc_limit(2 ** 62)
     st.close()
+
+
+def test_read_back_resources_belong_to_the_mesh(lib, stream):
+    """Pinned pages and streams are made once for a mesh's states, not once for each of them, a bounded
+    number of them is kept, and they go with the mesh."""
+    gks, stub = lib
+    sc = workloads.lake_at_rest(250, perturb=1e-2, seed=1)
+    before = {k: _stub.count(stub, k) for k in ("pinned_bytes", "streams", "device_bytes")}
+    mesh = gks.Mesh.from_scenario(sc)
+    held = []
+    for _ in range(3):
+        states = [gks.State.from_scenario(mesh, sc, stream=stream) for _ in range(2)]
+        for st in states:
+            st.read()
+            st.time()
+        held.append({k: _stub.count(stub, k) for k in ("pinned_bytes", "streams")})
+        threads = [threading.Thread(target=st.read) for st in states for _ in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        for st in states:
+            st.close()
+    assert held[0] == {"pinned_bytes": before["pinned_bytes"] + 4 * 2 ** 20, "streams": before["streams"] + 4}
+    for k, n in (("pinned_bytes", 8 * 2 ** 20), ("streams", 8)):
+        assert _stub.count(stub, k) - before[k] <= n
+    mesh.close()
+    assert {k: _stub.count(stub, k) for k in before} == before
