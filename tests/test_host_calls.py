@@ -140,3 +140,18 @@ def test_read_back_resources_belong_to_the_mesh(lib, stream):
         assert _stub.count(stub, k) - before[k] <= n
     mesh.close()
     assert {k: _stub.count(stub, k) for k in before} == before
+
+
+def test_a_checkpoint_waits_no_more_than_it_has_to(lib, stream):
+    """Small ones once, to save for the arrays in their order, to load for what is formed of the state; one
+    that does not fit a pinned page is loaded after the stream's earlier work."""
+    gks, stub = lib
+    for n, load in ((4, 1), (100, 2)):
+        st = _state(gks, stream, n)
+        stub.stub_reset()
+        blob = st.save()
+        assert _stub.count(stub, "waits") == 1
+        stub.stub_reset()
+        st.load(blob)
+        assert _stub.count(stub, "waits") == load
+        st.close()
