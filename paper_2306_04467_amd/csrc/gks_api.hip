@@ -658,16 +658,16 @@ gks_status copy_out(const gks_state *s, const double *src, void *dst, size_t byt
     return GKS_OK;
 }
 
-// the initial state as the device holds it (ghost cells zero)
+// the initial state as the device holds it (ghost cells zero): LayerW, then LayerG
 template <typename R>
 gks_status device_state(const gks::HostMesh &h, const double *W0, const double *gradW0, bool may_be_dry,
-                        std::vector<unsigned char> &wb, std::vector<unsigned char> &gb)
+                        std::vector<unsigned char> &buf)
 {
     const int64_t T = h.nt, TG = T + h.ng;
-    wb.assign((size_t)(2 * TG) * sizeof(gks::LayerW<R>), 0);
-    gb.assign((size_t)(2 * TG) * sizeof(gks::LayerG<R>), 0);
-    gks::LayerW<R> *w = reinterpret_cast<gks::LayerW<R> *>(wb.data());
-    gks::LayerG<R> *g = reinterpret_cast<gks::LayerG<R> *>(gb.data());
+    const size_t wn = (size_t)(2 * TG) * sizeof(gks::LayerW<R>);
+    buf.assign(wn + (size_t)(2 * TG) * sizeof(gks::LayerG<R>), 0);
+    gks::LayerW<R> *w = reinterpret_cast<gks::LayerW<R> *>(buf.data());
+    gks::LayerG<R> *g = reinterpret_cast<gks::LayerG<R> *>(buf.data() + wn);
     for (int v = 0; v < 6; v++) {
         const int l = v / 3, q = v % 3;
         for (int64_t c = 0; c < T; c++) {
@@ -874,9 +874,9 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
         }
         const int64_t T = h.nt, TG = T + h.ng, E = h.ne;
         // host conversion: the device state carries eta1 = h1 + B and grad(eta1), by cell and layer
-        std::vector<unsigned char> w0, g0;
-        const gks_status conv = prec == GKS_FP64 ? device_state<double>(h, W0, gradW0, prm[0].h_dry > 0, w0, g0)
-                                                 : device_state<float>(h, W0, gradW0, prm[0].h_dry > 0, w0, g0);
+        std::vector<unsigned char> w0;
+        const gks_status conv = prec == GKS_FP64 ? device_state<double>(h, W0, gradW0, prm[0].h_dry > 0, w0)
+                                                 : device_state<float>(h, W0, gradW0, prm[0].h_dry > 0, w0);
         if (conv != GKS_OK) return conv;
         gks_state *s = new gks_state();
         s->mesh = mesh;
@@ -887,6 +887,17 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
         s->stream = (hipStream_t)stream;
         const size_t rs = prec == GKS_FP64 ? sizeof(double) : sizeof(float);
         const size_t uT = (size_t)T, uTG = (size_t)TG, uE = (size_t)E, uS = (size_t)S;
+        // the scenarios' values and the non-finite flag, as they start, in one block and one copy; each on
+        // lines of its own (some are written by atomics beside readers of the others)
+        const size_t line = 256 / 8, sN = (uS + line - 1) / line * line;
+        std::vector<unsigned long long> small(5 * sN + line, 0);
+        auto put = [&](size_t at, double x) { std::memcpy(&small[at], &x, 8); };
+        for (size_t i = 0; i < uS; i++) {  // chi, t_end, then zeros: scal (2 S) and smax
+            put(i, prm[i].chi);
+            put(sN + i, prm[i].t_end > 0 ? prm[i].t_end : 1e300);
+        }
+        small[5 * sN] = ~0ull;
+        unsigned long long *dev = nullptr;
         struct Buf {
             void **p;
             size_t bytes;
@@ -895,8 +906,7 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
                     {&s->r0, 2 * uT * rs},
                     {(void **)&s->gP1, 4 * uT * 8}, {(void **)&s->eoh, (s->gm1 ? 8 : 6) * uE * 8},
                     {&s->eom, (s->gm1 ? 34 : 24) * uE * rs},
-                    {(void **)&s->scal, 2 * uS * 8}, {(void **)&s->part, 2048 * 8},
-                    {(void **)&s->chi, uS * 8}, {(void **)&s->tend, uS * 8}, {(void **)&s->bad, 8}, {(void **)&s->smax, uS * 8},
+                    {(void **)&s->part, 2048 * 8}, {(void **)&dev, small.size() * 8},
                     {(void **)&s->speed, (uT + 31) / 32 * 8},
                     {&s->src, s->src4 ? 8 * uT * rs : 8}};
         for (auto &b : bufs) {
@@ -909,11 +919,11 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
         }
         for (int i = 0; i < 2; i++) s->gW[i] = static_cast<char *>(s->W[i]) + w_bytes(prec, TG);
         s->Gc = s->Wc + 6 * uT;
-        std::vector<double> chi(S), tend(S), scal(2 * S, 0.0);
-        for (int32_t i = 0; i < S; i++) {
-            chi[i] = prm[i].chi;
-            tend[i] = prm[i].t_end > 0 ? prm[i].t_end : 1e300;
-        }
+        s->chi = reinterpret_cast<double *>(dev);
+        s->tend = s->chi + sN;
+        s->scal = s->chi + 2 * sN;
+        s->smax = dev + 4 * sN;
+        s->bad = dev + 5 * sN;
         s->p.G = prm[0].G;
         s->p.eps = prm[0].eps;
         s->p.eps_num = prm[0].eps_num;
@@ -930,14 +940,8 @@ gks_status gks_state_init(const gks_mesh *mesh_c, const gks_params *prm, const d
         // a failed copy releases the partly built state
         const gks_status r = [&]() -> gks_status {
             HIP_OK(hipMemcpy(s->W[0], w0.data(), w0.size(), hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(s->gW[0], g0.data(), g0.size(), hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(s->chi, chi.data(), S * 8, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(s->tend, tend.data(), S * 8, hipMemcpyHostToDevice));
-            HIP_OK(hipMemcpy(s->scal, scal.data(), 2 * S * 8, hipMemcpyHostToDevice));
-            const unsigned long long none = ~0ull;
-            HIP_OK(hipMemcpy(s->bad, &none, 8, hipMemcpyHostToDevice));
-            HIP_OK(hipMemset(s->W[1], 0, w_bytes(prec, TG)));
-            HIP_OK(hipMemset(s->gW[1], 0, 12 * TG * rs));
+            HIP_OK(hipMemcpy(dev, small.data(), small.size() * 8, hipMemcpyHostToDevice));
+            HIP_OK(hipMemset(s->W[1], 0, state_bytes(s)));
             // on the null stream, as the copies: the state's own may be one that is being captured, or
             // hold work that a new state need not wait for
             return complete(s, nullptr);

@@ -155,3 +155,17 @@ def test_a_checkpoint_waits_no_more_than_it_has_to(lib, stream):
         st.load(blob)
         assert _stub.count(stub, "waits") == load
         st.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_a_new_state_copies_twice(lib, stream, precision):
+    """The initial data, and the scenarios' values in one block (each copy is some 8 us, a small state's
+    initialisation is nothing else)."""
+    gks, stub = lib
+    sc = workloads.lake_at_rest(4, perturb=1e-2, seed=1)
+    mesh = gks.Mesh.from_scenario(sc)
+    gks.State.from_scenario(mesh, sc, stream=stream, precision=precision).close()  # the mesh's FP32 tables
+    stub.stub_reset()
+    st = gks.State.from_scenario(mesh, sc, stream=stream, precision=precision)
+    assert _stub.count(stub, "copies") == 2
+    st.close()
