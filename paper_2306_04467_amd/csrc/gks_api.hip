@@ -346,14 +346,21 @@ std::vector<double> operators_block_major(const gks::HostMesh &h)
 {
     const int64_t T = h.nt, C = gks::RECON_CELLS, nb = (T + C - 1) / C, n = gks::OP_LOADS * 4 * C;
     std::vector<double> out((size_t)(nb * n), 0.0);
-    for (int64_t b = 0; b < nb; b++)
-        for (int64_t r = 0; r < 17; r++)
-            for (int64_t k = 0; k < 9; k++) {
-                const int64_t i = 9 * r + k;
-                const double *from = &h.M[(size_t)((k * 17 + r) * T + b * C)];
-                double *to = &out[(size_t)(b * n + (i / 4 * C) * 4 + i % 4)];
-                for (int64_t l = 0; l < C && b * C + l < T; l++) to[4 * l] = from[l];
-            }
+    for (int64_t b = 0; b < nb; b++) {
+        const int64_t cells = std::min(C, T - b * C);
+        for (int64_t j = 0; j < gks::OP_LOADS; j++) {
+            double *to = &out[(size_t)(b * n + j * 4 * C)];
+            const double *from[4] = {};
+            for (int64_t e = 0; e < 4 && 4 * j + e < 9 * 17; e++)
+                from[e] = &h.M[(size_t)(((4 * j + e) % 9 * 17 + (4 * j + e) / 9) * T + b * C)];
+            if (from[3])  // in the order of the writes
+                for (int64_t l = 0; l < cells; l++)
+                    for (int e = 0; e < 4; e++) to[4 * l + e] = from[e][l];
+            else
+                for (int e = 0; e < 4 && from[e]; e++)
+                    for (int64_t l = 0; l < cells; l++) to[4 * l + e] = from[e][l];
+        }
+    }
     return out;
 }
 
@@ -383,16 +390,23 @@ gks_status upload_mesh(gks_mesh *m)
     up(h.eL, &d.eL);
     up(h.eR, &d.eR);
     up(h.eslot, &d.eslot);
-    up(h.gsrc, &d.gsrc);
     {
-        // each cell's ghosts, for the kernel that updates the cell
-        std::vector<int32_t> gfirst((size_t)h.nt + 1, 0), gof((size_t)h.ng);
-        for (int64_t g = 0; g < h.ng; g++) gfirst[(size_t)h.gsrc[g] + 1]++;
-        for (int64_t c = 0; c < h.nt; c++) gfirst[(size_t)c + 1] += gfirst[(size_t)c];
-        std::vector<int32_t> next(gfirst.begin(), gfirst.end() - 1);
-        for (int64_t g = 0; g < h.ng; g++) gof[(size_t)next[(size_t)h.gsrc[g]]++] = (int32_t)g;
-        up(gfirst, &d.gfirst);
-        up(gof, &d.gof);
+        // the ghosts' source cells, then each cell's ghosts, for the kernel that updates the cell
+        const size_t T = (size_t)h.nt, NG = (size_t)h.ng;
+        std::vector<int32_t> ghosts(2 * NG + T + 1, 0), next(T);
+        int32_t *gof = ghosts.data() + NG, *gfirst = gof + NG;
+        for (size_t g = 0; g < NG; g++) {
+            ghosts[g] = h.gsrc[g];
+            gfirst[(size_t)h.gsrc[g] + 1]++;
+        }
+        for (size_t c = 0; c < T; c++) {
+            next[c] = gfirst[c];
+            gfirst[c + 1] += gfirst[c];
+        }
+        for (size_t g = 0; g < NG; g++) gof[next[(size_t)h.gsrc[g]]++] = (int32_t)g;
+        up(ghosts, &d.gsrc);
+        d.gof = d.gsrc + NG;
+        d.gfirst = d.gof + NG;
     }
     up(h.scell, &d.scell);
     up(h.cand, &d.cand);

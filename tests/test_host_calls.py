@@ -169,3 +169,13 @@ def test_a_new_state_copies_twice(lib, stream, precision):
     st = gks.State.from_scenario(mesh, sc, stream=stream, precision=precision)
     assert _stub.count(stub, "copies") == 2
     st.close()
+
+
+def test_a_new_mesh_copies_its_ghost_tables_at_once(lib):
+    """One allocation and one copy a table, and the ghosts' three in one: 23 copies."""
+    gks, stub = lib
+    sc = workloads.lake_at_rest(4, perturb=1e-2, seed=1)
+    stub.stub_reset()
+    mesh = gks.Mesh.from_scenario(sc)
+    assert mesh.n_ghost > 0 and _stub.count(stub, "copies") == 23
+    mesh.close()
