@@ -8,7 +8,7 @@
 //             log10(s / h)/4, and of the layer's momentum variation against h sqrt(G h); then the
 //             face neighbours' area ratios and the cell's edge lengths over hs (static, from the mesh)
 //   inference BF16 MFMA (v_mfma_f32_32x32x16_bf16), FP32 accumulation, 32 cells per wave; the
-//             44 inputs are padded with zeros to 48 (six K-steps of 8)
+//             44 inputs are padded with zeros to 48 (three K-steps of 16)
 //   training  FP32 on the matrix cores: tiles of 32 samples forward, backward and into block-wise
 //             weight-gradient sums, added in a fixed order (deterministic) by the Adam step
 #pragma once
@@ -36,9 +36,10 @@ __device__ inline void field_features(const MeshDev &m, double G, const LayerW<R
     x[18] = mom_feature(fmax(max_diff<R>(rhs[1]), max_diff<R>(rhs[2])), h, G);
 }
 
-// all 44 features of cell c (training export)
+// all 44 features of cell c (training export), 256 threads a block: without the bound the compiler keeps to
+// the 128 registers of a block of 1024, and the three variables' right-hand sides spill in FP64
 template <typename R>
-__global__ void k_features(MeshDev m, double G, const LayerW<R> *__restrict__ W,
+__global__ void __launch_bounds__(256) k_features(MeshDev m, double G, const LayerW<R> *__restrict__ W,
                            const LayerG<R> *__restrict__ gW, float *__restrict__ X)
 {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -117,7 +118,7 @@ __global__ void __launch_bounds__(64 * IND_WAVES) k_indicator(MeshDev m, double 
     }
 }
 
-// the same network on stored feature rows X[n][40] (threshold selection on training samples)
+// the same network on stored feature rows X[n][44] (threshold selection on training samples)
 __global__ void __launch_bounds__(64 * IND_WAVES) k_mlp_infer(const float *__restrict__ X, int64_t n,
                                                                const short *__restrict__ W1b,
                                                                const short *__restrict__ W2b,
