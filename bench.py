@@ -200,7 +200,7 @@ def tune(st):
         return None
     t0 = time.time()
     chosen = st.autotune(reps=3)
-    out = {k: v for k, v in chosen.items() if k in ("ghost", "hhat", "plane", "flux", "update")}
+    out = {k: v for k, v in chosen.items() if k in ("plane", "flux", "update")}
     log(f"autotune {json.dumps(out)} ({time.time() - t0:.1f}s)")
     return out
 

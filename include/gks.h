@@ -335,7 +335,8 @@ gks_status gks_trainer_add_state(gks_trainer *tr, gks_state *st, double tol, int
 /* Number of samples and of label-1 samples (either may be NULL). */
 gks_status gks_trainer_info(const gks_trainer *tr, int64_t *n_samples, int64_t *n_positive);
 /* Mean loss and its gradient [7105] at the current parameters over the samples idx [B] (host),
- * 1 <= B <= max_batch (synchronising).  Sums over the batch run in sample order. */
+ * 1 <= B <= max_batch (synchronising).  Sums over the batch run in a fixed order: the same call gives
+ * the same bits. */
 gks_status gks_trainer_grad(gks_trainer *tr, const int32_t *idx, int32_t B, float *loss, float *grad);
 /* Adam (beta1 0.9, beta2 0.999, eps 1e-8, learning rate lr) over `epochs` passes of minibatches
  * of `batch` samples, the order of each pass a Fisher-Yates shuffle drawn from splitmix64 seeded
@@ -352,8 +353,8 @@ gks_status gks_trainer_logits(gks_trainer *tr, float *logits);
  * max_false_skip * n samples of label 0 would be skipped, with the inference arithmetic. */
 gks_status gks_trainer_threshold(gks_trainer *tr, double max_false_skip, float *threshold);
 
-/* Launch-shape autotuner (for batches and single meshes alike): for the ghost, force-model, flux
- * and update kernels it times `reps` full steps of this state with 64, 128 and 256 threads per
+/* Launch-shape autotuner (for batches and single meshes alike): for the force-model, flux and
+ * update kernels it times `reps` full steps of this state with 64, 128 and 256 threads per
  * block, one kernel class after the other, and keeps the fastest; the state's values, time and
  * step size are restored afterwards (results are independent of the launch shape).  chosen (may be
  * NULL): host [GKS_KERNEL_COUNT] threads per block of each kernel class after tuning.  A captured

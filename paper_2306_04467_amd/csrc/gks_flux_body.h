@@ -1,7 +1,8 @@
 // The body of k_flux: one lane's edge e, Gauss point g and layer lay, in a function with the kernel's
 // parameters and a constant LAY (the wave's layer; -1: the lanes hold both).  It is included and not
-// called: inlined from a function, its FP32 products are contracted into other sums, and the mixed
-// path's results, whose rounding a few obtuse cells amplify, are held to their bits.
+// called: inlined from a function, its FP32 products are contracted into other sums, and a few obtuse
+// cells amplify the mixed path's rounding.  That keeps the bits with one compiler; another may contract
+// the sums otherwise, as their order is not written out.
     if (e >= m.E) return;
     const int64_t T = m.T, E = m.E;
     const int sc = m.escen ? (int)GKS_IX(m.escen[e], m.S) : 0;

@@ -618,18 +618,20 @@ __device__ inline bool wd_band(const MeshDev &m, const Phys &p, const LayerW<R> 
 
 // One wave takes the 32 cells of a block of operators; a lane holds all three variables of its layer.
 //
-// Bound by the rate of issue and by the latency of the scattered reads, at the occupancy that the 27
-// coefficients a lane keeps allow (168 registers, three waves a SIMD in FP64; four in FP32), the
-// operators' stream (1,248 bytes a cell in FP64, 624 in FP32) beneath it.  With the state as one
-// array a variable, 15 scattered 8-byte reads a stencil cell kept the address units 78 % busy, and the
-// operators, staged by a block through LDS behind barriers, the reads, the arithmetic and the records
-// ran one after another (taking any of them out shortened the kernel by its own time).  Hence a layer's
-// averages and gradients each in one piece (one wide read a stencil cell), a wave to itself without a
-// barrier, the operators read straight into registers eight loads ahead and shared between a cell's two
-// lanes by DPP, and the records turned in LDS into whole lines.  520k cells, between events: FP64 285 us
-// before, 228 after; FP32 148, 128; 80k cells FP64 47.7, 39.8.  At 800 cells one wave's chain is all
-// there is, 11.4 before, 13.6 after; 20 loads ahead instead of eight leave that and all sizes unchanged
-// or slower (80k 46.5).
+// On large meshes bound by memory: 520k cells FP64 move 1.29 GB a launch at the rate of a large copy, of
+// which the operators' stream is half (1,248 bytes a cell; 624 in FP32).  On small ones by the rate of
+// issue and the latency of the scattered reads along one wave's chain.  The 27 coefficients a lane keeps
+// allow three waves a SIMD in FP64 (168 registers; where the indicator is evaluated two, 174: its two
+// stages take 272 us on average at 520k cells, 299 before) and four in FP32.
+// Before, with the state as one array a variable, 15 scattered 8-byte reads a stencil cell kept the address
+// units 78 % busy, and the operators, staged by a block through LDS behind barriers, the reads, the
+// arithmetic and the records ran one after another (taking any of them out shortened the kernel by its own
+// time).  Hence a layer's averages and gradients each in one piece (one wide read a stencil cell), a wave
+// to itself whose barriers are no instructions, the operators read straight into registers eight loads
+// ahead and shared between a cell's two lanes by DPP, and the records turned in LDS into whole lines.
+// 520k cells, between events: FP64 285 us before, 228 after; FP32 148, 128; 80k cells FP64 47.7, 39.8.  At
+// 800 cells one wave's chain is all there is, 11.4 before, 13.6 after; 20 loads ahead instead of eight
+// leave that and all sizes unchanged or slower (80k 46.5).
 // IND: the learned indicator decides per cell whether the smoothness indicators are computed.
 // IND = 1: its 44 features come from the right-hand sides the wave has gathered anyway; the wave
 // evaluates the network for its 32 cells on the matrix cores and the decisions go to ind.mask.
@@ -666,8 +668,9 @@ __global__ void __launch_bounds__(64, (sizeof(R) == 8 ? 3 : 4)) k_recon(MeshDev 
     const int64_t blk = xcd_block(), c0 = blk * RECON_CELLS;
     const int ncell = T - c0 < RECON_CELLS ? (int)(T - c0) : RECON_CELLS;
     const bool valid = lane < ncell;
-    // lanes beyond the last cell compute it again and write nothing; a wave's cells lie at a uniform
-    // base plus a small index, so that the tables' addresses stay in scalar registers
+    // lanes beyond the last cell take its state and tables with the zeros that pad the operators, and write
+    // nothing; a wave's cells lie at a uniform base plus a small index, so that the tables' addresses stay
+    // in scalar registers
     const unsigned cl = (valid ? lane : ncell - 1) & (RECON_CELLS - 1);
     const int64_t c = c0 + cl;
     int32_t nb[9];
@@ -1123,8 +1126,8 @@ __device__ inline void begin_step(const MeshDev &m, const Phys &p, int step, int
 // which costs less than the heights' way through memory and two more launches: between events, three
 // kernels (weights to a mark per cell, heights per edge, planes per cell) took 18.7 us a stage at 800
 // cells FP64 where this one takes 9.5, 20.3 / 11.6 at 80k, 34.2 / 27.0 at 520k.
-// Reading all three edges before the first is used and the short error function: 800 cells 6.9 -> 5.1 us a
-// launch (in a trace), 10k 7.9 -> 5.3, 160k wet/dry 28.8 -> 24.5; 20k FP32, the reading alone, 9.0 -> 8.0.
+// Reading all three edges before the first is used and the short error function: 800 cells 6.9 -> 5.5 us a
+// launch (in a trace), 10k 7.9 -> 5.7, 160k wet/dry 28.8 -> 24.7; 20k FP32, the reading alone, 9.0 -> 8.1.
 //
 // In a step's first stage one more block per scenario sets the step size from the largest wave speeds
 // (nothing reads it before the fluxes).  As two kernels of their own over the state, the step sizes cost
@@ -1359,9 +1362,8 @@ __host__ __device__ inline bool gks_point(const SideL<R> &sl, const SideL<R> &sr
                                  double h_dry = 0.0)
 {
     // the bottom's moments are added unconditionally: for the upper layer (and a flat bottom) the
-    // slope is zero and they add exact zeros.  A branch on the slope diverges inside every wave
-    // (lanes of both layers alternate) and kept 56 more registers live (222 against 166 in FP64:
-    // 2 instead of 3 waves per SIMD).
+    // slope is zero and they add exact zeros.  A branch on the slope would diverge inside every wave,
+    // whose lanes alternate between the layers in FP32
     // reciprocals formed once (lam = 1/(G h)); 1/(2 sqrt(pi lam)) = sqrt(lam) th / sqrt(pi)
     const R iG = div_(R(1), G), ihL = sl.ih, ihR = sr.ih;
     const R lamL = iG * ihL, lamR = iG * ihR;
@@ -1774,11 +1776,14 @@ __global__ void __launch_bounds__(256) k_flux(MeshDev m, Phys p, GpRecs<R> rec,
 //
 // Two lanes a cell, lane l layer l (0 upper, 1 lower), the other layer's slopes by a swap in the pair; a
 // cell's lanes also write its ghosts in the new state, so that the next stage starts with the
-// reconstruction.  Bound by memory where the mesh is large: 460 MB at 520k cells FP64 in the first
-// stage, 97 us at the rate of a large copy; the two stages take 108.7 us on average, between events,
-// where one thread a cell and a kernel for the ghosts took 104.3 and 8.9 (180k FP32: 26.8, 25.1 + 6.7;
-// 10k FP64: 9.1, 9.7 + 6.8).  With the ghosts written by one thread a cell, it spills (134.9, 28.5, 14.4);
-// the edges' values in blocks of 16 edges instead of rows change nothing (112.0, 73.0 at 520k FP32 / 72.9).
+// reconstruction, and in the second stage the wave speeds.  Bound by memory where the mesh is large: at
+// 520k cells FP64 the first stage moves 441 MB, 85 us at the rate of a large copy, in 127 us, the second
+// 331 MB, 64 us, in 82.
+// By itself it is slower than one thread a cell was, whose two stages took 104.3 us on average, between
+// events, where these take 108.7 without the wave speeds; the kernel for the ghosts, 8.9, is gone
+// (180k FP32: 26.8, 25.1 + 6.7; 10k FP64: 9.1, 9.7 + 6.8).  With the ghosts written by one thread a cell
+// it spills (134.9, 28.5, 14.4); the edges' values in blocks of 16 edges instead of rows change nothing
+// (112.0, 73.0 at 520k FP32 / 72.9).
 template <typename R, int STAGE, int SRC = 0, int GM = 0>
 __global__ void __launch_bounds__(256) k_update(MeshDev m, Phys p, const double *__restrict__ eoh, const R *__restrict__ eom,
                                                 const LayerW<R> *__restrict__ Win, const LayerG<R> *__restrict__ Gin,
@@ -2023,10 +2028,9 @@ __global__ void __launch_bounds__(256) k_snapshot(MeshDev m, const LayerW<R> *__
     else outG[i - m0] = x;
 }
 
-// Rows of the checkpoint's arrays, between the device's layout and the checkpoint's component-major
-// one: h2 and eta1 [2][TG] in double, the momenta [4][TG], the gradients [12][TG]; the kernel moves values
-// [i0, i1) of the 18 TG, TO_STATE from `raw` into the state, else the other way.  raw holds the first
-// 2 TG values as doubles and the rest as R, from byte 16 TG on.
+// The checkpoint's arrays between the device's layout and the checkpoint's component-major one: h2 and
+// eta1 [2][TG] in double, the momenta [4][TG], the gradients [12][TG]; TO_STATE from `raw` into the state,
+// else the other way.  raw holds the first 2 TG values as doubles and the rest as R, from byte 16 TG on.
 template <typename R, bool TO_STATE>
 __global__ void __launch_bounds__(256) k_checkpoint(MeshDev m, LayerW<R> *__restrict__ W, LayerG<R> *__restrict__ G,
                                                     void *__restrict__ raw)
