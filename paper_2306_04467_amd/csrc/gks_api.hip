@@ -624,7 +624,9 @@ gks_status bad_status(unsigned long long v)
 // plain / by threads: 24,200 cells (1.2 and 2.3 MB) 281 / 334 us, 80,000 (3.8 and 7.7 MB) 828 / 642,
 // 180,000 (8.6 and 17 MB) 1,900 / 1,080, a million 12,600 / 4,900.  The line is above where the two meet
 // because the streams of a process's first such read cost 17 ms once.  On one stream in turn the threads
-// take 1,390 us at 180,000 and 5,900 at a million, with pages of 2 MiB 1,240 and 5,060.
+// take 1,390 us at 180,000 and 5,900 at a million, with pages of 2 MiB 1,240 and 5,060; two threads 1,250 and
+// 6,080, three 1,150 and 5,840, four 1,140 and 5,030, six 1,080 and 4,270, eight 1,080 and 3,990: beyond four
+// each brings little at ordinary sizes and takes a core and a page.
 // The snapshot is complete (the stream was waited for), the state's device current and io_mu held.
 gks_status copy_out(const gks_state *s, const double *src, void *dst, size_t bytes)
 {

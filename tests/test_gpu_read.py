@@ -74,6 +74,10 @@ def test_reading_leaves_the_run_as_it_is(gks, n, precision):
         a.stage(0)
         half = [a.read() for _ in range(2)]
         assert np.array_equal(half[0][0], half[1][0]) and np.array_equal(half[0][1], half[1][1])
+        # alone, the gradients are packed from another value on, in other pieces
+        G = np.zeros_like(half[0][1])
+        assert gks.load().gks_state_read(a._h, None, G.ctypes.data_as(ctypes.POINTER(ctypes.c_double)), None) == 0
+        assert np.array_equal(G, half[0][1])
         a.stage(1)
         saved, read = [], []
         threads = [threading.Thread(target=lambda: saved.append(a.save())) for _ in range(2)]
